@@ -529,7 +529,8 @@ fstat_status launch_chunk(const fstat_plan* p, const PlanConst& P, const double*
   if (!grouped) {
     // the grouped (search) path computed every parameter block up front
     if ((s = tm.open(0)) != FSTAT_OK) return s;
-    hipLaunchKernelGGL(k_prologue, dim3((n + 63) / 64), dim3(64), 0, st, P, templates, map, ws);
+    hipLaunchKernelGGL(k_prologue, dim3(n), dim3(kParamThreads), 0, st, P, templates, map, ws,
+                     map.tmpl[0] == 0);
   }
   const int n_res = grouped ? map.n_grp : n;
   const FftVariant cv = pick_cols(p->log_rr, cols_choice(p), grouped);
@@ -624,7 +625,6 @@ fstat_status run(const fstat_plan* p, const fstat_inputs* in, const double* temp
   KernelTimer none;
   KernelTimer& tm = timer ? *timer : none;
   tm.st = st;
-  hipLaunchKernelGGL(k_twiddles, dim3(kTwLen / 256), dim3(256), 0, st, ws);
   for (int64_t t = 0; t < ntmpl; t += slots) {
     ChunkMap map;
     std::memset(&map, 0, sizeof map);
@@ -703,7 +703,8 @@ fstat_status launch_grad_bin_chunk(const fstat_plan* p, const PlanConst& P,
                                    hipStream_t st) {
   const int n = map.n_tmpl;
   const unsigned tiles = unsigned(p->k_pad / kResTile);
-  hipLaunchKernelGGL(k_prologue, dim3((n + 63) / 64), dim3(64), 0, st, P, templates, map, ws);
+  hipLaunchKernelGGL(k_prologue, dim3(n), dim3(kParamThreads), 0, st, P, templates, map, ws,
+                     map.tmpl[0] == 0);
   hipLaunchKernelGGL(resample_bin_kernel(p), dim3(tiles, n),
                      dim3(kResThreads), 0, st, P, ws, map, bins);
   hipLaunchKernelGGL(k_bin_final, dim3(n), dim3(kFinalThreads), 0, st, P, ws, map,
@@ -724,7 +725,8 @@ fstat_status launch_grad_chunk(const fstat_plan* p, const PlanConst& P, const do
                                float* twoF, void* ws, hipStream_t st) {
   const int n = map.n_tmpl;
   const unsigned tiles = unsigned(p->k_pad / kResTile);
-  hipLaunchKernelGGL(k_prologue, dim3((n + 63) / 64), dim3(64), 0, st, P, templates, map, ws);
+  hipLaunchKernelGGL(k_prologue, dim3(n), dim3(kParamThreads), 0, st, P, templates, map, ws,
+                     map.tmpl[0] == 0);
   launch_knots(p, P, map, slots, false, n, ws, st);
   launch_resample(p, P, map, slots, false, n, ws, st);
   const FftVariant cv = pick_cols(p->log_rr, cols_choice(p), false);
@@ -842,11 +844,10 @@ fstat_status search_launch(fstat_search* sr, const fstat_inputs* in, const doubl
   P.slot_stride = int64_t(slot_bytes(p->desc.n_fft));
   P.knot_offset = 0;
   P.params = static_cast<char*>(ws) + search_params_offset(sr);
-  hipLaunchKernelGGL(k_twiddles, dim3(kTwLen / 256), dim3(256), 0, st, ws);
   fstat_status s0 = tm.open(0);
   if (s0 != FSTAT_OK) return s0;
   const int64_t nt = std::max<int64_t>(sr->ntmpl, sr->slots);
-  hipLaunchKernelGGL(k_params, dim3(unsigned((nt + 63) / 64)), dim3(64), 0, st, P, templates,
+  hipLaunchKernelGGL(k_params, dim3(unsigned(nt)), dim3(kParamThreads), 0, st, P, templates,
                      sr->ntmpl, ws, sr->slots, out);
   for (const ChunkMap& map : sr->chunks) {
     fstat_status s = launch_chunk(p, P, templates, map, sr->slots, true, out, nullptr, ws, st, tm);
@@ -1596,7 +1597,6 @@ fstat_status fstat_compute_2f_grad(const fstat_plan* plan, const fstat_inputs* i
   P.part_offset = int64_t(kParamBytes + size_t(4) * plan->desc.n_fft * sizeof(float2));
   P.knot_offset = P.part_offset + int64_t(grad_part_bytes(plan));
   hipStream_t st = static_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(k_twiddles, dim3(kTwLen / 256), dim3(256), 0, st, workspace);
   for (int64_t t = 0; t < ntmpl; t += slots) {
     ChunkMap map;
     std::memset(&map, 0, sizeof map);
@@ -1641,8 +1641,6 @@ fstat_status fstat_compute_2f_grad_bin(const fstat_plan* plan, const fstat_input
   P.part_offset = int64_t(kParamBytes);
   P.knot_offset = 0;  // the single-bin tiles solve their own knots
   hipStream_t st = static_cast<hipStream_t>(stream);
-  // (clears the flagged-template counter)
-  hipLaunchKernelGGL(k_twiddles, dim3(kTwLen / 256), dim3(256), 0, st, workspace);
   for (int64_t t = 0; t < ntmpl; t += slots) {
     ChunkMap map;
     std::memset(&map, 0, sizeof map);

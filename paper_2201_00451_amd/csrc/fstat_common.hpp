@@ -225,20 +225,14 @@ struct ChunkMap {
 
 constexpr size_t kParamBytes = 1024;
 static_assert(sizeof(TmplParams) <= kParamBytes, "param block");
-// Workspace header: moment partials, then the FP32 twiddle table W_4096^e
-// (stage twiddles of every line length <= 4096) written from FP64 at the
-// start of every call, and reserved space.
+// Workspace header: moment partials, then reserved space.
 constexpr int kTwLen = 4096;
 constexpr size_t kMomentBytes = size_t(kMaxDet) * kMomBlocks * 10 * sizeof(double);
-constexpr size_t kTwOffset = kMomentBytes;
-constexpr size_t kHeaderBytes = kTwOffset + 3 * kTwLen * sizeof(float2) + 4096;
-__host__ __device__ inline float2* tw_stage(void* ws) {
-  return reinterpret_cast<float2*>(static_cast<char*>(ws) + kTwOffset);
-}
+constexpr size_t kHeaderBytes = kMomentBytes + 3 * kTwLen * sizeof(float2) + 4096;
 // In the reserved space: the number of templates of the current call whose
 // outputs are NaN (cleared by the first kernel of every call, counted once
 // per template by the row pass or the single-bin reduction).
-constexpr size_t kFlagOffset = kTwOffset + 3 * kTwLen * sizeof(float2);
+constexpr size_t kFlagOffset = kMomentBytes + 3 * kTwLen * sizeof(float2);
 __host__ __device__ inline unsigned long long* flag_counter(void* ws) {
   return reinterpret_cast<unsigned long long*>(static_cast<char*>(ws) + kFlagOffset);
 }
@@ -298,6 +292,51 @@ __host__ __device__ inline float2* group_buf(void* ws, const PlanConst& P, int s
                                              int arr) {
   return reinterpret_cast<float2*>(group_base(ws, P, slots, b) + kGroupHeader) +
          size_t(arr) * P.k_pad;
+}
+
+// Compile-time cos and sin of pi * n / d (Taylor series after reduction to
+// [-pi/4, pi/4]); used only to build constant tables.
+__host__ __device__ constexpr double ct_poly_sin(double x) {
+  double term = x, sum = x;
+  for (int k = 1; k < 14; ++k) {
+    term *= -x * x / double((2 * k) * (2 * k + 1));
+    sum += term;
+  }
+  return sum;
+}
+__host__ __device__ constexpr double ct_poly_cos(double x) {
+  double term = 1.0, sum = 1.0;
+  for (int k = 1; k < 14; ++k) {
+    term *= -x * x / double((2 * k - 1) * (2 * k));
+    sum += term;
+  }
+  return sum;
+}
+// cos(pi q / 4) and sin(pi q / 4) for integer q, then angle addition
+__host__ __device__ constexpr double ct_cospi(int n, int d) {
+  // pi n/d = pi (q/4) + r with |r| <= pi/8
+  const double x = double(n) / double(d);
+  const int q = int(x * 4.0 + (x >= 0 ? 0.5 : -0.5));
+  const double r = kPi * (x - q / 4.0);
+  const int qm = ((q % 8) + 8) % 8;
+  const double h = 0.70710678118654752440;
+  const double cq = qm == 0 ? 1.0 : qm == 1 ? h : qm == 2 ? 0.0 : qm == 3 ? -h
+                  : qm == 4 ? -1.0 : qm == 5 ? -h : qm == 6 ? 0.0 : h;
+  const double sq = qm == 0 ? 0.0 : qm == 1 ? h : qm == 2 ? 1.0 : qm == 3 ? h
+                  : qm == 4 ? 0.0 : qm == 5 ? -h : qm == 6 ? -1.0 : -h;
+  return cq * ct_poly_cos(r) - sq * ct_poly_sin(r);
+}
+__host__ __device__ constexpr double ct_sinpi(int n, int d) {
+  const double x = double(n) / double(d);
+  const int q = int(x * 4.0 + (x >= 0 ? 0.5 : -0.5));
+  const double r = kPi * (x - q / 4.0);
+  const int qm = ((q % 8) + 8) % 8;
+  const double h = 0.70710678118654752440;
+  const double cq = qm == 0 ? 1.0 : qm == 1 ? h : qm == 2 ? 0.0 : qm == 3 ? -h
+                  : qm == 4 ? -1.0 : qm == 5 ? -h : qm == 6 ? 0.0 : h;
+  const double sq = qm == 0 ? 0.0 : qm == 1 ? h : qm == 2 ? 1.0 : qm == 3 ? h
+                  : qm == 4 ? 0.0 : qm == 5 ? -h : qm == 6 ? -1.0 : -h;
+  return sq * ct_poly_cos(r) + cq * ct_poly_sin(r);
 }
 
 // Raw buffer access (gfx9 buffer descriptor): a 32-bit per-lane byte offset

@@ -11,8 +11,7 @@
 // Inside a pass, lines are transformed in LDS by a mixed-radix Stockham
 // autosort: every thread holds whole radix-R butterflies (R <= 32) in
 // registers; the first stage reads HBM and the last one writes it.  Stage
-// twiddles come from an FP32 table written from FP64 once per call and
-// copied to LDS; the four-step twiddles from the exact quarter-turn split of
+// twiddles come from a constant FP32 table copied to LDS; the four-step twiddles from the exact quarter-turn split of
 // their exponent and the rotation polynomials.  The HBM traffic is one read
 // and one write of the series per pass.
 #pragma once
@@ -198,16 +197,35 @@ __device__ __forceinline__ void fft_middle(float2* buf, const float2* twl, int t
   }
 }
 
-// FP32 stage twiddle table W_4096^e from FP64, written at the start of every
-// call; each FFT workgroup copies the W_L^e, e < L/2, it needs into LDS.
-// It also clears the call's flagged-template counter.
-__global__ void k_twiddles(void* ws) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e == 0) *flag_counter(ws) = 0ull;
-  if (e >= kTwLen) return;
-  double s, c;
-  sincospi(-2.0 * double(e) / double(kTwLen), &s, &c);
-  tw_stage(ws)[e] = make_float2(float(c), float(s));
+// FP32 stage twiddle table W_4096^e, evaluated in FP64 at compile time (one
+// octant, the rest by symmetry): it ships with the code object, so no call
+// spends a launch on it (a kernel that wrote it into the workspace took 2.4
+// us of every call).  Each FFT workgroup copies the W_L^e it needs into LDS.
+struct alignas(16) StageTable {
+  float w[2 * kTwLen];  // (re, im) pairs
+};
+__host__ __device__ constexpr StageTable make_stage_table() {
+  StageTable t{};
+  double c[kTwLen / 8 + 1] = {}, s[kTwLen / 8 + 1] = {};
+  for (int i = 0; i <= kTwLen / 8; ++i) {
+    c[i] = ct_poly_cos(2.0 * kPi * i / kTwLen);
+    s[i] = ct_poly_sin(2.0 * kPi * i / kTwLen);
+  }
+  for (int e = 0; e < kTwLen; ++e) {
+    const int q = e / (kTwLen / 4), r = e % (kTwLen / 4);
+    const bool lo = r <= kTwLen / 8;
+    const int m = kTwLen / 4 - r;
+    const double x = lo ? c[r] : s[m], y = lo ? s[r] : c[m];
+    const double cs = q == 0 ? x : q == 1 ? -y : q == 2 ? -x : y;
+    const double sn = q == 0 ? y : q == 1 ? x : q == 2 ? -y : -x;
+    t.w[2 * e] = float(cs);
+    t.w[2 * e + 1] = float(-sn);
+  }
+  return t;
+}
+static __device__ const StageTable kStageTable = make_stage_table();
+__device__ __forceinline__ const float2* tw_stage() {
+  return reinterpret_cast<const float2*>(kStageTable.w);
 }
 
 // W_N^e for 0 <= e < N <= 2^24.
@@ -382,7 +400,7 @@ __global__ __launch_bounds__(NT) void k_fft_cols(PlanConst P, void* ws, ChunkMap
   const int tid = threadIdx.x;
   const int64_t C = int64_t(1) << log_c;
   {
-    const float2* __restrict__ tws = tw_stage(ws);
+    const float2* __restrict__ tws = tw_stage();
     for (int e = tid; e < L / 2; e += NT) twl[e] = tws[e * (kTwLen / L)];
   }
   float2 v[PER0][R0];
@@ -416,7 +434,7 @@ __global__ __launch_bounds__(NT, NT / 128) void k_fft_cols_half(PlanConst P, voi
   float2* twl = lds + NL * Lay::pitch;
   const int tid = threadIdx.x;
   const int64_t C = int64_t(1) << log_c;
-  const float2* __restrict__ tws = tw_stage(ws);
+  const float2* __restrict__ tws = tw_stage();
   for (int e = tid; e < H / 2; e += NT) twl[e] = tws[e * (kTwLen / H)];
   const ColItem it = cols_item<GROUPED>(P, ws, map, slots, int(C / NL),
                                         int(xcd_remap(blockIdx.x, gridDim.x)));
@@ -786,7 +804,7 @@ __global__ __launch_bounds__(NT) void k_fft_rows(PlanConst P, void* ws, ChunkMap
   // has finished (column pass of this chunk), so their status words restart
   if (blockIdx.x == 0 && tid < map.n_reset) *group_status(ws, P, slots, map.reset_buf[tid]) = 0;
   {
-    const float2* __restrict__ tws = tw_stage(ws);
+    const float2* __restrict__ tws = tw_stage();
     for (int e = tid; e < L / 2; e += NT) twl[e] = tws[e * (kTwLen / L)];
   }
   const RowItem it =
@@ -822,7 +840,7 @@ k_fft_rows_half(
   const int64_t Rr = int64_t(1) << log_rr;
   const int tid = threadIdx.x;
   if (blockIdx.x == 0 && tid < map.n_reset) *group_status(ws, P, slots, map.reset_buf[tid]) = 0;
-  const float2* __restrict__ tws = tw_stage(ws);
+  const float2* __restrict__ tws = tw_stage();
   for (int e = tid; e < H / 2; e += NT) twl[e] = tws[e * (kTwLen / H)];
   const RowItem it =
       rows_item<MODE>(P, ws, map, int(xcd_remap(blockIdx.x, gridDim.x)), int(Rr / RQ), RQ);
@@ -912,7 +930,7 @@ __global__ __launch_bounds__(NT, NT / 128) void k_fft_rows_split(PlanConst P, vo
   // has finished (column pass of this chunk), so their status words restart
   if (blockIdx.x == 0 && tid < map.n_reset) *group_status(ws, P, slots, map.reset_buf[tid]) = 0;
   {
-    const float2* __restrict__ tws = tw_stage(ws);
+    const float2* __restrict__ tws = tw_stage();
     for (int e = tid; e < L / 2; e += NT) twl[e] = tws[e * (kTwLen / L)];
   }
   const RowItem it =

@@ -122,12 +122,9 @@ __host__ __device__ inline Jks jks_coeffs(const DetConst& d, double sd, double c
   return k;
 }
 
-// Per template: sky vector, antenna coefficients, A, B, C, D of eq. Fstat,
-// the whitening of (a, b) and the alpha/delta derivatives of the whitened
-// coefficients.  The detector loops run over the compile-time maximum so that
-// every index is static and the parameter block stays in registers.
-__host__ __device__ inline void template_params(const PlanConst& P, const double* row,
-                                                TmplParams& tp) {
+// A template's row: orbit, knot spacing, spin-down phase, sky vector and its
+// derivatives, and the status bits these give.
+__host__ __device__ inline void row_params(const PlanConst& P, const double* row, TmplParams& tp) {
   double alpha = row[0], delta = row[1];
   tp.df = row[2];
   tp.f1dot = row[3];
@@ -199,151 +196,250 @@ __host__ __device__ inline void template_params(const PlanConst& P, const double
   tp.dnhat[1][0] = -sd * ca_;
   tp.dnhat[1][1] = -sd * sa;
   tp.dnhat[1][2] = cdl;
-  // e^{i n alpha}, n = 0..4
+#pragma unroll
+  for (int X = 0; X < kMaxDet; ++X)
+    tp.alpha_cyc[X] = X < P.ndet ? alpha / (2.0 * kPi) - P.det[X].lst0_cyc : 0.0;
+  tp.status = status;
+}
+
+// One detector's share of a sum of eq. Fstat at the sky position (alpha,
+// delta): term 0..2 are A, B, C, 3..5 their derivatives with respect to
+// alpha, 6..8 with respect to delta.  alpha enters through S_n = e^{i n alpha}
+// conj(M_n): dS_n = i n S_n; delta through the coefficients (the product is
+// bilinear).
+constexpr int kMatrixTerms = 9;
+__host__ __device__ inline double matrix_term(const DetConst& d, const double* moments,
+                                              const Jks& k, double sa, double ca, int term) {
   cd ea[5];
   ea[0] = {1.0, 0.0};
-  ea[1] = {ca_, sa};
+  ea[1] = {ca, sa};
 #pragma unroll
   for (int n = 2; n < 5; ++n) ea[n] = cd_mul(ea[n - 1], ea[1]);
-  double A = 0.0, B = 0.0, C = 0.0;
-  // derivatives of A, B, C with respect to alpha (index 0) and delta (1)
-  double dA[2] = {0.0, 0.0}, dB[2] = {0.0, 0.0}, dC[2] = {0.0, 0.0};
+  cd S[5];
 #pragma unroll
-  for (int X = 0; X < kMaxDet; ++X) {
-    tp.alpha_cyc[X] = 0.0;
+  for (int n = 0; n < 5; ++n) {
+    S[n] = cd_mul(ea[n], cd_conj({moments[2 * n], moments[2 * n + 1]}));
+    if (term >= 3 && term < 6) S[n] = {-double(n) * S[n].i, double(n) * S[n].r};
+  }
+  // term mod 3: a a (A), b b (B) or a b (C)
+  const bool da = term >= 6;
+  const int ab = term % 3;
+  double pl[5], pr[5];
 #pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    pl[i] = ab == 1 ? (da ? k.dpb[i] : k.pb[i]) : (da ? k.dpa[i] : k.pa[i]);
+    pr[i] = ab == 0 ? k.pa[i] : k.pb[i];
+  }
+  const cd p[3] = {{pl[0], 0.0}, {pl[1], -pl[2]}, {pl[3], -pl[4]}};
+  const cd q[3] = {{pr[0], 0.0}, {pr[1], -pr[2]}, {pr[3], -pr[4]}};
+  double v = moment_product(p, q, S);
+  if (da) {
+    if (ab == 2) {
+      const cd p2[3] = {{k.pa[0], 0.0}, {k.pa[1], -k.pa[2]}, {k.pa[3], -k.pa[4]}};
+      const cd q2[3] = {{k.dpb[0], 0.0}, {k.dpb[1], -k.dpb[2]}, {k.dpb[3], -k.dpb[4]}};
+      v += moment_product(p2, q2, S);
+    } else {
+      v *= 2.0;
+    }
+  }
+  return d.w * v;
+}
+
+// 2F = 2 F^T M^-1 F is unchanged by a constant invertible map of (a, b).
+// Whitening by the Cholesky factor of M = [[A, C], [C, B]] in FP64 makes
+// M' = I, so the FP32 epilogue sums two squares instead of cancelling terms of
+// size cond(M).  m: the sums of matrix_term over the detectors.
+struct Whitening {
+  double l11, l21, l22, r;
+  double dl11[2], dr[2], dl22[2];  // d/d alpha, d/d delta (r = C/A)
+  bool valid;                      // M is positive definite
+};
+__host__ __device__ inline Whitening whiten(const double* m) {
+  const double A = m[0], B = m[1], C = m[2];
+  Whitening w;
+  const double Dd = A * B - C * C;
+  w.valid = A > 0.0 && Dd > 0.0 && __builtin_isfinite(Dd);
+  w.l11 = sqrt(A);
+  w.l21 = C / w.l11;
+  w.l22 = sqrt(Dd / A);
+  w.r = C / A;
+  // derivatives of the whitened coefficients: a' = a / l11,
+  // b' = (b - r a) / l22 with r = C/A, l11^2 = A, l22^2 = B - C^2/A
+#pragma unroll
+  for (int th = 0; th < 2; ++th) {
+    const double dA = m[3 + 3 * th], dB = m[4 + 3 * th], dC = m[5 + 3 * th];
+    w.dl11[th] = dA / (2.0 * w.l11);
+    w.dr[th] = (dC * A - C * dA) / (A * A);
+    w.dl22[th] = (dB - (2.0 * C * dC * A - C * C * dA) / (A * A)) / (2.0 * w.l22);
+  }
+  return w;
+}
+
+// Whitened, weighted coefficient q of detector X and its sky derivatives.
+__host__ __device__ inline void whitened_coef(const DetConst& d, const Jks& k, const Whitening& w,
+                                              int X, int q, TmplParams& tp) {
+  const double bq = k.pb[q] - w.r * k.pa[q];
+  tp.ca[X][q] = static_cast<float>(d.w * k.pa[q] / w.l11);
+  tp.cb[X][q] = static_cast<float>(d.w * bq / w.l22);
+#pragma unroll
+  for (int th = 0; th < 2; ++th) {
+    const double dpaq = th == 1 ? k.dpa[q] : 0.0;
+    const double dpbq = th == 1 ? k.dpb[q] : 0.0;
+    const double dbq = dpbq - w.dr[th] * k.pa[q] - w.r * dpaq;
+    tp.dca[th][X][q] =
+        static_cast<float>(d.w * (dpaq / w.l11 - k.pa[q] * w.dl11[th] / (w.l11 * w.l11)));
+    tp.dcb[th][X][q] =
+        static_cast<float>(d.w * (dbq / w.l22 - bq * w.dl22[th] / (w.l22 * w.l22)));
+  }
+}
+
+// Per template, serially (the kernels spread the same pieces over a block):
+// the row's parameters, A, B, C of eq. Fstat and their sky derivatives, the
+// whitened coefficients.
+__host__ __device__ inline void template_params(const PlanConst& P, const double* row,
+                                                TmplParams& tp) {
+  row_params(P, row, tp);
+  double sa, ca, sd, cdl;
+  sincos(row[0], &sa, &ca);
+  sincos(row[1], &sd, &cdl);
+  double m[kMatrixTerms] = {0.0};
+  for (int X = 0; X < P.ndet; ++X)
+    for (int t = 0; t < kMatrixTerms; ++t)
+      m[t] += matrix_term(P.det[X], P.moments + X * 10, jks_coeffs(P.det[X], sd, cdl), sa, ca, t);
+  const Whitening w = whiten(m);
+  if (!w.valid) tp.status |= kStatusTiming;
+  tp.l11 = static_cast<float>(w.l11);
+  tp.l21 = static_cast<float>(w.l21);
+  tp.l22 = static_cast<float>(w.l22);
+  for (int X = 0; X < kMaxDet; ++X)
     for (int q = 0; q < 5; ++q) {
       tp.ca[X][q] = tp.cb[X][q] = 0.0f;
       tp.dca[0][X][q] = tp.dcb[0][X][q] = tp.dca[1][X][q] = tp.dcb[1][X][q] = 0.0f;
+      if (X < P.ndet)
+        whitened_coef(P.det[X], jks_coeffs(P.det[X], sd, cdl), w, X, q, tp);
     }
-    if (X >= P.ndet) continue;
-    const DetConst& d = P.det[X];
-    const Jks k = jks_coeffs(d, sd, cdl);
-    tp.alpha_cyc[X] = alpha / (2.0 * kPi) - d.lst0_cyc;
-    // S_n = e^{i n alpha} conj(M_n)
-    cd S[5];
-#pragma unroll
-    for (int n = 0; n < 5; ++n)
-      S[n] = cd_mul(ea[n], cd_conj({P.moments[X * 10 + 2 * n], P.moments[X * 10 + 2 * n + 1]}));
-    const cd p[3] = {{k.pa[0], 0.0}, {k.pa[1], -k.pa[2]}, {k.pa[3], -k.pa[4]}};
-    const cd q[3] = {{k.pb[0], 0.0}, {k.pb[1], -k.pb[2]}, {k.pb[3], -k.pb[4]}};
-    A += d.w * moment_product(p, p, S);
-    B += d.w * moment_product(q, q, S);
-    C += d.w * moment_product(p, q, S);
-    // alpha enters through S_n = e^{i n alpha} conj(M_n): dS_n = i n S_n
-    cd dS[5];
-#pragma unroll
-    for (int n = 0; n < 5; ++n) dS[n] = {-double(n) * S[n].i, double(n) * S[n].r};
-    dA[0] += d.w * moment_product(p, p, dS);
-    dB[0] += d.w * moment_product(q, q, dS);
-    dC[0] += d.w * moment_product(p, q, dS);
-    // delta enters through the coefficients (the product is bilinear)
-    const cd dp[3] = {{k.dpa[0], 0.0}, {k.dpa[1], -k.dpa[2]}, {k.dpa[3], -k.dpa[4]}};
-    const cd dq[3] = {{k.dpb[0], 0.0}, {k.dpb[1], -k.dpb[2]}, {k.dpb[3], -k.dpb[4]}};
-    dA[1] += d.w * 2.0 * moment_product(dp, p, S);
-    dB[1] += d.w * 2.0 * moment_product(dq, q, S);
-    dC[1] += d.w * (moment_product(dp, q, S) + moment_product(p, dq, S));
-  }
-  // 2F = 2 F^T M^-1 F is unchanged by a constant invertible map of (a, b).
-  // Whitening by the Cholesky factor of M in FP64 makes M' = I, so the FP32
-  // epilogue sums two squares instead of cancelling terms of size cond(M).
-  double Dd = A * B - C * C;
-  if (!(A > 0.0) || !(Dd > 0.0) || !__builtin_isfinite(Dd)) status |= kStatusTiming;
-  const double l11 = sqrt(A), l21 = C / l11, l22 = sqrt(Dd / A);
-  const double r = C / A;
-  tp.l11 = static_cast<float>(l11);
-  tp.l21 = static_cast<float>(l21);
-  tp.l22 = static_cast<float>(l22);
-  // derivatives of the whitened coefficients: a' = a / l11,
-  // b' = (b - r a) / l22 with r = C/A, l11^2 = A, l22^2 = B - C^2/A
-  double dl11[2], dr[2], dl22[2];
-#pragma unroll
-  for (int th = 0; th < 2; ++th) {
-    dl11[th] = dA[th] / (2.0 * l11);
-    dr[th] = (dC[th] * A - C * dA[th]) / (A * A);
-    dl22[th] = (dB[th] - (2.0 * C * dC[th] * A - C * C * dA[th]) / (A * A)) / (2.0 * l22);
-  }
-#pragma unroll
-  for (int X = 0; X < kMaxDet; ++X) {
-    if (X >= P.ndet) continue;
-    const double w = P.det[X].w;
-    const Jks k = jks_coeffs(P.det[X], sd, cdl);
-#pragma unroll
-    for (int q = 0; q < 5; ++q) {
-      const double bq = k.pb[q] - r * k.pa[q];
-      tp.ca[X][q] = static_cast<float>(w * k.pa[q] / l11);
-      tp.cb[X][q] = static_cast<float>(w * bq / l22);
-#pragma unroll
-      for (int th = 0; th < 2; ++th) {
-        const double dpaq = th == 1 ? k.dpa[q] : 0.0;
-        const double dpbq = th == 1 ? k.dpb[q] : 0.0;
-        const double dbq = dpbq - dr[th] * k.pa[q] - r * dpaq;
-        tp.dca[th][X][q] =
-            static_cast<float>(w * (dpaq / l11 - k.pa[q] * dl11[th] / (l11 * l11)));
-        tp.dcb[th][X][q] = static_cast<float>(w * (dbq / l22 - bq * dl22[th] / (l22 * l22)));
+}
+
+// Everything the kernels need about one template, by one block of
+// kParamThreads: template_params plus the coverage check of the source-frame
+// grid and the adjoint's sky shift.  The work is a chain of dependent FP64
+// operations (about 2000 per detector in one thread), so it is bound by their
+// latency and is split by what is independent: the first wave takes the
+// matrix terms, one per lane (detector x term), then the coefficients, one per
+// lane (detector x coefficient); the second wave solves the grid's ends, one
+// lane per detector and end, and projects the sky shift.  Measured, one
+// thread per template against one block: 1 template of 1 detector 11.0 to 6.5
+// us, 7 of 3 detectors 26.7 to 10.4 us, 16 eccentric ones of 2 detectors 30.7
+// to 10.8 us.
+//
+// Coverage: every sample's source time lies inside the computed grid, and
+// the interpolation taps of the last sample end before the last computed
+// point, so grid points beyond k_pad are exactly zero.
+constexpr int kParamThreads = 128;
+static_assert(kMaxDet * kMatrixTerms <= 64 && kMaxDet * 5 <= 64, "one wave holds the terms");
+static_assert(sizeof(TmplParams) % sizeof(uint64_t) == 0, "copied in 8-byte words");
+__device__ inline void block_params(const PlanConst& P, const double* __restrict__ row,
+                                    TmplParams* __restrict__ out) {
+  __shared__ TmplParams tp;
+  __shared__ double term[kMaxDet][kMatrixTerms];
+  __shared__ double shift[2];
+  const int lane = threadIdx.x & 63;
+  const bool first = threadIdx.x < 64;
+  double sd = 0.0, cdl = 0.0;
+  if (first) {
+    double sa, ca;
+    sincos(row[0], &sa, &ca);
+    sincos(row[1], &sd, &cdl);
+    const int X = lane / kMatrixTerms, t = lane % kMatrixTerms;
+    if (X < P.ndet)
+      term[X][t] = matrix_term(P.det[X], P.moments + X * 10, jks_coeffs(P.det[X], sd, cdl), sa,
+                               ca, t);
+  } else {
+    TmplParams rp;
+    row_params(P, row, rp);
+    bool bad = false;
+    if (lane < 2 * P.ndet) {
+      if ((rp.status & kStatusGroupMask) == 0) {
+        const DetConst& d = P.det[lane >> 1];
+        const double k = (lane & 1) ? double(P.k_pad - 1) : 0.0;
+        const GlobalRoemer re{d.ephem, rp.nhat, P.n_eph, P.eph_t0, P.eph_dt, P.inv_eph_dt};
+        const double u = k + d.off + grid_delay<true>(re, rp, P.tau0 + k * P.dt) * P.inv_dt;
+        bad = (lane & 1) ? !(u >= double(d.n - 1 + P.D)) : !(u <= 0.0);
       }
+    } else if (lane >= 62) {
+      const double n[3] = {lane == 62 ? rp.dnhat[0][0] : rp.dnhat[1][0],
+                           lane == 62 ? rp.dnhat[0][1] : rp.dnhat[1][1],
+                           lane == 62 ? rp.dnhat[0][2] : rp.dnhat[1][2]};
+      const GlobalRoemer rq{P.det[0].ephem, n, P.n_eph, P.eph_t0, P.eph_dt, P.inv_eph_dt};
+      double dv;
+      rq(P.tau0 + 0.5 * double(P.k_pad) * P.dt, shift[lane - 62], dv);
+    }
+    const bool uncovered = __any(bad);
+    if (lane == 0) {
+      tp = rp;
+      tp.status |= uncovered ? kStatusCoverage : 0;
     }
   }
-  tp.status = status;
-}
-
-// Everything the kernels need about one template: template_params plus the
-// coverage check of the source-frame grid and the adjoint's sky shift.
-__device__ inline void full_params(const PlanConst& P, const double* row, TmplParams& tp) {
-  template_params(P, row, tp);
-  int status = tp.status;
-  // Coverage: every sample's source time lies inside the computed grid, and
-  // the interpolation taps of the last sample end before the last computed
-  // point, so grid points beyond k_pad are exactly zero.
-  if ((status & kStatusGroupMask) == 0) {
+  __syncthreads();
+  if (first) {
+    double m[kMatrixTerms];
 #pragma unroll
-    for (int X = 0; X < kMaxDet; ++X) {
-      if (X >= P.ndet) continue;
-      const DetConst& d = P.det[X];
-      const GlobalRoemer re{d.ephem, tp.nhat, P.n_eph, P.eph_t0, P.eph_dt, P.inv_eph_dt};
-      double u_first = 0.0 + d.off + grid_delay<true>(re, tp, P.tau0) * P.inv_dt;
-      double k_last = double(P.k_pad - 1);
-      double u_last = k_last + d.off + grid_delay<true>(re, tp, P.tau0 + k_last * P.dt) * P.inv_dt;
-      if (!(u_first <= 0.0) || !(u_last >= double(d.n - 1 + P.D))) status |= kStatusCoverage;
+    for (int t = 0; t < kMatrixTerms; ++t) {
+      m[t] = 0.0;
+      for (int X = 0; X < P.ndet; ++X) m[t] += term[X][t];
+    }
+    const Whitening w = whiten(m);
+    if (lane == 0) {
+      tp.status |= w.valid ? 0 : kStatusTiming;
+      tp.l11 = static_cast<float>(w.l11);
+      tp.l21 = static_cast<float>(w.l21);
+      tp.l22 = static_cast<float>(w.l22);
+    }
+    if (lane < 2) tp.dshift[lane] = shift[lane];
+    const int X = lane / 5, q = lane % 5;
+    if (X < P.ndet) {
+      whitened_coef(P.det[X], jks_coeffs(P.det[X], sd, cdl), w, X, q, tp);
+    } else if (X < kMaxDet) {
+      tp.ca[X][q] = tp.cb[X][q] = 0.0f;
+      tp.dca[0][X][q] = tp.dcb[0][X][q] = tp.dca[1][X][q] = tp.dcb[1][X][q] = 0.0f;
     }
   }
-  tp.status = status;
-  const double t_mid = P.tau0 + 0.5 * double(P.k_pad) * P.dt;
-  const DetConst& d0 = P.det[0];
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const GlobalRoemer rq{d0.ephem, tp.dnhat[q], P.n_eph, P.eph_t0, P.eph_dt, P.inv_eph_dt};
-    double v, dv;
-    rq(t_mid, v, dv);
-    tp.dshift[q] = v;
-  }
+  __syncthreads();
+  const uint64_t* src = reinterpret_cast<const uint64_t*>(&tp);
+  uint64_t* dst = reinterpret_cast<uint64_t*>(out);
+  for (int i = threadIdx.x; i < int(sizeof(TmplParams) / sizeof(uint64_t)); i += kParamThreads)
+    dst[i] = src[i];
 }
 
-// Parameter blocks of the templates of one chunk, into their slots.
-__global__ __launch_bounds__(64) void k_prologue(PlanConst P, const double* __restrict__ templates,
-                                                 ChunkMap map, void* ws) {
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= map.n_tmpl) return;
-  TmplParams tp;
-  full_params(P, templates + map.tmpl[g] * P.tmpl_stride, tp);
-  *slot_params(ws, P, g) = tp;
+// Parameter blocks of the templates of one chunk, into their slots (one block
+// each).  A call's first chunk also clears its flagged-template counter.
+__global__ __launch_bounds__(kParamThreads) void k_prologue(PlanConst P,
+                                                            const double* __restrict__ templates,
+                                                            ChunkMap map, void* ws, int clear) {
+  const int g = blockIdx.x;
+  if (clear && g == 0 && threadIdx.x == 0) *flag_counter(ws) = 0ull;
+  block_params(P, templates + map.tmpl[g] * P.tmpl_stride, slot_params(ws, P, g));
 }
 
 // Search path, once per run: the parameter blocks of all templates into the
 // per-template array P.params, the status words of the group buffers cleared
-// for the first chunk, and the candidate count and per-template maxima of
-// the run cleared (in a kernel, so that a captured graph needs no memset).
-__global__ __launch_bounds__(64) void k_params(PlanConst P, const double* __restrict__ templates,
-                                               int64_t ntmpl, void* ws, int slots,
-                                               RowOutput out) {
-  const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t < slots) *group_status(ws, P, slots, int(t)) = 0;
-  if (t == 0 && out.count) *out.count = 0ull;
+// for the first chunk, and the flagged-template counter, the candidate count
+// and the per-template maxima of the run cleared (in a kernel, so that a
+// captured graph needs no memset).
+__global__ __launch_bounds__(kParamThreads) void k_params(PlanConst P,
+                                                          const double* __restrict__ templates,
+                                                          int64_t ntmpl, void* ws, int slots,
+                                                          RowOutput out) {
+  const int64_t t = blockIdx.x;
+  if (threadIdx.x == 0) {
+    if (t < slots) *group_status(ws, P, slots, int(t)) = 0;
+    if (t == 0) *flag_counter(ws) = 0ull;
+    if (t == 0 && out.count) *out.count = 0ull;
+    if (t < ntmpl && out.best) out.best[t] = 0ull;
+  }
   if (t >= ntmpl) return;
-  if (out.best) out.best[t] = 0ull;
-  TmplParams tp;
-  full_params(P, templates + t * P.tmpl_stride, tp);
-  *reinterpret_cast<TmplParams*>(P.params + size_t(t) * kParamBytes) = tp;
+  block_params(P, templates + t * P.tmpl_stride,
+               reinterpret_cast<TmplParams*>(P.params + size_t(t) * kParamBytes));
 }
 
 }  // namespace fstat

@@ -38,51 +38,6 @@
 
 namespace fstat {
 
-// Compile-time cos and sin of pi * n / d (Taylor series after reduction to
-// [-pi/4, pi/4]); used only to build tap constants.
-__host__ __device__ constexpr double ct_poly_sin(double x) {
-  double term = x, sum = x;
-  for (int k = 1; k < 14; ++k) {
-    term *= -x * x / double((2 * k) * (2 * k + 1));
-    sum += term;
-  }
-  return sum;
-}
-__host__ __device__ constexpr double ct_poly_cos(double x) {
-  double term = 1.0, sum = 1.0;
-  for (int k = 1; k < 14; ++k) {
-    term *= -x * x / double((2 * k - 1) * (2 * k));
-    sum += term;
-  }
-  return sum;
-}
-// cos(pi q / 4) and sin(pi q / 4) for integer q, then angle addition
-__host__ __device__ constexpr double ct_cospi(int n, int d) {
-  // pi n/d = pi (q/4) + r with |r| <= pi/8
-  const double x = double(n) / double(d);
-  const int q = int(x * 4.0 + (x >= 0 ? 0.5 : -0.5));
-  const double r = kPi * (x - q / 4.0);
-  const int qm = ((q % 8) + 8) % 8;
-  const double h = 0.70710678118654752440;
-  const double cq = qm == 0 ? 1.0 : qm == 1 ? h : qm == 2 ? 0.0 : qm == 3 ? -h
-                  : qm == 4 ? -1.0 : qm == 5 ? -h : qm == 6 ? 0.0 : h;
-  const double sq = qm == 0 ? 0.0 : qm == 1 ? h : qm == 2 ? 1.0 : qm == 3 ? h
-                  : qm == 4 ? 0.0 : qm == 5 ? -h : qm == 6 ? -1.0 : -h;
-  return cq * ct_poly_cos(r) - sq * ct_poly_sin(r);
-}
-__host__ __device__ constexpr double ct_sinpi(int n, int d) {
-  const double x = double(n) / double(d);
-  const int q = int(x * 4.0 + (x >= 0 ? 0.5 : -0.5));
-  const double r = kPi * (x - q / 4.0);
-  const int qm = ((q % 8) + 8) % 8;
-  const double h = 0.70710678118654752440;
-  const double cq = qm == 0 ? 1.0 : qm == 1 ? h : qm == 2 ? 0.0 : qm == 3 ? -h
-                  : qm == 4 ? -1.0 : qm == 5 ? -h : qm == 6 ? 0.0 : h;
-  const double sq = qm == 0 ? 0.0 : qm == 1 ? h : qm == 2 ? 1.0 : qm == 3 ? h
-                  : qm == 4 ? 0.0 : qm == 5 ? -h : qm == 6 ? -1.0 : -h;
-  return sq * ct_poly_cos(r) + cq * ct_poly_sin(r);
-}
-
 // Tap constants of half-width D, built at compile time into constant memory
 // (read with uniform indices, whether or not the tap loop is unrolled):
 //   A_t, B_t, C_t as above; Ct_t = cos(pi c_t / D), St_t = sin(pi c_t / D).

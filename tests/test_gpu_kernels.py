@@ -1,0 +1,48 @@
+"""Kernels at the sizes where they can go wrong: remainders, edges of tiles and
+the smallest and largest of their ranges, against the FP64 oracle or an exact
+reference of the same operation, through the C ABI."""
+import numpy as np
+import pytest
+
+from oracle import fstat_oracle as O
+from paper_2201_00451_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+# the forward path's bar against the oracle
+RTOL, ATOL = 1e-4, 1e-3
+
+
+@pytest.fixture(scope="module")
+def torch_dev():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU test run without a visible GPU")
+    from paper_2201_00451_amd import binding
+    binding.load_library()
+    return torch
+
+
+def check_2f(gpu, ref):
+    gpu = gpu.cpu().numpy().astype(np.float64)
+    strong = ref >= 10.0
+    assert np.all(np.isfinite(gpu))
+    assert np.max(np.abs(gpu - ref)[strong] / ref[strong]) <= RTOL
+    assert np.max(np.abs(gpu - ref)[~strong]) <= ATOL
+
+
+@pytest.mark.parametrize("ndet,kepler", [(1, False), (4, False), (4, True)])
+def test_parameter_blocks_of_every_detector_count(torch_dev, ndet, kepler):
+    """The parameter kernel's lanes at one detector and at the maximum (four),
+    with isolated and eccentric rows, in the plain and the grouped path."""
+    from paper_2201_00451_amd import binding
+    extra = dict(binary=True, ecc=0.2, argp=0.7) if kepler else {}
+    ds = synth.small_case(seed=90 + ndet, n=3001, n_fft=1 << 13, ndet=ndet, ntmpl=3, gaps=True,
+                          noise_vars=[1.0, 0.7, 1.4, 0.9][:ndet], **extra)
+    ref = O.oracle_twoF(ds)
+    dd = binding.DeviceData(ds, batch=3)
+    plain = binding.compute_2f(dd, ds.templates)
+    grouped = binding.Search(dd, ds.templates, slots=2).run()
+    binding.sync_check()
+    assert torch_dev.equal(plain, grouped)
+    check_2f(plain, ref)
