@@ -410,9 +410,10 @@ int64_t rows_items(const fstat_plan* p, const FftVariant& v, int n) {
 
 // Resampling kernels for a supported interpolation half-width: knots solved
 // ahead, and the tiles that solve their own timing.
+using ResAheadFn = void (*)(PlanConst, void*, ChunkMap, int, int);
 using ResFn = void (*)(PlanConst, void*, ChunkMap, int);
 template <bool GROUPED>
-ResFn resample_kernel_g(int D) {
+ResAheadFn resample_kernel_g(int D) {
   switch (D) {
     case 4: return &k_resample<4, GROUPED>;
     case 6: return &k_resample<6, GROUPED>;
@@ -458,7 +459,8 @@ void launch_knots(const fstat_plan* p, const PlanConst& P, const ChunkMap& map, 
                      dim3(kKnotThreads), 0, st, P, ws, map, slots);
 }
 
-ResFn resample_kernel(const fstat_plan* p, bool grouped) {
+constexpr int64_t kSpanMinTiles = 2048;
+ResAheadFn resample_kernel(const fstat_plan* p, bool grouped) {
   const int D = p->desc.sinc_halfwidth;
   return grouped ? resample_kernel_g<true>(D) : resample_kernel_g<false>(D);
 }
@@ -474,8 +476,14 @@ ResFn resample_own_kernel(const fstat_plan* p, bool grouped) {
 void launch_resample(const fstat_plan* p, const PlanConst& P, const ChunkMap& map, int slots,
                      bool grouped, int n_res, void* ws, hipStream_t st) {
   const int64_t tiles = p->k_pad / kResTile;
-  hipLaunchKernelGGL(resample_kernel(p, grouped), dim3(unsigned(tiles), n_res),
-                     dim3(kResThreads), 0, st, P, ws, map, slots);
+  // Two tiles a block halve what a block spends on its records and edges, but
+  // also the blocks: below about eight tiles per compute unit the launch is a
+  // single wave of blocks and lasts as long as one of them (measured, one
+  // against two tiles: 342 tiles 10.2 against 13.4 us, 973 22.1 / 25.8, 2392
+  // 26.4 / 25.4, 5076 46.9 / 45.4, 81024 631 / 498).
+  const int span = tiles * n_res >= kSpanMinTiles ? kSpanTiles : 1;
+  hipLaunchKernelGGL(resample_kernel(p, grouped), dim3(unsigned((tiles + span - 1) / span), n_res),
+                     dim3(kResThreads), span_lds_bytes(p->desc.ndet), st, P, ws, map, slots, span);
   hipLaunchKernelGGL(resample_own_kernel(p, grouped),
                      dim3(unsigned(std::min<int64_t>(tiles, 256)), n_res), dim3(kResThreads), 0,
                      st, P, ws, map, slots);

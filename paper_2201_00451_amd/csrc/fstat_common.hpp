@@ -28,10 +28,23 @@ constexpr int kResThreads = 256;
 constexpr int kResPerThread = kResTile / kResThreads;
 // Waves per SIMD of the resampling kernel whose timing knots were solved
 // ahead (its registers: 512 / waves).
-constexpr int kResWavesAhead = 5;
+constexpr int kResWavesAhead = 6;
 constexpr int kResWcap = kResTile + kResTile / 16 + 64 + 8;
 // Flags of the staged window's 32-sample blocks (any live sample).
 constexpr int kResBlk = (kResWcap + kResThreads) / 32 + 2;
+// Where the timing knots were solved ahead, a block takes a span of kSpanTiles
+// tiles: its window's capacity (every tile of the span within kResWcap, and up
+// to 63 samples that align its start), the window's block flags (at most 64:
+// one ballot reads them), the samples per thread and detector loaded ahead of
+// the correction, and the capacities of the records kept in LDS (spans of
+// kSpanTiles tiles at knot spacings of 32 and 64, of one tile at 16).
+constexpr int kSpanTiles = 2;
+constexpr int kSpanCap = kSpanTiles * kResWcap + 64;
+constexpr int kSpanBlk = kSpanCap / 32 + 10;
+constexpr int kStageRounds = 5;
+constexpr int kSpanGrid = kSpanTiles * kResTile / 32 + 1;
+constexpr int kSpanSamp = (kResWcap + 64) / 16 + 2;
+static_assert(kSpanBlk <= 64 && kSpanCap / 32 + 2 <= kSpanSamp, "one ballot, one record area");
 
 // Ephemeris nodes a resampling tile stages in LDS (projected on the sky), per
 // detector: bounds the ephemeris spacing from below (a tile spans its

@@ -24,12 +24,8 @@
 // df (FP64 phase, FP32 rotation) and writes y_a', y_b' (float2) with
 // coalesced stores.  FP64 is used only for times and phases.
 //
-// The half-width D is a template parameter: with s = f + c_t, c_t = D-1-t,
-//   h_t = sin(pi f) * [A_t cos(pi f/D) + B_t sin(pi f/D) + C_t] / s,
-//   A_t = (-1)^{c_t} cos(pi c_t/D) / (2 pi), B_t = -(-1)^{c_t} sin(pi c_t/D) / (2 pi),
-//   C_t = (-1)^{c_t} / (2 pi),
-// so each tap costs one reciprocal, two FMAs for the window and two for the
-// accumulation; sin(pi f) multiplies the finished sum.
+// The half-width D is a template parameter: the taps are polynomials in the
+// point's fraction f with compile-time coefficients (make_tap_poly).
 #pragma once
 
 #include <utility>
@@ -62,71 +58,106 @@ __host__ __device__ constexpr TapConst make_taps() {
 template <int D>
 __constant__ TapConst kTaps = make_taps<D>();
 
-// One tap of the forward interpolation with its constants as compile-time
-// literals: with c = D - 1 - T the tap's integer offset,
-//   h_T (up to the common factor sin(pi f) / (2 pi)) =
-//     (-1)^c (1 + cos(pi c/D) cos(pi f/D) - sin(pi c/D) sin(pi f/D)) / (f + c),
-// the Hann window by angle addition and the sinc's alternating sign folded
-// into the accumulation.  Two literal FMAs for the window, one reciprocal,
-// one multiply and two FMAs per tap; no constant reaches a register.
-template <int D, int T>
-__device__ __forceinline__ void interp_tap(float f, float wc, float ws, const float2* zp,
-                                           float& sx, float& sy) {
-  constexpr int c = D - 1 - T;
-  constexpr float cs = float(ct_cospi(c, D));
-  constexpr float sn = float(ct_sinpi(c, D));
-  const float w = fmaf(wc, cs, fmaf(ws, -sn, 1.0f));
-  float h = w * __builtin_amdgcn_rcpf(f + float(c));
-  if constexpr ((c & 1) != 0) h = -h;
-  const float2 zv = zp[T];
-  sx = fmaf(h, zv.x, sx);
-  sy = fmaf(h, zv.y, sy);
+// The forward interpolation's taps as polynomials.  With g = f - 1/2 in
+// [-1/2, 1/2] the taps at the offsets s = f + m and s = f - 1 - m (m = 0 ..
+// D - 1) are h(g + m + 1/2) and, h being even, h(-g + m + 1/2): the pair is
+// E_m(g^2) +- g O_m(g^2) with E_m and O_m the even and odd parts of one
+// polynomial in g.  make_tap_poly builds it at compile time in FP64: the
+// Chebyshev interpolant of h on 16 nodes, cut at degree 9 (8 for the outer
+// quarter of the pairs, where the window is small), which is within 2e-8 of h;
+// with the FP32 Horner evaluation a tap is within 9e-8 (the closed form
+// sin(pi f) w(s) / s reaches 2e-7).  A pair costs 11 operations of 2.3-2.8
+// cycles each where the closed form cost two reciprocals (8.2 cycles each),
+// four window FMAs and two products, and nothing per point besides g^2: no
+// sine of the offset, no window phase, no special case at f = 0.
+constexpr int kTapCoef = 5;
+struct TapPoly {
+  float e[kTapCoef], o[kTapCoef];
+};
+template <int D>
+__host__ __device__ constexpr int tap_odd_terms(int m) {
+  return m >= (3 * D + 3) / 4 ? kTapCoef - 1 : kTapCoef;
 }
-template <int D, int... T>
-__device__ __forceinline__ void interp_taps(std::integer_sequence<int, T...>, float f, float wc,
-                                            float ws, const float2* zp, float& sx, float& sy) {
-  (interp_tap<D, T>(f, wc, ws, zp, sx, sy), ...);
+template <int D, int M>
+__host__ __device__ constexpr TapPoly make_tap_poly() {
+  constexpr int K = 16, N = 2 * kTapCoef;  // nodes; coefficients of g^0 .. g^9
+  double y[K] = {}, cheb[N] = {}, t0[N] = {}, t1[N] = {}, mono[N] = {};
+  for (int k = 0; k < K; ++k) {
+    const double g = 0.5 * ct_cospi(2 * k + 1, 2 * K);
+    const double s = g + M + 0.5;
+    // sin(pi s) = (-1)^M cos(pi g)
+    const double sn = ((M & 1) ? -1.0 : 1.0) * ct_poly_cos(kPi * g);
+    y[k] = sn / (kPi * s) * 0.5 * (1.0 + ct_poly_cos(kPi * s / D));
+  }
+  const int deg = kTapCoef - 1 + tap_odd_terms<D>(M);
+  for (int j = 0; j <= deg; ++j) {
+    for (int k = 0; k < K; ++k) cheb[j] += y[k] * ct_cospi(j * (2 * k + 1), 2 * K);
+    cheb[j] *= (j == 0 ? 1.0 : 2.0) / K;
+  }
+  // sum of cheb[j] T_j(x), x = 2 g, in powers of g
+  t0[0] = 1.0;
+  t1[1] = 2.0;
+  for (int i = 0; i < N; ++i) mono[i] = cheb[0] * t0[i] + cheb[1] * t1[i];
+  for (int j = 2; j <= deg; ++j) {
+    double t2[N] = {};
+    for (int i = 0; i < N; ++i) t2[i] = (i > 0 ? 4.0 * t1[i - 1] : 0.0) - t0[i];
+    for (int i = 0; i < N; ++i) {
+      mono[i] += cheb[j] * t2[i];
+      t0[i] = t1[i];
+      t1[i] = t2[i];
+    }
+  }
+  TapPoly p{};
+  for (int i = 0; i < kTapCoef; ++i) {
+    p.e[i] = float(mono[2 * i]);
+    p.o[i] = float(mono[2 * i + 1]);
+  }
+  return p;
 }
 
-// sin(pi f) / (2 pi) for 0 <= f < 1 from h = min(f, 1 - f) (exact for f >=
-// 1/2): the odd Taylor series of sin(pi h) / (2 pi) through h^13, whose first
-// omitted term is below 7e-10 of the value at h = 1/2, so the result keeps
-// its relative precision at both ends of the interval, where the sinc's
-// numerator meets the vanishing denominator of the nearest tap.
-struct SinPiCoef {
-  float c[7];
-};
-__host__ __device__ constexpr SinPiCoef make_sinpi_coef() {
-  SinPiCoef k{};
-  double t = 0.5;  // pi / (2 pi)
-  for (int n = 0; n < 7; ++n) {
-    k.c[n] = float(t);
-    t *= -(kPi * kPi) / double((2 * n + 2) * (2 * n + 3));
-  }
-  return k;
-}
-__device__ __forceinline__ float sinpi_over_2pi(float f) {
-  constexpr SinPiCoef k = make_sinpi_coef();
-  const float h = fminf(f, 1.0f - f);
-  const float u = h * h;
-  float p = k.c[6];
+// The two taps of pair M at g (u = g^2).
+template <int D, int M>
+__device__ __forceinline__ void tap_pair(float g, float u, float& hp, float& hm) {
+  constexpr TapPoly p = make_tap_poly<D, M>();
+  constexpr int no = tap_odd_terms<D>(M);
+  // the first step as a product and a sum: an FMA takes one literal, so two
+  // would keep the leading coefficients of every pair in registers
+  float e = __fmul_rn(u, p.e[kTapCoef - 1]), o = __fmul_rn(u, p.o[no - 1]);
+  e = __fadd_rn(e, p.e[kTapCoef - 2]);
+  o = __fadd_rn(o, p.o[no - 2]);
 #pragma unroll
-  for (int n = 5; n >= 0; --n) p = fmaf(p, u, k.c[n]);
-  return h * p;
+  for (int i = kTapCoef - 3; i >= 0; --i) e = fmaf(e, u, p.e[i]);
+#pragma unroll
+  for (int i = no - 3; i >= 0; --i) o = fmaf(o, u, p.o[i]);
+  hp = fmaf(g, o, e);
+  hm = fmaf(-g, o, e);
+}
+template <int D, int M>
+__device__ __forceinline__ void interp_pair(float g, float u, const float2* zp, float& sx,
+                                            float& sy) {
+  float hp, hm;
+  tap_pair<D, M>(g, u, hp, hm);
+  const float2 zl = zp[D - 1 - M], zr = zp[D + M];
+  sx = fmaf(hp, zl.x, sx);
+  sy = fmaf(hp, zl.y, sy);
+  sx = fmaf(hm, zr.x, sx);
+  sy = fmaf(hm, zr.y, sy);
+}
+template <int D, int... M>
+__device__ __forceinline__ void interp_pairs(std::integer_sequence<int, M...>, float g, float u,
+                                             const float2* zp, float& sx, float& sy) {
+  // outer pairs first
+  (interp_pair<D, D - 1 - M>(g, u, zp, sx, sy), ...);
 }
 
 // Step (v): the 2D-tap interpolation of the samples zp[0 .. 2D) at the
 // fraction f of the point between zp[D - 1] and zp[D].
 template <int D>
 __device__ __forceinline__ float2 sinc_interp(float f, const float2* zp) {
-  static_assert(D >= 4, "the window phase stays within one eighth turn");
-  if (f == 0.0f) return zp[D - 1];
-  // window phase pi f / D: 2 f / D <= 1/2 quarter turns, no reduction
-  const float2 wcs = cis_quarter(0, 4.0f * (f * (0.5f / float(D))));
+  const float g = f - 0.5f;
   float sx = 0.f, sy = 0.f;
-  interp_taps<D>(std::make_integer_sequence<int, 2 * D>{}, f, wcs.x, wcs.y, zp, sx, sy);
-  const float sp = sinpi_over_2pi(f);
-  return make_float2(sx * sp, sy * sp);
+  interp_pairs<D>(std::make_integer_sequence<int, D>{}, g, g * g, zp, sx, sy);
+  return make_float2(sx, sy);
 }
 
 // The weighting of step (vi): the whitened antenna patterns of detector X
@@ -207,29 +238,6 @@ __device__ inline void antenna_taylor(const TmplParams& tp, int X, double x_cyc,
     o[4] = (p1 + 16.0f * p2) * (1.0f / 24.0f);
     o[5] = (q1 + 32.0f * q2) * (1.0f / 120.0f);
   }
-}
-
-// Steps (v) and (vi) at one grid point whose taps start at base in the staged
-// window zs (fraction f), with the antenna patterns from the tile's Taylor
-// coefficients c (uniform across the tile) at the angle offset d (radians).
-template <int D>
-__device__ __forceinline__ void interp_point_taylor(const float2* zs, const int32_t* blk, int W,
-                                                    int base, float f, float d,
-                                                    const float (&c)[kTaylorCoef], float2& acc_a,
-                                                    float2& acc_b) {
-  base = base < 0 ? 0 : (base > W - 2 * D ? W - 2 * D : base);
-  if (!taps_live<D>(blk, base)) return;
-  const float2 zh = sinc_interp<D>(f, zs + base);
-  float a = c[5], b = c[11];
-#pragma unroll
-  for (int n = 4; n >= 0; --n) {
-    a = fmaf(a, d, c[n]);
-    b = fmaf(b, d, c[6 + n]);
-  }
-  acc_a.x = fmaf(a, zh.x, acc_a.x);
-  acc_a.y = fmaf(a, zh.y, acc_a.y);
-  acc_b.x = fmaf(b, zh.x, acc_b.x);
-  acc_b.y = fmaf(b, zh.y, acc_b.y);
 }
 
 // q = (T_k - tau_k)/dt at grid offset k within its knot interval from the
@@ -511,189 +519,288 @@ __device__ inline bool resample_tile(const PlanConst& P, const TmplParams& tp,
   return true;
 }
 
-// The tile for a template whose timing knots k_knots solved ahead (knot
-// area kn): each thread reads the knot records of its own samples and grid
-// points, so a pass of kDetPass detectors has two phases, the corrected
-// samples into LDS and then interpolation and weighting, with one barrier
-// between them.  The window of a detector runs from the tile's first source
-// position to the one of the interval just past the tile (T_k is monotonic in
-// k).  The grid points take their source positions from the FP32 interval
-// cubics relative to the intervals' integers, and (plans with res_taylor) the
-// antenna patterns from the tile's Taylor record, so the interpolation phase
-// runs without FP64 arithmetic.
-template <int D>
-__device__ inline bool resample_tile_gk(const PlanConst& P, const TmplParams& tp,
-                                        const double2* __restrict__ kn, int32_t* status_word,
-                                        int64_t k_s, float2* zsa, int32_t* blka,
-                                        float2 (&acc_a)[kResPerThread],
-                                        float2 (&acc_b)[kResPerThread]) {
-  constexpr int kRounds = (kResWcap + kResThreads - 1) / kResThreads;
-  const int tid = threadIdx.x;
+// Reads of memory that no thread of the running kernel writes, at an address
+// uniform across the wave: scalar loads (one per wave instead of one per
+// lane through the vector memory path).
+template <class T>
+__device__ __forceinline__ T scalar_load(const T* p) {
+  return *reinterpret_cast<const __attribute__((address_space(4))) T*>(
+      reinterpret_cast<uintptr_t>(p));
+}
+__device__ __forceinline__ int32_t uniform_i32(int32_t v) {
+  return __builtin_amdgcn_readfirstlane(v);
+}
+
+// The weighting of step (vi) with the antenna patterns from the tile's Taylor
+// coefficients c (uniform across the tile) at the angle offset d (radians).
+__device__ __forceinline__ void weight_taylor(float2 zh, float d, const float* c, float2& acc_a,
+                                              float2& acc_b) {
+  float a = c[5], b = c[11];
 #pragma unroll
-  for (int i = 0; i < kResPerThread; ++i) {
-    acc_a[i] = make_float2(0.f, 0.f);
-    acc_b[i] = make_float2(0.f, 0.f);
+  for (int n = 4; n >= 0; --n) {
+    a = fmaf(a, d, c[n]);
+    b = fmaf(b, d, c[6 + n]);
   }
-  const int kl = tp.knot_log2;
+  acc_a.x = fmaf(a, zh.x, acc_a.x);
+  acc_a.y = fmaf(a, zh.y, acc_a.y);
+  acc_b.x = fmaf(b, zh.x, acc_b.x);
+  acc_b.y = fmaf(b, zh.y, acc_b.y);
+}
+
+// The heterodyne correction of one sample at t samples into its interval:
+// x exp(-2 pi i f_h (t_src - t_det)), the phase in quarter turns from the
+// interval's record (k0, k1, k2, k3).
+__device__ __forceinline__ float2 correct_sample(float2 x, double t, double k0, double k1,
+                                                 double k2, double k3) {
+  const double c4 = fma(fma(fma(k3, t, k2), t, k1), t, k0);
+  const double q = rint(c4);
+  const float2 e = cis_quarter(int(q), static_cast<float>(c4 - q));
+  return make_float2(x.x * e.x + x.y * e.y, x.y * e.x - x.x * e.y);
+}
+
+// What a span's block keeps in LDS per detector besides its window: the records
+// of the sample and grid intervals it touches, the tiles' Taylor records, and
+// the window's block flags.
+struct alignas(16) SpanRec {
+  double2 samp[kSpanSamp][2];
+  float4 grid[kSpanGrid];
+  float tile[kSpanTiles][kTileRecUnits * 4];
+  int32_t grid_i[kSpanGrid];
+  int32_t blk[kSpanBlk];
+};
+__host__ __device__ inline size_t span_lds_bytes(int ndet) {
+  return size_t(ndet) * (kSpanCap * sizeof(float2) + sizeof(SpanRec));
+}
+static_assert(kSpanCap % 2 == 0, "records behind the windows stay 16-byte aligned");
+static_assert(kMaxDet * 64 <= kResThreads && kSpanGrid <= 40 && kSpanTiles * kTileRecUnits <= 24,
+              "64 threads load a detector's grid and tile records");
+static_assert(kDetPass * 128 <= kResThreads && 2 * kSpanSamp <= 128,
+              "128 threads load a detector's sample records");
+
+// Templates whose timing knots k_knots solved ahead (knot area kn): a block
+// takes a span of n_t tiles starting at tile t0.  The span's samples of every
+// detector go into LDS corrected, then each tile is interpolated and weighted
+// from the interval records.  A detector's window runs from the span's first
+// source position to the one of the interval just past it (T_k is monotonic in
+// k); it starts at a multiple of the coarsest knot spacing, so at an interval.
+// The grid points take their source positions from the FP32 interval cubics
+// relative to the intervals' integers, and (plans with res_taylor) the antenna
+// patterns from the tile's Taylor record, so the interpolation runs without
+// FP64 arithmetic.
+//
+// Bound by latency before it is bound by arithmetic: every record and sample
+// is a first touch (a miss of L2), so the span waits for memory twice, once for
+// the window's edges (with the grid and tile records in flight beside them)
+// and once for the samples and their records; everything later reads LDS.
+// Measured on 32 templates of 5.2 M points and two detectors, after a tile per
+// block that read its records where it used them (2245 us): records in LDS and
+// loads batched 2120 us, two tiles per block 1720 us, six waves per SIMD
+// instead of five 1675 us (24 bytes spilled); of the time without arithmetic
+// (1180 us with taps, corrections, sample loads and stores taken out) most was
+// the chain of dependent misses.
+// store(k, acc_a, acc_b) receives every point.  Returns false, after flagging
+// the template's status word, when the template must report NaN (the return
+// is uniform across the block).
+template <int D, class Store>
+__device__ __forceinline__ bool resample_span(const PlanConst& P, const TmplParams& tp,
+                                              const double2* __restrict__ kn, int kl,
+                                              int32_t* status_word, int32_t t0, int n_t,
+                                              float2* zsa, SpanRec* recs, Store&& store) {
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int w0 = uniform_i32(tid) & ~63;
   const int G = 1 << kl;
   const float inv_gf = 1.0f / float(G);
-  const double tau_s = P.tau0 + P.dt * double(k_s);
-  const int64_t e_s = k_s >> kl;  // the tile's first interval
-  // d(angle)/d(grid step) of the sidereal angle x, radians
-  const float dstep = float(-2.0 * kPi * P.sid_rate_cyc * P.dt);
-  for (int X0 = 0; X0 < P.ndet; X0 += kDetPass) {
+  const int32_t k_s = t0 << kResTileLog;
+  // grid records 0 .. n_t 512 / G (the last one is the edge past the span) and
+  // tile records, into registers; they go to LDS after the samples' loads
+  // have been issued
+  const int gX = tid >> 6;
+  float4 grec = make_float4(0.f, 0.f, 0.f, 0.f);
+  int32_t girec = 0;
+  const bool has_grid = gX < P.ndet && lane <= (n_t << kResTileLog) >> kl;
+  const bool has_tile = gX < P.ndet && lane >= 40 && lane < 40 + n_t * kTileRecUnits;
+  if (has_grid || has_tile) {
+    const double2* ka = kn + gX * P.knot_stride;
+    const float4* src = has_grid
+                            ? reinterpret_cast<const float4*>(ka) + (k_s >> kl) + lane
+                            : reinterpret_cast<const float4*>(ka + P.knot_toff) +
+                                  int64_t(t0) * kTileRecUnits + (lane - 40);
+    grec = *src;
+    if (has_grid) girec = reinterpret_cast<const int32_t*>(ka + P.knot_ioff)[(k_s >> kl) + lane];
+  }
+  bool wbad = false;
+  int32_t ja_all[kMaxDet];
+#pragma unroll
+  for (int X0 = 0; X0 < kMaxDet; X0 += kDetPass) {
+    if (X0 >= P.ndet) break;
     const int np = P.ndet - X0 < kDetPass ? P.ndet - X0 : kDetPass;
-    int64_t lo[kDetPass];
-    int W[kDetPass];
-    bool wbad = false;
+    // floor of the source position at the tiles' first points and at the one
+    // past the span (theta(0) in [0, 1], 1 after rounding): every load before
+    // the first use, so that one wait covers them (a single detector loads its
+    // own twice)
+    float eth[kDetPass][kSpanTiles + 1];
+    int32_t ei[kDetPass][kSpanTiles + 1];
 #pragma unroll
     for (int xp = 0; xp < kDetPass; ++xp) {
-      lo[xp] = 0;
-      W[xp] = 0;
-      if (xp >= np) continue;
-      const double2* ka = kn + (X0 + xp) * P.knot_stride;
-      const float4* gr = reinterpret_cast<const float4*>(ka);
-      const int32_t* gi = reinterpret_cast<const int32_t*>(ka + P.knot_ioff);
-      const int64_t e_e = (k_s + kResTile) >> kl;
-      // floor of the source position at the tile's first point and at the
-      // point just past it (theta(0) in [0, 1], 1 after rounding)
-      const int64_t j_first = k_s + gi[e_s] + (gr[e_s].x >= 1.0f ? 1 : 0);
-      const int64_t j_last = k_s + kResTile + gi[e_e] + (gr[e_e].x >= 1.0f ? 1 : 0);
-      lo[xp] = uniform_i64(j_first - D + 1);
-      const int64_t nwin = j_last + D - lo[xp] + 1;
-      // delay drift beyond 1/16 per tile: flag the template (NaN output)
-      if (nwin > kResWcap || nwin < 2 * D) wbad = true;
-      W[xp] = __builtin_amdgcn_readfirstlane(int(nwin));
-    }
-    if (wbad) {
-      if (tid == 0) atomicOr(status_word, kStatusWindow);
-      return false;
-    }
-    // corrected input samples z_j = x_j exp(-2 pi i f_h (t_src,j - t_j)) from
-    // the sample knots; a zero sample (outside the data, or in a gap) stays
-    // zero
-#pragma unroll 1
-    for (int xp = 0; xp < np; ++xp) {
-      const DetConst& d = P.det[X0 + xp];
-      const int64_t lox = xp ? lo[1] : lo[0];
-      const int Wx = xp ? W[1] : W[0];
-      // window offsets w in [wlo, whi) hold data samples j = lox + w; the
-      // interval records from the one of sample lox on (floor division)
-      const int32_t wlo = lox < 0 ? int32_t(-lox) : 0;
-      const int32_t whi = d.n - lox < int64_t(Wx) ? int32_t(d.n - lox) : Wx;
-      const int32_t jph = int32_t(lox & (G - 1));
-      const double2* sr = kn + (X0 + xp) * P.knot_stride + P.knot_soff + 2 * (lox >> kl);
-      const float2* xs = d.x + lox;
-      float2 xv[kRounds];
-      double2 k0[kRounds], k1[kRounds];
-      // a wave whose lanes all lie past the window skips the round (its
-      // 32-sample blocks lie past the last one a tap reads)
-      const int w0 = __builtin_amdgcn_readfirstlane(tid) & ~63;
-      const bool any = wlo < whi;
+      const double2* ka = kn + (X0 + (xp < np ? xp : 0)) * P.knot_stride;
 #pragma unroll
-      for (int r = 0; r < kRounds; ++r) {
-        const int w = r * kResThreads + tid;
-        const bool in = w >= wlo && w < whi;
-        xv[r] = in ? xs[w] : make_float2(0.f, 0.f);
-        // record of the sample's interval (of the nearest data sample); none
-        // for a wave past the window
-        const bool rec = any && r * kResThreads + w0 < Wx;
-        const int32_t wc = rec ? (w < wlo ? wlo : (w >= whi ? whi - 1 : w)) : wlo;
-        const double2* rc = sr + 2 * ((jph + wc) >> kl);
-        k0[r] = rec ? rc[0] : make_double2(0.0, 0.0);
-        k1[r] = rec ? rc[1] : make_double2(0.0, 0.0);
+      for (int h = 0; h <= kSpanTiles; ++h) {
+        const int32_t e = (k_s + (h < n_t ? h : n_t) * kResTile) >> kl;
+        eth[xp][h] = scalar_load(reinterpret_cast<const float*>(ka) + 4 * e);
+        ei[xp][h] = scalar_load(reinterpret_cast<const int32_t*>(ka + P.knot_ioff) + e);
       }
+    }
+    // samples ja + w, w < W
+    int32_t ja[kDetPass], W[kDetPass];
 #pragma unroll
-      for (int r = 0; r < kRounds; ++r) {
-        if (r * kResThreads + w0 >= Wx) break;
+    for (int xp = 0; xp < kDetPass; ++xp) {
+      int32_t j[kSpanTiles + 1];
+#pragma unroll
+      for (int h = 0; h <= kSpanTiles; ++h)
+        j[h] = k_s + (h < n_t ? h : n_t) * kResTile + ei[xp][h] + (eth[xp][h] >= 1.0f ? 1 : 0);
+      ja[xp] = (j[0] - D + 1) & ~((1 << kKnotLogMax) - 1);
+#pragma unroll
+      for (int h = 0; h < kSpanTiles; ++h) {
+        const int32_t nwin = j[h + 1] - j[h] + 2 * D;
+        // delay drift beyond 1/16 per tile: flag the template (NaN output)
+        wbad |= h < n_t && (nwin > kResWcap || nwin < 2 * D);
+      }
+      W[xp] = j[kSpanTiles] + D - ja[xp] + 1;
+      ja_all[X0 + xp] = ja[xp];
+    }
+    if (wbad) break;
+    // the samples of both detectors and their intervals' records, all loads in
+    // flight at once (rounds past the first kStageRounds: windows stretched
+    // by extreme delays only)
+    float2 xv[kDetPass][kStageRounds];
+#pragma unroll
+    for (int xp = 0; xp < kDetPass; ++xp) {
+      if (xp >= np) break;
+      const DetConst& d = P.det[X0 + xp];
+      const float2* xs = d.x + ja[xp];
+      const uint32_t nx = uint32_t(d.n);
+#pragma unroll
+      for (int r = 0; r < kStageRounds; ++r) {
         const int w = r * kResThreads + tid;
-        const float2 x = xv[r];
+        const bool in = w < W[xp] && uint32_t(ja[xp] + w) < nx;
+        xv[xp][r] = in ? xs[w] : make_float2(0.f, 0.f);
+      }
+    }
+    {
+      const int xp = tid >> 7, p = tid & 127;
+      if (xp < np && p < 2 * kSpanSamp) {
+        const int32_t jx = xp ? ja[1] : ja[0];
+        const int32_t e_max = int32_t(P.det[X0 + xp].n - 1) >> kl;
+        int32_t e = (jx >> kl) + (p >> 1);
+        e = e < 0 ? 0 : (e > e_max ? e_max : e);
+        recs[X0 + xp].samp[p >> 1][p & 1] =
+            kn[(X0 + xp) * P.knot_stride + P.knot_soff + 2 * e + (p & 1)];
+      }
+    }
+    if (X0 == 0) {
+      if (has_grid) {
+        recs[gX].grid[lane] = grec;
+        recs[gX].grid_i[lane] = girec;
+      }
+      if (has_tile) *reinterpret_cast<float4*>(&recs[gX].tile[0][4 * (lane - 40)]) = grec;
+    }
+    __syncthreads();
+    // corrected samples z_j = x_j exp(-2 pi i f_h (t_src,j - t_j)); a zero
+    // sample (outside the data, or in a gap) stays zero
+#pragma unroll
+    for (int xp = 0; xp < kDetPass; ++xp) {
+      if (xp >= np) break;
+      SpanRec& rec = recs[X0 + xp];
+      float2* zx = zsa + (X0 + xp) * kSpanCap;
+      auto put = [&](int wu, float2 x) {
+        const int w = wu + lane;
         const bool live = x.x != 0.f || x.y != 0.f;
         float2 z = make_float2(0.f, 0.f);
         if (live) {
-          // heterodyne phase in quarter turns
-          const double t = double((jph + w) & (G - 1));
-          const double c4 = fma(fma(fma(k1[r].y, t, k1[r].x), t, k0[r].y), t, k0[r].x);
-          const double q = rint(c4);
-          const float2 e = cis_quarter(int(q), static_cast<float>(c4 - q));
-          // x * exp(-2 pi i f_h dl)
-          z = make_float2(x.x * e.x + x.y * e.y, x.y * e.x - x.x * e.y);
+          const double2 k01 = rec.samp[w >> kl][0], k23 = rec.samp[w >> kl][1];
+          z = correct_sample(x, double(w & (G - 1)), k01.x, k01.y, k23.x, k23.y);
         }
-        if (w < Wx) zsa[xp * kResWcap + w] = z;
+        if (w < W[xp]) zx[w] = z;
         // which 32-sample blocks of the window hold a live sample
         const unsigned long long mb = __ballot(live);
-        if ((tid & 63) == 0) {
-          const int b = w >> 5;
-          blka[xp * kResBlk + b] = uint32_t(mb) != 0u;
-          blka[xp * kResBlk + b + 1] = uint32_t(mb >> 32) != 0u;
+        if (lane == 0) {
+          rec.blk[wu >> 5] = uint32_t(mb) != 0u;
+          rec.blk[(wu >> 5) + 1] = uint32_t(mb >> 32) != 0u;
         }
+      };
+#pragma unroll
+      for (int r = 0; r < kStageRounds; ++r) {
+        if (r * kResThreads + w0 >= W[xp]) break;
+        put(r * kResThreads + w0, xv[xp][r]);
+      }
+#pragma unroll 1
+      for (int wu = kStageRounds * kResThreads + w0; wu < W[xp]; wu += kResThreads) {
+        const bool in = wu + lane < W[xp] && uint32_t(ja[xp] + wu + lane) < uint32_t(P.det[X0 + xp].n);
+        put(wu, in ? P.det[X0 + xp].x[ja[xp] + wu + lane] : make_float2(0.f, 0.f));
       }
     }
-    __syncthreads();
-    // interpolation and antenna weighting (each accumulator takes the
-    // detectors in order)
+  }
+  if (wbad) {
+    if (tid == 0) atomicOr(status_word, kStatusWindow);
+    return false;
+  }
+  __syncthreads();
+  // d(angle)/d(grid step) of the sidereal angle x, radians
+  const float dstep = float(-2.0 * kPi * P.sid_rate_cyc * P.dt);
 #pragma unroll 1
-    for (int xp = 0; xp < np; ++xp) {
-      const int X = X0 + xp;
-      const double2* ka = kn + X * P.knot_stride;
-      const float4* gr = reinterpret_cast<const float4*>(ka) + e_s;
-      const int32_t* gi = reinterpret_cast<const int32_t*>(ka + P.knot_ioff) + e_s;
-      const int64_t lox = xp ? lo[1] : lo[0];
-      const int Wx = xp ? W[1] : W[0];
-      const int32_t sb = int32_t(k_s - lox) - (D - 1);
-      if (P.res_taylor) {
-        // the tile's record: uniform, scalar registers
-        const float* tr = reinterpret_cast<const float*>(ka + P.knot_toff +
-                                                         (k_s >> kResTileLog) * kTileRecUnits);
-        float c[kTaylorCoef];
+  for (int h = 0; h < n_t; ++h) {
+    const int32_t k_t = k_s + h * kResTile;
+    float2 acc_a[kResPerThread], acc_b[kResPerThread];
 #pragma unroll
-        for (int n = 0; n < kTaylorCoef; ++n) c[n] = tr[n];
-        const float th_r = tr[kTaylorCoef];
-        const int32_t i_r = __float_as_int(tr[kTaylorCoef + 1]);
+    for (int i = 0; i < kResPerThread; ++i)
+      acc_a[i] = acc_b[i] = make_float2(0.f, 0.f);
+#pragma unroll 1
+    for (int X = 0; X < P.ndet; ++X) {
+      const SpanRec& rec = recs[X];
+      const float2* zx = zsa + X * kSpanCap;
+      const int32_t ja = X == 0 ? ja_all[0] : X == 1 ? ja_all[1] : X == 2 ? ja_all[2] : ja_all[3];
+      // the window's live blocks as a bit mask in scalar registers
+      const unsigned long long mask = __ballot(lane < kSpanBlk && rec.blk[lane < kSpanBlk ? lane : 0]);
+      const int32_t sb = k_t - ja - (D - 1);
+      const float* tr = rec.tile[h];
+      const float th_r = tr[kTaylorCoef];
+      const int32_t i_r = __float_as_int(tr[kTaylorCoef + 1]);
 #pragma unroll
-        for (int i = 0; i < kResPerThread; ++i) {
-          const int kk = tid + i * kResThreads;
-          const float4 cq = gr[kk >> kl];
-          const int32_t im = gi[kk >> kl];
-          const float v = float(kk & (G - 1)) * inv_gf;
-          const float th = fmaf(fmaf(fmaf(cq.w, v, cq.z), v, cq.y), v, cq.x);
-          const float fl = floorf(th);
-          float f = th - fl;
-          int base = sb + im + kk + int(fl);
-          if (f >= 1.0f) {
-            f = 0.0f;
-            base += 1;
-          }
-          // sidereal angle offset from the tile's middle point
-          const float d = (float(kk - kResTile / 2 + (im - i_r)) + (th - th_r)) * dstep;
-          interp_point_taylor<D>(zsa + xp * kResWcap, blka + xp * kResBlk, Wx, base, f, d, c,
-                                 acc_a[i], acc_b[i]);
+      for (int i = 0; i < kResPerThread; ++i) {
+        const int kk = tid + i * kResThreads;
+        const int e = (h * kResTile + kk) >> kl;
+        const float4 cq = rec.grid[e];
+        const int32_t im = rec.grid_i[e];
+        const float v = float(kk & (G - 1)) * inv_gf;
+        const float th = fmaf(fmaf(fmaf(cq.w, v, cq.z), v, cq.y), v, cq.x);
+        const float fl = floorf(th);
+        float f = th - fl;
+        int base = sb + im + kk + int(fl);
+        if (f >= 1.0f) {
+          f = 0.0f;
+          base += 1;
         }
-      } else {
-#pragma unroll
-        for (int i = 0; i < kResPerThread; ++i) {
-          const int kk = tid + i * kResThreads;
-          const float4 cq = gr[kk >> kl];
-          const int32_t im = gi[kk >> kl];
-          const float v = float(kk & (G - 1)) * inv_gf;
-          const float th = fmaf(fmaf(fmaf(cq.w, v, cq.z), v, cq.y), v, cq.x);
-          const float fl = floorf(th);
-          float f = th - fl;
-          int base = sb + im + kk + int(fl);
-          if (f >= 1.0f) {
-            f = 0.0f;
-            base += 1;
-          }
-          base = base < 0 ? 0 : (base > Wx - 2 * D ? Wx - 2 * D : base);
-          if (!taps_live<D>(blka + xp * kResBlk, base)) continue;
-          const float2 zh = sinc_interp<D>(f, zsa + xp * kResWcap + base);
+        // monotonic T_k keeps the taps in the window, the clamp guards memory
+        base = base < 0 ? 0 : (base > kSpanCap - 2 * D ? kSpanCap - 2 * D : base);
+        // taps that all fall on zero samples add nothing (they reach two
+        // blocks at most)
+        if (((mask >> (base >> 5)) & 3u) == 0u) continue;
+        const float2 zh = sinc_interp<D>(f, zx + base);
+        if (P.res_taylor) {
+          // sidereal angle offset from the tile's middle point
+          const float dx = (float(kk - kResTile / 2 + (im - i_r)) + (th - th_r)) * dstep;
+          weight_taylor(zh, dx, tr, acc_a[i], acc_b[i]);
+        } else {
           // q = u - k - off
           const double q = (double(im) - P.det[X].off) + double(th);
-          weight_add(P, tp, X, tau_s + P.dt * double(kk), q, zh, acc_a[i], acc_b[i]);
+          weight_add(P, tp, X, P.tau0 + P.dt * double(k_t + kk), q, zh, acc_a[i], acc_b[i]);
         }
       }
     }
-    if (X0 + kDetPass < P.ndet) __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kResPerThread; ++i)
+      store(k_t + tid + i * kResThreads, acc_a[i], acc_b[i]);
   }
   return true;
 }
@@ -883,40 +990,42 @@ __device__ __forceinline__ bool knots_ahead(const ResTarget& r) {
   return r.kn != nullptr && r.tp->knot_log2 >= kKnotLogGlobal;
 }
 template <bool GROUPED>
-__device__ __forceinline__ void res_store(const ResTarget& r, int64_t k_s,
-                                          const float2 (&acc_a)[kResPerThread],
-                                          const float2 (&acc_b)[kResPerThread]) {
-#pragma unroll
-  for (int i = 0; i < kResPerThread; ++i) {
-    const int64_t k = k_s + threadIdx.x + i * kResThreads;
-    if (GROUPED) {
-      r.ya[k] = acc_a[i];
-      r.yb[k] = acc_b[i];
-    } else {
-      // spin-down phase and sub-bin offset: y = acc * exp(-2 pi i cyc)
-      const float2 e = spindown_rotation(r.tp->sd, k);
-      r.ya[k] = cmul_exact(acc_a[i], e);
-      r.yb[k] = cmul_exact(acc_b[i], e);
-    }
+__device__ __forceinline__ void res_store(const ResTarget& r, int64_t k, float2 a, float2 b) {
+  if (GROUPED) {
+    r.ya[k] = a;
+    r.yb[k] = b;
+  } else {
+    // spin-down phase and sub-bin offset: y = acc * exp(-2 pi i cyc)
+    const float2 e = spindown_rotation(r.tp->sd, k);
+    r.ya[k] = cmul_exact(a, e);
+    r.yb[k] = cmul_exact(b, e);
   }
 }
 
-// Templates whose knots were solved ahead: one tile per block.  Without the
-// in-tile timing the kernel fits 96 registers without spills, five waves per
-// SIMD, which covers the tile's memory latencies better (binary workload, per
-// template: 102 us at four waves, 89 at five, 96 at six with 48 bytes
-// spilled, 153 at eight).
+// Templates whose knots were solved ahead: `span` tiles per block (at most
+// kSpanTiles), as one span where the LDS records hold it (knot spacings of 32
+// and 64), else tile by tile.
 template <int D, bool GROUPED>
 __global__ __launch_bounds__(kResThreads, kResWavesAhead) void k_resample(PlanConst P, void* ws,
-                                                                       ChunkMap map, int slots) {
+                                                                       ChunkMap map, int slots,
+                                                                       int span) {
+  extern __shared__ float2 zs[];
   const ResTarget r = res_target<GROUPED>(P, ws, map, slots);
   if (!r.live || !knots_ahead(r)) return;
-  __shared__ float2 zs[kDetPass * kResWcap];
-  __shared__ int32_t blk[kDetPass * kResBlk];
-  const int64_t k_s = int64_t(blockIdx.x) * kResTile;
-  float2 acc_a[kResPerThread], acc_b[kResPerThread];
-  if (!resample_tile_gk<D>(P, *r.tp, r.kn, r.status, k_s, zs, blk, acc_a, acc_b)) return;
-  res_store<GROUPED>(r, k_s, acc_a, acc_b);
+  const int32_t tiles = int32_t(P.k_pad >> kResTileLog);
+  const int32_t t_b = int32_t(blockIdx.x) * span;
+  const int32_t t_e = t_b + span < tiles ? t_b + span : tiles;
+  SpanRec* recs = reinterpret_cast<SpanRec*>(zs + P.ndet * kSpanCap);
+  const int kl = uniform_i32(r.tp->knot_log2);
+  const int step = kl > kKnotLogGlobal ? span : 1;
+#pragma unroll 1
+  for (int32_t t = t_b; t < t_e; t += step) {
+    if (t != t_b) __syncthreads();  // the last tile has read the window
+    const int n_t = t_e - t < step ? t_e - t : step;
+    if (!resample_span<D>(P, *r.tp, r.kn, kl, r.status, t, n_t, zs, recs,
+                          [&](int32_t k, float2 a, float2 b) { res_store<GROUPED>(r, k, a, b); }))
+      return;
+  }
 }
 
 // The other templates (knot spacing below 16 points, or no knot area): the
@@ -936,7 +1045,9 @@ __global__ __launch_bounds__(kResThreads, 4) void k_resample_own(PlanConst P, vo
     const int64_t k_s = t * kResTile;
     float2 acc_a[kResPerThread], acc_b[kResPerThread];
     if (!resample_tile<D, KEP>(P, *r.tp, r.status, k_s, zs, blk, acc_a, acc_b)) return;
-    res_store<GROUPED>(r, k_s, acc_a, acc_b);
+#pragma unroll
+    for (int i = 0; i < kResPerThread; ++i)
+      res_store<GROUPED>(r, k_s + threadIdx.x + i * kResThreads, acc_a[i], acc_b[i]);
     // the next tile's first phase rewrites what this one's last read
     __syncthreads();
   }

@@ -46,3 +46,31 @@ def test_parameter_blocks_of_every_detector_count(torch_dev, ndet, kepler):
     binding.sync_check()
     assert torch_dev.equal(plain, grouped)
     check_2f(plain, ref)
+
+
+@pytest.mark.parametrize("ndet,D,porb_d,log_g", [(1, 8, 0.5, 6), (2, 8, 0.2, 5), (2, 16, 0.1, 4),
+                                                 (3, 4, 0.2, 5), (4, 12, 0.5, 6)])
+def test_resampling_spans(torch_dev, ndet, D, porb_d, log_g):
+    """Blocks of two tiles (a launch of many tiles) against blocks of one (one
+    template at a time), bit for bit, at every knot spacing solved ahead, with
+    an odd number of tiles, gaps and a ragged end; one template against the
+    oracle."""
+    from paper_2201_00451_amd import binding
+    ds = synth.small_case(seed=95, n=35801, n_fft=1 << 16, ndet=ndet, D=D, binary=True, gaps=True,
+                          ntmpl=32, noise_vars=[1.0, 0.7, 1.4, 0.9][:ndet])
+    ds.templates[:, 5] = 0.3 + 1e-4 * np.arange(32)
+    ds.templates[:, 6] = porb_d * synth.DAY
+    ds = synth.finish(ds)
+    # the knot spacing the library's rule gives these orbits
+    om = 2 * np.pi / (porb_d * synth.DAY)
+    budget = min(2e-7 / ds.f_het, 1e-7 * ds.dt)
+    fits = [(2.0 ** l * ds.dt) ** 4 / 384 * (0.3031 * om ** 4 + 1e-16) <= budget for l in (4, 5, 6)]
+    assert sum(fits) + 3 == log_g
+    dd = binding.DeviceData(ds)
+    k_pad, _, _ = dd.plan.info()
+    assert (k_pad // 512) % 2 == 1 and (k_pad // 512) * 32 >= 2048
+    many = binding.Search(dd, ds.templates, slots=32).run()
+    one = binding.compute_2f(dd, ds.templates)
+    binding.sync_check()
+    assert torch_dev.equal(many, one)
+    check_2f(many[17:18], O.oracle_twoF(ds, ds.templates[17:18]))
