@@ -408,12 +408,13 @@ int64_t rows_items(const fstat_plan* p, const FftVariant& v, int n) {
   return ((int64_t(1) << p->log_rr) / v.lines) * n;
 }
 
-// Resampling kernels for a supported interpolation half-width: knots solved
-// ahead, and the tiles that solve their own timing.
-using ResAheadFn = void (*)(PlanConst, void*, ChunkMap, int, int);
-using ResFn = void (*)(PlanConst, void*, ChunkMap, int);
+// Kernels of the resampling for a supported interpolation half-width: the
+// timing ahead of it (and the tiles that solve their own), and the templates
+// whose knots were solved ahead.
+using TimingFn = void (*)(PlanConst, void*, ChunkMap, int, int);
+using ResFn = void (*)(PlanConst, void*, ChunkMap, int, int);
 template <bool GROUPED>
-ResAheadFn resample_kernel_g(int D) {
+ResFn resample_kernel_g(int D) {
   switch (D) {
     case 4: return &k_resample<4, GROUPED>;
     case 6: return &k_resample<6, GROUPED>;
@@ -425,68 +426,56 @@ ResAheadFn resample_kernel_g(int D) {
   }
 }
 template <bool GROUPED, bool KEP>
-ResFn resample_own_kernel_g(int D) {
+TimingFn timing_kernel_g(int D) {
   switch (D) {
-    case 4: return &k_resample_own<4, GROUPED, KEP>;
-    case 6: return &k_resample_own<6, GROUPED, KEP>;
-    case 8: return &k_resample_own<8, GROUPED, KEP>;
-    case 10: return &k_resample_own<10, GROUPED, KEP>;
-    case 12: return &k_resample_own<12, GROUPED, KEP>;
-    case 16: return &k_resample_own<16, GROUPED, KEP>;
+    case 4: return &k_timing<4, GROUPED, KEP>;
+    case 6: return &k_timing<6, GROUPED, KEP>;
+    case 8: return &k_timing<8, GROUPED, KEP>;
+    case 10: return &k_timing<10, GROUPED, KEP>;
+    case 12: return &k_timing<12, GROUPED, KEP>;
+    case 16: return &k_timing<16, GROUPED, KEP>;
     default: return nullptr;
   }
 }
 // Plans with Keplerian rows take the kernels that carry the Kepler solver.
 bool kepler_plan(const fstat_plan* p) { return (p->desc.flags & FSTAT_PLAN_KEPLER) != 0; }
-using KnotFn = void (*)(PlanConst, void*, ChunkMap, int);
-KnotFn knot_kernel(const fstat_plan* p, bool grouped) {
-  if (kepler_plan(p)) return grouped ? &k_knots<true, true> : &k_knots<false, true>;
-  return grouped ? &k_knots<true, false> : &k_knots<false, false>;
+TimingFn timing_kernel(const fstat_plan* p, bool grouped) {
+  const int D = p->desc.sinc_halfwidth;
+  if (kepler_plan(p))
+    return grouped ? timing_kernel_g<true, true>(D) : timing_kernel_g<false, true>(D);
+  return grouped ? timing_kernel_g<true, false>(D) : timing_kernel_g<false, false>(D);
 }
-// Timing knots of the chunk's groups (grouped) or slots, ahead of the
-// resampling (templates with a coarser knot spacing only; the kernel skips
-// the others).  Nothing when the slots carry no knot area.
-void launch_knots(const fstat_plan* p, const PlanConst& P, const ChunkMap& map, int slots,
-                  bool grouped, int n_res, void* ws, hipStream_t st) {
-  if (n_res < 1 || (!grouped && P.knot_offset == 0)) return;
-  // at the coarsest knot spacing (finer ones loop)
-  int64_t scap = 0;
-  for (int X = 0; X < P.ndet; ++X)
-    scap = std::max<int64_t>(scap, ((P.det[X].n - 1) >> kKnotLogMax) + 2);
-  const int64_t blocks = knot_grid_blocks((P.k_pad >> kKnotLogMax) + 1) +
-                         knot_tile_blocks(P.k_pad) + knot_samp_blocks(scap);
-  hipLaunchKernelGGL(knot_kernel(p, grouped), dim3(unsigned(blocks), n_res, p->desc.ndet),
-                     dim3(kKnotThreads), 0, st, P, ws, map, slots);
-}
-
-constexpr int64_t kSpanMinTiles = 2048;
-ResAheadFn resample_kernel(const fstat_plan* p, bool grouped) {
+ResFn resample_kernel(const fstat_plan* p, bool grouped) {
   const int D = p->desc.sinc_halfwidth;
   return grouped ? resample_kernel_g<true>(D) : resample_kernel_g<false>(D);
 }
-ResFn resample_own_kernel(const fstat_plan* p, bool grouped) {
-  const int D = p->desc.sinc_halfwidth;
-  if (kepler_plan(p))
-    return grouped ? resample_own_kernel_g<true, true>(D) : resample_own_kernel_g<false, true>(D);
-  return grouped ? resample_own_kernel_g<true, false>(D) : resample_own_kernel_g<false, false>(D);
+// The timing of the chunk's groups (grouped) or slots: knot blocks for the
+// coarsest spacing (finer ones loop), then at most 256 blocks per template
+// that walk the tiles of a template solving its own.
+void launch_timing(const fstat_plan* p, const PlanConst& P, const ChunkMap& map, int slots,
+                   bool grouped, int n_res, void* ws, hipStream_t st) {
+  int64_t scap = 0;
+  for (int X = 0; X < P.ndet; ++X)
+    scap = std::max<int64_t>(scap, ((P.det[X].n - 1) >> kKnotLogMax) + 2);
+  const int64_t kblocks = knot_grid_blocks((P.k_pad >> kKnotLogMax) + 1) +
+                          knot_tile_blocks(P.k_pad) + knot_samp_blocks(scap);
+  const int64_t tiles = p->k_pad / kResTile;
+  hipLaunchKernelGGL(timing_kernel(p, grouped),
+                     dim3(unsigned(kblocks * P.ndet + std::min<int64_t>(tiles, 256)), n_res),
+                     dim3(kResThreads), 0, st, P, ws, map, slots, int(kblocks));
 }
-// Both resampling kernels over the chunk's groups (grouped) or slots; each
-// skips the templates the other takes.  The own-timing kernel walks the tiles
-// with at most 256 blocks per template.
+// Two tiles a block halve what a block spends on its records and edges, but
+// also the blocks: below about eight tiles per compute unit the launch is a
+// single wave of blocks and lasts as long as one of them (measured, one
+// against two tiles: 342 tiles 10.2 against 13.4 us, 973 22.1 / 25.8, 2392
+// 26.4 / 25.4, 5076 46.9 / 45.4, 81024 631 / 498).
+constexpr int64_t kSpanMinTiles = 2048;
 void launch_resample(const fstat_plan* p, const PlanConst& P, const ChunkMap& map, int slots,
                      bool grouped, int n_res, void* ws, hipStream_t st) {
   const int64_t tiles = p->k_pad / kResTile;
-  // Two tiles a block halve what a block spends on its records and edges, but
-  // also the blocks: below about eight tiles per compute unit the launch is a
-  // single wave of blocks and lasts as long as one of them (measured, one
-  // against two tiles: 342 tiles 10.2 against 13.4 us, 973 22.1 / 25.8, 2392
-  // 26.4 / 25.4, 5076 46.9 / 45.4, 81024 631 / 498).
   const int span = tiles * n_res >= kSpanMinTiles ? kSpanTiles : 1;
   hipLaunchKernelGGL(resample_kernel(p, grouped), dim3(unsigned((tiles + span - 1) / span), n_res),
                      dim3(kResThreads), span_lds_bytes(p->desc.ndet), st, P, ws, map, slots, span);
-  hipLaunchKernelGGL(resample_own_kernel(p, grouped),
-                     dim3(unsigned(std::min<int64_t>(tiles, 256)), n_res), dim3(kResThreads), 0,
-                     st, P, ws, map, slots);
 }
 
 // Optional per-kernel timing: events recorded before and after each launch.
@@ -543,13 +532,13 @@ fstat_status launch_chunk(const fstat_plan* p, const PlanConst& P, const double*
   const int n_res = grouped ? map.n_grp : n;
   const FftVariant cv = pick_cols(p->log_rr, cols_choice(p), grouped);
   const FftVariant rv = pick_rows(p->log_c, rows_choice(p), forward_row_mode(out));
-  if (!resample_kernel(p, grouped) || !resample_own_kernel(p, grouped) || !cv.fn || !rv.fn)
+  if (!resample_kernel(p, grouped) || !timing_kernel(p, grouped) || !cv.fn || !rv.fn)
     return fail(FSTAT_EINTERNAL, "no kernel for D=%d, FFT lines 2^%d x 2^%d",
                 p->desc.sinc_halfwidth, p->log_rr, p->log_c);
   if (n_res > 0) {
-    // (the knots are timed with the prologue)
+    // (the timing counts with the prologue)
     if ((s = tm.open(0)) != FSTAT_OK) return s;
-    launch_knots(p, P, map, slots, grouped, n_res, ws, st);
+    launch_timing(p, P, map, slots, grouped, n_res, ws, st);
     if ((s = tm.open(1)) != FSTAT_OK) return s;
     launch_resample(p, P, map, slots, grouped, n_res, ws, st);
   }
@@ -735,7 +724,7 @@ fstat_status launch_grad_chunk(const fstat_plan* p, const PlanConst& P, const do
   const unsigned tiles = unsigned(p->k_pad / kResTile);
   hipLaunchKernelGGL(k_prologue, dim3(n), dim3(kParamThreads), 0, st, P, templates, map, ws,
                      map.tmpl[0] == 0);
-  launch_knots(p, P, map, slots, false, n, ws, st);
+  launch_timing(p, P, map, slots, false, n, ws, st);
   launch_resample(p, P, map, slots, false, n, ws, st);
   const FftVariant cv = pick_cols(p->log_rr, cols_choice(p), false);
   const ColsFn cols = reinterpret_cast<ColsFn>(const_cast<void*>(cv.fn));

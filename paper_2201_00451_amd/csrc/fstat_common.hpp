@@ -88,7 +88,7 @@ constexpr int kSampKnots = (kResWcap - 1) / (1 << kKnotLogMin) + 2;
 // Capacities at the smallest such G.
 constexpr int kKnotLogGlobal = 4;
 constexpr int kTileRecUnits = 4;
-// k_knots: blocks of kKnotThreads knots, each block's last knot the next
+// k_timing: blocks of kKnotThreads knots, each block's last knot the next
 // block's first, so that every grid interval finds both its ends in one block.
 constexpr int kKnotThreads = 256;
 __host__ __device__ inline int64_t knot_grid_blocks(int64_t gcap) {

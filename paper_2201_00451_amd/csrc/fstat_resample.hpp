@@ -577,7 +577,7 @@ static_assert(kMaxDet * 64 <= kResThreads && kSpanGrid <= 40 && kSpanTiles * kTi
 static_assert(kDetPass * 128 <= kResThreads && 2 * kSpanSamp <= 128,
               "128 threads load a detector's sample records");
 
-// Templates whose timing knots k_knots solved ahead (knot area kn): a block
+// Templates whose timing knots k_timing solved ahead (knot area kn): a block
 // takes a span of n_t tiles starting at tile t0.  The span's samples of every
 // detector go into LDS corrected, then each tile is interpolated and weighted
 // from the interval records.  A detector's window runs from the span's first
@@ -821,9 +821,96 @@ __device__ __forceinline__ double2 grid_knot(const PlanConst& P, const TmplParam
   return make_double2(dl * P.inv_dt, (rbd - x) / (1.0 + x));
 }
 
+// Resampling kernels.  GROUPED = false: blockIdx.y is a template slot; the
+// spin-down phase is applied and y_a', y_b' go to the slot's arrays 0 and 1.
+// GROUPED = true: blockIdx.y is a sky/orbit group of the chunk; the series is
+// written without the spin-down phase to the group's buffer, which every
+// template of the group reads (the reuse of the sky-dependent barycentring
+// across spin-down templates that Sec. 4.1 measures).
+//
+// Where a resampling block writes, and whether the template (group) is
+// live: a leader whose sky or orbit is invalid invalidates the whole group
+// (its status word tells every member's column pass not to read the buffer).
+struct ResTarget {
+  const TmplParams* tp;
+  int32_t* status;
+  float2* ya;
+  float2* yb;
+  const double2* kn;  // knot area (null: none)
+  bool live;
+};
+template <bool GROUPED>
+__device__ __forceinline__ ResTarget res_target(const PlanConst& P, void* ws, const ChunkMap& map,
+                                                int slots) {
+  const int gi = blockIdx.y;
+  const int slot = GROUPED ? map.grp_slot[gi] : gi;
+  ResTarget r;
+  r.tp = tmpl_params(ws, P, map, slot);
+  r.status = GROUPED ? group_status(ws, P, slots, map.grp_buf[gi])
+                     : &tmpl_params(ws, P, map, slot)->status;
+  r.ya = GROUPED ? group_buf(ws, P, slots, map.grp_buf[gi], 0) : slot_buf(ws, P, slot, 0);
+  r.yb = GROUPED ? group_buf(ws, P, slots, map.grp_buf[gi], 1) : slot_buf(ws, P, slot, 1);
+  r.kn = P.knot_bytes == 0 ? nullptr
+         : GROUPED         ? group_knots(ws, P, slots, map.grp_buf[gi])
+                           : slot_knots(ws, P, slot);
+  r.live = true;
+  if (GROUPED) {
+    const int32_t gflag = r.tp->status & kStatusGroupMask;
+    if (gflag != 0) {
+      if (threadIdx.x == 0 && blockIdx.x == 0) atomicOr(r.status, gflag);
+      r.live = false;
+    }
+  } else if (r.tp->status != 0) {
+    r.live = false;
+  }
+  return r;
+}
+// Whether a template's timing knots were solved ahead (k_timing).
+__device__ __forceinline__ bool knots_ahead(const ResTarget& r) {
+  return r.kn != nullptr && r.tp->knot_log2 >= kKnotLogGlobal;
+}
+template <bool GROUPED>
+__device__ __forceinline__ void res_store(const ResTarget& r, int64_t k, float2 a, float2 b) {
+  if (GROUPED) {
+    r.ya[k] = a;
+    r.yb[k] = b;
+  } else {
+    // spin-down phase and sub-bin offset: y = acc * exp(-2 pi i cyc)
+    const float2 e = spindown_rotation(r.tp->sd, k);
+    r.ya[k] = cmul_exact(a, e);
+    r.yb[k] = cmul_exact(b, e);
+  }
+}
+
+// Templates whose knots were solved ahead: `span` tiles per block (at most
+// kSpanTiles), as one span where the LDS records hold it (knot spacings of 32
+// and 64), else tile by tile.
+template <int D, bool GROUPED>
+__global__ __launch_bounds__(kResThreads, kResWavesAhead) void k_resample(PlanConst P, void* ws,
+                                                                       ChunkMap map, int slots,
+                                                                       int span) {
+  extern __shared__ float2 zs[];
+  const ResTarget r = res_target<GROUPED>(P, ws, map, slots);
+  if (!r.live || !knots_ahead(r)) return;
+  const int32_t tiles = int32_t(P.k_pad >> kResTileLog);
+  const int32_t t_b = int32_t(blockIdx.x) * span;
+  const int32_t t_e = t_b + span < tiles ? t_b + span : tiles;
+  SpanRec* recs = reinterpret_cast<SpanRec*>(zs + P.ndet * kSpanCap);
+  const int kl = uniform_i32(r.tp->knot_log2);
+  const int step = kl > kKnotLogGlobal ? span : 1;
+#pragma unroll 1
+  for (int32_t t = t_b; t < t_e; t += step) {
+    if (t != t_b) __syncthreads();  // the last tile has read the window
+    const int n_t = t_e - t < step ? t_e - t : step;
+    if (!resample_span<D>(P, *r.tp, r.kn, kl, r.status, t, n_t, zs, recs,
+                          [&](int32_t k, float2 a, float2 b) { res_store<GROUPED>(r, k, a, b); }))
+      return;
+  }
+}
+
 // Timing knots of one template (slot) or sky/orbit group whose knot spacing
-// G = 2^tp.knot_log2 is at least 2^kKnotLogGlobal, for the detector
-// blockIdx.z: the same FP64 solves as the tiles' own knots (steps (iv) and
+// G = 2^tp.knot_log2 is at least 2^kKnotLogGlobal, for the detector X and
+// its block b: the same FP64 solves as the tiles' own knots (steps (iv) and
 // (iii) of Sec. 3), one knot per thread, with the Roemer delay from the
 // detector's tabulated trajectory (the interval read last kept in
 // registers).  Three ranges of blocks:
@@ -835,21 +922,11 @@ __device__ __forceinline__ double2 grid_knot(const PlanConst& P, const TmplParam
 //  - the rest solve the sample knots.
 // A delay beyond the plan's max_delay flags the template (as a tile whose
 // delay leaves its staged nodes does).
-template <bool GROUPED, bool KEP>
-__global__ __launch_bounds__(kKnotThreads) void k_knots(PlanConst P, void* ws, ChunkMap map,
-                                                        int slots) {
-  const int gi = blockIdx.y;
-  const int slot = GROUPED ? map.grp_slot[gi] : gi;
-  const TmplParams& tp = *tmpl_params(ws, P, map, slot);
-  if (GROUPED ? (tp.status & kStatusGroupMask) != 0 : tp.status != 0) return;
-  const int kl = tp.knot_log2;
-  if (kl < kKnotLogGlobal) return;
-  int32_t* status_word = GROUPED ? group_status(ws, P, slots, map.grp_buf[gi])
-                                 : &tmpl_params(ws, P, map, slot)->status;
-  const int X = blockIdx.z;
+template <bool KEP>
+__device__ __forceinline__ void solve_knots(const PlanConst& P, const TmplParams& tp, int kl,
+                                            double2* kn, int32_t* status_word, int X, int64_t b) {
   const DetConst& d = P.det[X];
-  double2* kn = (GROUPED ? group_knots(ws, P, slots, map.grp_buf[gi]) : slot_knots(ws, P, slot)) +
-                X * P.knot_stride;
+  kn += X * P.knot_stride;
   const int G = 1 << kl;
   const CachedRoemer re{d.ephem, tp.nhat, P.n_eph, P.eph_t0, P.eph_dt, P.inv_eph_dt};
   // blocks launched per range: enough for the coarsest spacing; a template
@@ -860,7 +937,6 @@ __global__ __launch_bounds__(kKnotThreads) void k_knots(PlanConst P, void* ws, C
   const int64_t gblocks = knot_grid_blocks((P.k_pad >> kKnotLogMax) + 1);
   const int64_t tblocks = knot_tile_blocks(P.k_pad);
   const int64_t sblocks = knot_samp_blocks(scap);
-  const int64_t b = blockIdx.x;
   __shared__ double2 nb[kKnotThreads];
   bool far = false;
   if (b < gblocks) {
@@ -941,107 +1017,32 @@ __global__ __launch_bounds__(kKnotThreads) void k_knots(PlanConst P, void* ws, C
   if (far) atomicOr(status_word, kStatusNodes);
 }
 
-// Resampling kernels.  GROUPED = false: blockIdx.y is a template slot; the
-// spin-down phase is applied and y_a', y_b' go to the slot's arrays 0 and 1.
-// GROUPED = true: blockIdx.y is a sky/orbit group of the chunk; the series is
-// written without the spin-down phase to the group's buffer, which every
-// template of the group reads (the reuse of the sky-dependent barycentring
-// across spin-down templates that Sec. 4.1 measures).
-//
-// Where a resampling block writes, and whether the template (group) is
-// live: a leader whose sky or orbit is invalid invalidates the whole group
-// (its status word tells every member's column pass not to read the buffer).
-struct ResTarget {
-  const TmplParams* tp;
-  int32_t* status;
-  float2* ya;
-  float2* yb;
-  const double2* kn;  // knot area (null: none)
-  bool live;
-};
-template <bool GROUPED>
-__device__ __forceinline__ ResTarget res_target(const PlanConst& P, void* ws, const ChunkMap& map,
-                                                int slots) {
-  const int gi = blockIdx.y;
-  const int slot = GROUPED ? map.grp_slot[gi] : gi;
-  ResTarget r;
-  r.tp = tmpl_params(ws, P, map, slot);
-  r.status = GROUPED ? group_status(ws, P, slots, map.grp_buf[gi])
-                     : &tmpl_params(ws, P, map, slot)->status;
-  r.ya = GROUPED ? group_buf(ws, P, slots, map.grp_buf[gi], 0) : slot_buf(ws, P, slot, 0);
-  r.yb = GROUPED ? group_buf(ws, P, slots, map.grp_buf[gi], 1) : slot_buf(ws, P, slot, 1);
-  r.kn = P.knot_bytes == 0 ? nullptr
-         : GROUPED         ? group_knots(ws, P, slots, map.grp_buf[gi])
-                           : slot_knots(ws, P, slot);
-  r.live = true;
-  if (GROUPED) {
-    const int32_t gflag = r.tp->status & kStatusGroupMask;
-    if (gflag != 0) {
-      if (threadIdx.x == 0 && blockIdx.x == 0) atomicOr(r.status, gflag);
-      r.live = false;
-    }
-  } else if (r.tp->status != 0) {
-    r.live = false;
-  }
-  return r;
-}
-// Whether a template's timing knots were solved ahead (k_knots).
-__device__ __forceinline__ bool knots_ahead(const ResTarget& r) {
-  return r.kn != nullptr && r.tp->knot_log2 >= kKnotLogGlobal;
-}
-template <bool GROUPED>
-__device__ __forceinline__ void res_store(const ResTarget& r, int64_t k, float2 a, float2 b) {
-  if (GROUPED) {
-    r.ya[k] = a;
-    r.yb[k] = b;
-  } else {
-    // spin-down phase and sub-bin offset: y = acc * exp(-2 pi i cyc)
-    const float2 e = spindown_rotation(r.tp->sd, k);
-    r.ya[k] = cmul_exact(a, e);
-    r.yb[k] = cmul_exact(b, e);
-  }
-}
-
-// Templates whose knots were solved ahead: `span` tiles per block (at most
-// kSpanTiles), as one span where the LDS records hold it (knot spacings of 32
-// and 64), else tile by tile.
-template <int D, bool GROUPED>
-__global__ __launch_bounds__(kResThreads, kResWavesAhead) void k_resample(PlanConst P, void* ws,
-                                                                       ChunkMap map, int slots,
-                                                                       int span) {
-  extern __shared__ float2 zs[];
-  const ResTarget r = res_target<GROUPED>(P, ws, map, slots);
-  if (!r.live || !knots_ahead(r)) return;
-  const int32_t tiles = int32_t(P.k_pad >> kResTileLog);
-  const int32_t t_b = int32_t(blockIdx.x) * span;
-  const int32_t t_e = t_b + span < tiles ? t_b + span : tiles;
-  SpanRec* recs = reinterpret_cast<SpanRec*>(zs + P.ndet * kSpanCap);
-  const int kl = uniform_i32(r.tp->knot_log2);
-  const int step = kl > kKnotLogGlobal ? span : 1;
-#pragma unroll 1
-  for (int32_t t = t_b; t < t_e; t += step) {
-    if (t != t_b) __syncthreads();  // the last tile has read the window
-    const int n_t = t_e - t < step ? t_e - t : step;
-    if (!resample_span<D>(P, *r.tp, r.kn, kl, r.status, t, n_t, zs, recs,
-                          [&](int32_t k, float2 a, float2 b) { res_store<GROUPED>(r, k, a, b); }))
-      return;
-  }
-}
-
-// The other templates (knot spacing below 16 points, or no knot area): the
-// tile solves its own timing (four waves per SIMD, 128 registers: its FP64
-// and LDS latency chains hide better with more waves).  A block walks tiles
-// blockIdx.x, + gridDim.x, ..., so that a launch over templates that all had
-// their knots solved ahead is a few thousand blocks that return at once.
+// Ahead of the resampling, per template (slot) or group: the timing knots
+// (kblocks blocks per detector), or, where the knot spacing is below 16
+// points, the whole resampling, the tiles solving their own timing (walked by
+// the blocks past the knots'; their FP64 and LDS latency chains want four waves
+// per SIMD, 128 registers).  Which of the two a template takes is known on the
+// device only; one launch carries both, so a bank of either kind pays for one
+// kernel (a launch of the tiles alone, whose blocks all return at once, took
+// 2-5 us of a small search and 10 us of a large one).
 template <int D, bool GROUPED, bool KEP>
-__global__ __launch_bounds__(kResThreads, 4) void k_resample_own(PlanConst P, void* ws,
-                                                               ChunkMap map, int slots) {
+__global__ __launch_bounds__(kResThreads, 4) void k_timing(PlanConst P, void* ws, ChunkMap map,
+                                                           int slots, int kblocks) {
+  static_assert(kKnotThreads == kResThreads, "one block size for both");
   const ResTarget r = res_target<GROUPED>(P, ws, map, slots);
-  if (!r.live || knots_ahead(r)) return;
+  if (!r.live) return;
+  const int b = blockIdx.x, nk = kblocks * P.ndet;
+  if (b < nk) {
+    if (knots_ahead(r))
+      solve_knots<KEP>(P, *r.tp, r.tp->knot_log2, const_cast<double2*>(r.kn), r.status,
+                       b / kblocks, b % kblocks);
+    return;
+  }
+  if (knots_ahead(r)) return;
   __shared__ float2 zs[kDetPass * kResWcap];
   __shared__ int32_t blk[kDetPass * kResBlk];
   const int64_t tiles = P.k_pad / kResTile;
-  for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+  for (int64_t t = b - nk; t < tiles; t += int(gridDim.x) - nk) {
     const int64_t k_s = t * kResTile;
     float2 acc_a[kResPerThread], acc_b[kResPerThread];
     if (!resample_tile<D, KEP>(P, *r.tp, r.status, k_s, zs, blk, acc_a, acc_b)) return;
