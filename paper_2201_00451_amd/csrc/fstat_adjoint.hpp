@@ -67,13 +67,14 @@ constexpr int kGradParams = 7;  // df, f1dot, alpha, delta, asini, porb, tp
 // and 1 hold conj(X)).  ONEHOT = true (single-bin path): L = 2F(m) at one bin
 // m, so H is non-zero only at m and X_k = H_m exp(-2 pi i m k / N) in closed
 // form; the slot holds no arrays.
-// Two waves per SIMD (249 registers at two outputs per thread, no spills).
+// The timing of every grid point and sample is solved (FP64): the templates
+// that k_grad_span does not take.  Two waves per SIMD (249 registers at two
+// outputs per thread, no spills); a block walks tiles.
 template <int D, bool ONEHOT, bool KEP>
-__global__ __launch_bounds__(kResThreads, 2) void k_grad(PlanConst P, void* ws) {
-  const int slot = blockIdx.y;
+__device__ __forceinline__ void grad_tile(const PlanConst& P, void* ws, int slot, int64_t tile) {
   const TmplParams& tp = *slot_params(ws, P, slot);
-  double* partial = slot_partials(ws, P, slot) + size_t(blockIdx.x) * 8;
-  const int64_t k_s = int64_t(blockIdx.x) * kResTile;
+  double* partial = slot_partials(ws, P, slot) + size_t(tile) * 8;
+  const int64_t k_s = tile * kResTile;
   const int tid = threadIdx.x;
 
   __shared__ float2 zs[kResWcap];
@@ -85,10 +86,6 @@ __global__ __launch_bounds__(kResThreads, 2) void k_grad(PlanConst P, void* ws) 
   __shared__ int bad;
   __shared__ double red[kResThreads / 64][kGradParams];
 
-  if (tp.status != 0) {
-    if (tid < 8) partial[tid] = 0.0;
-    return;
-  }
   if (tid == 0) bad = 0;
   bool oob = false;
   const bool binary = tp.asini != 0.0;
@@ -325,6 +322,18 @@ __global__ __launch_bounds__(kResThreads, 2) void k_grad(PlanConst P, void* ws) 
     double v = 0.0;
     for (int w = 0; w < kResThreads / 64; ++w) v += red[w][tid];
     partial[tid] = bad ? __builtin_nan("") : v;
+  }
+}
+
+template <int D, bool ONEHOT, bool KEP>
+__global__ __launch_bounds__(kResThreads, 2) void k_grad(PlanConst P, void* ws) {
+  const int slot = blockIdx.y;
+  const TmplParams& tp = *slot_params(ws, P, slot);
+  if (tp.status != 0 || span_timed(P, tp)) return;
+  const int64_t tiles = P.k_pad / kResTile;
+  for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+    grad_tile<D, ONEHOT, KEP>(P, ws, slot, t);
+    __syncthreads();
   }
 }
 

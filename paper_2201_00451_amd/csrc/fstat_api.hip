@@ -17,6 +17,7 @@
 #include "fstat_prologue.hpp"
 #include "fstat_resample.hpp"
 #include "fstat_adjoint.hpp"
+#include "fstat_refine.hpp"
 #include "fstat_sft.hpp"
 
 using namespace fstat;
@@ -646,42 +647,61 @@ size_t grad_slot_bytes(const fstat_plan* p) {
   return slot_bytes(p->desc.n_fft, 4, grad_part_bytes(p) + knot_area_bytes(p));
 }
 
+// The gradient kernels and the single-bin transforms come in pairs, one for
+// the templates whose timing is smooth over a tile (span) and one that solves
+// every point; which one a template takes is known on the device only, so both
+// are launched and each skips the other's templates.
 using GradFn = void (*)(PlanConst, void*);
 template <bool ONEHOT, bool KEP>
-GradFn grad_kernel_o(int D) {
+GradFn grad_kernel_o(int D, bool span) {
   switch (D) {
-    case 4: return &k_grad<4, ONEHOT, KEP>;
-    case 6: return &k_grad<6, ONEHOT, KEP>;
-    case 8: return &k_grad<8, ONEHOT, KEP>;
-    case 10: return &k_grad<10, ONEHOT, KEP>;
-    case 12: return &k_grad<12, ONEHOT, KEP>;
-    case 16: return &k_grad<16, ONEHOT, KEP>;
+    case 4: return span ? &k_grad_span<4, ONEHOT, KEP> : &k_grad<4, ONEHOT, KEP>;
+    case 6: return span ? &k_grad_span<6, ONEHOT, KEP> : &k_grad<6, ONEHOT, KEP>;
+    case 8: return span ? &k_grad_span<8, ONEHOT, KEP> : &k_grad<8, ONEHOT, KEP>;
+    case 10: return span ? &k_grad_span<10, ONEHOT, KEP> : &k_grad<10, ONEHOT, KEP>;
+    case 12: return span ? &k_grad_span<12, ONEHOT, KEP> : &k_grad<12, ONEHOT, KEP>;
+    case 16: return span ? &k_grad_span<16, ONEHOT, KEP> : &k_grad<16, ONEHOT, KEP>;
     default: return nullptr;
   }
 }
-GradFn grad_kernel(const fstat_plan* p, bool onehot) {
+GradFn grad_kernel(const fstat_plan* p, bool onehot, bool span) {
   const int D = p->desc.sinc_halfwidth;
   if (kepler_plan(p))
-    return onehot ? grad_kernel_o<true, true>(D) : grad_kernel_o<false, true>(D);
-  return onehot ? grad_kernel_o<true, false>(D) : grad_kernel_o<false, false>(D);
+    return onehot ? grad_kernel_o<true, true>(D, span) : grad_kernel_o<false, true>(D, span);
+  return onehot ? grad_kernel_o<true, false>(D, span) : grad_kernel_o<false, false>(D, span);
 }
 
 using BinFn = void (*)(PlanConst, void*, ChunkMap, const int64_t*);
 template <bool KEP>
-BinFn resample_bin_kernel_k(int D) {
+BinFn bin_kernel_k(int D, bool span) {
   switch (D) {
-    case 4: return &k_resample_bin<4, KEP>;
-    case 6: return &k_resample_bin<6, KEP>;
-    case 8: return &k_resample_bin<8, KEP>;
-    case 10: return &k_resample_bin<10, KEP>;
-    case 12: return &k_resample_bin<12, KEP>;
-    case 16: return &k_resample_bin<16, KEP>;
+    case 4: return span ? &k_bin_span<4, KEP> : &k_resample_bin<4, KEP>;
+    case 6: return span ? &k_bin_span<6, KEP> : &k_resample_bin<6, KEP>;
+    case 8: return span ? &k_bin_span<8, KEP> : &k_resample_bin<8, KEP>;
+    case 10: return span ? &k_bin_span<10, KEP> : &k_resample_bin<10, KEP>;
+    case 12: return span ? &k_bin_span<12, KEP> : &k_resample_bin<12, KEP>;
+    case 16: return span ? &k_bin_span<16, KEP> : &k_resample_bin<16, KEP>;
     default: return nullptr;
   }
 }
-BinFn resample_bin_kernel(const fstat_plan* p) {
-  return kepler_plan(p) ? resample_bin_kernel_k<true>(p->desc.sinc_halfwidth)
-                        : resample_bin_kernel_k<false>(p->desc.sinc_halfwidth);
+BinFn bin_kernel(const fstat_plan* p, bool span) {
+  return kepler_plan(p) ? bin_kernel_k<true>(p->desc.sinc_halfwidth, span)
+                        : bin_kernel_k<false>(p->desc.sinc_halfwidth, span);
+}
+// Blocks per template of a pair's kernels: spans of kSpanTiles tiles, and at
+// most 256 blocks that walk the tiles.
+unsigned span_blocks(const fstat_plan* p) {
+  return unsigned((p->k_pad / kResTile + kSpanTiles - 1) / kSpanTiles);
+}
+unsigned walk_blocks(const fstat_plan* p) {
+  return unsigned(std::min<int64_t>(p->k_pad / kResTile, 256));
+}
+void launch_grad(const fstat_plan* p, const PlanConst& P, bool onehot, int n, void* ws,
+                 hipStream_t st) {
+  hipLaunchKernelGGL(grad_kernel(p, onehot, true), dim3(span_blocks(p), n), dim3(kResThreads),
+                     span_lds_bytes(p->desc.ndet), st, P, ws);
+  hipLaunchKernelGGL(grad_kernel(p, onehot, false), dim3(walk_blocks(p), n), dim3(kResThreads), 0,
+                     st, P, ws);
 }
 
 // Single-bin adjoint slot: the parameter block and 8 doubles of partials per
@@ -702,12 +722,13 @@ fstat_status launch_grad_bin_chunk(const fstat_plan* p, const PlanConst& P,
   const unsigned tiles = unsigned(p->k_pad / kResTile);
   hipLaunchKernelGGL(k_prologue, dim3(n), dim3(kParamThreads), 0, st, P, templates, map, ws,
                      map.tmpl[0] == 0);
-  hipLaunchKernelGGL(resample_bin_kernel(p), dim3(tiles, n),
-                     dim3(kResThreads), 0, st, P, ws, map, bins);
+  hipLaunchKernelGGL(bin_kernel(p, true), dim3(span_blocks(p), n), dim3(kResThreads),
+                     span_lds_bytes(p->desc.ndet), st, P, ws, map, bins);
+  hipLaunchKernelGGL(bin_kernel(p, false), dim3(walk_blocks(p), n), dim3(kResThreads), 0, st, P,
+                     ws, map, bins);
   hipLaunchKernelGGL(k_bin_final, dim3(n), dim3(kFinalThreads), 0, st, P, ws, map,
                      int64_t(tiles), bins, twoF);
-  hipLaunchKernelGGL(grad_kernel(p, true), dim3(tiles, n),
-                     dim3(kResThreads), 0, st, P, ws);
+  launch_grad(p, P, true, n, ws, st);
   hipLaunchKernelGGL(k_grad_final, dim3(n), dim3(kFinalThreads), 0, st, P, ws, map,
                      int64_t(tiles), grad);
   return check_hip(hipGetLastError(), "single-bin adjoint launch");
@@ -744,8 +765,7 @@ fstat_status launch_grad_chunk(const fstat_plan* p, const PlanConst& P, const do
   hipLaunchKernelGGL(reinterpret_cast<RowsFn>(const_cast<void*>(rc.fn)), rgrid_c, dim3(rc.threads),
                      rc.lds, st, P, ws, map, slots, p->log_rr,
                      row_output(nullptr, nullptr));
-  hipLaunchKernelGGL(grad_kernel(p, false), dim3(tiles, n),
-                     dim3(kResThreads), 0, st, P, ws);
+  launch_grad(p, P, false, n, ws, st);
   hipLaunchKernelGGL(k_grad_final, dim3(n), dim3(kFinalThreads), 0, st, P, ws, map,
                      int64_t(tiles), grad);
   return check_hip(hipGetLastError(), "adjoint launch");

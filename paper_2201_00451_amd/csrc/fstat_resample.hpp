@@ -78,7 +78,10 @@ template <int D>
 __host__ __device__ constexpr int tap_odd_terms(int m) {
   return m >= (3 * D + 3) / 4 ? kTapCoef - 1 : kTapCoef;
 }
-template <int D, int M>
+// DERIV: the same for the derivative dh/ds (within 5e-8 of it per unit of its
+// largest value, pi/2): the pair is then E_m(g^2) + g O_m(g^2) and, h' being
+// odd, g O_m(g^2) - E_m(g^2).
+template <int D, int M, bool DERIV = false>
 __host__ __device__ constexpr TapPoly make_tap_poly() {
   constexpr int K = 16, N = 2 * kTapCoef;  // nodes; coefficients of g^0 .. g^9
   double y[K] = {}, cheb[N] = {}, t0[N] = {}, t1[N] = {}, mono[N] = {};
@@ -86,10 +89,15 @@ __host__ __device__ constexpr TapPoly make_tap_poly() {
     const double g = 0.5 * ct_cospi(2 * k + 1, 2 * K);
     const double s = g + M + 0.5;
     // sin(pi s) = (-1)^M cos(pi g)
-    const double sn = ((M & 1) ? -1.0 : 1.0) * ct_poly_cos(kPi * g);
-    y[k] = sn / (kPi * s) * 0.5 * (1.0 + ct_poly_cos(kPi * s / D));
+    const double sgn = (M & 1) ? -1.0 : 1.0;
+    const double sinc = sgn * ct_poly_cos(kPi * g) / (kPi * s);
+    const double win = 0.5 * (1.0 + ct_poly_cos(kPi * s / D));
+    y[k] = sinc * win;
+    if (DERIV)  // cos(pi s) = -(-1)^M sin(pi g)
+      y[k] = (-sgn * ct_poly_sin(kPi * g) - sinc) / s * win -
+             sinc * 0.5 * kPi / D * ct_poly_sin(kPi * s / D);
   }
-  const int deg = kTapCoef - 1 + tap_odd_terms<D>(M);
+  const int deg = DERIV ? 2 * kTapCoef - 1 : kTapCoef - 1 + tap_odd_terms<D>(M);
   for (int j = 0; j <= deg; ++j) {
     for (int k = 0; k < K; ++k) cheb[j] += y[k] * ct_cospi(j * (2 * k + 1), 2 * K);
     cheb[j] *= (j == 0 ? 1.0 : 2.0) / K;
@@ -219,14 +227,14 @@ __device__ __forceinline__ void interp_point(const PlanConst& P, const TmplParam
 // tile takes this form.  c[0..5]: a_0..a_5, c[6..11]: b_0..b_5.
 constexpr int kTaylorCoef = 12;
 static_assert(kTaylorCoef + 2 <= kTileRecUnits * 4, "a tile record holds the coefficients");
-__device__ inline void antenna_taylor(const TmplParams& tp, int X, double x_cyc,
+__device__ inline void antenna_taylor(const float* ka, const float* kb, double x_cyc,
                                       float (&c)[kTaylorCoef]) {
   const float2 e = cis_cycles(x_cyc);
   const float c1 = e.x, s1 = e.y;
   const float c2 = c1 * c1 - s1 * s1, s2 = 2.0f * s1 * c1;
 #pragma unroll
   for (int ab = 0; ab < 2; ++ab) {
-    const float* k = ab ? tp.cb[X] : tp.ca[X];
+    const float* k = ab ? kb : ka;
     // value p and derivative q of the first and second harmonic at x_r
     const float p1 = k[1] * c1 + k[2] * s1, q1 = k[2] * c1 - k[1] * s1;
     const float p2 = k[3] * c2 + k[4] * s2, q2 = k[4] * c2 - k[3] * s2;
@@ -805,20 +813,46 @@ __device__ __forceinline__ bool resample_span(const PlanConst& P, const TmplPara
   return true;
 }
 
-// Grid knot at k: q = (T_k - tau_k)/dt from the detector epoch of tau = tau0 +
-// k dt (fixed point and two Newton steps) and dq/dk = (R'(tau) - roemer'(T)) /
-// (1 + roemer'(T)); far: the delay exceeds the plan's max_delay.
+// Grid knot at k (a whole or fractional grid point): q = (T_k - tau_k)/dt from
+// the detector epoch of tau = tau0 + k dt (fixed point and two Newton steps)
+// and dq/dk = (R'(tau) - roemer'(T)) / (1 + roemer'(T)); far: the delay exceeds
+// `limit`.
 template <bool KEP>
 __device__ __forceinline__ double2 grid_knot(const PlanConst& P, const TmplParams& tp,
-                                             const CachedRoemer& re, int64_t k, bool& far) {
-  const double tau = P.tau0 + P.dt * double(k);
+                                             const CachedRoemer& re, double k, double limit,
+                                             bool& far) {
+  const double tau = P.tau0 + P.dt * k;
   double rb, rbd, x;
   orbit_delay<KEP>(tp, tau, rb, rbd);
   double dl = grid_delay_rb(re, rb, tau);
   dl = grid_delay_newton(re, tau, rb, dl, x);
   dl = grid_delay_newton(re, tau, rb, dl, x);
-  far = !(fabs(dl) <= P.max_delay);
+  far = !(fabs(dl) <= limit);
   return make_double2(dl * P.inv_dt, (rbd - x) / (1.0 + x));
+}
+
+// The record of a grid interval from its end knots a, b (g grid steps apart;
+// last: the point past the grid, its position only): the source position
+// relative to its integer part as a cubic (resample_span).
+__device__ __forceinline__ void grid_record(double off, double2 a, double2 b, double g, bool last,
+                                            float4& rec, int32_t& whole) {
+  double2 c0 = make_double2(a.x, 0.0), c1 = make_double2(0.0, 0.0);
+  if (!last) hermite_interval(a, b, g, c0, c1);
+  const double x = off + c0.x;
+  const double fx = floor(x);
+  rec = make_float4(float(x - fx), float(c0.y), float(c1.x), float(c1.y));
+  whole = int32_t(fx);
+}
+// The record of a sample interval from its end knots (phase in cycles, change
+// per sample), g samples apart: quarter turns as a cubic in the sample offset
+// (scalings by powers of two: exact), the constant modulo one turn.
+__device__ __forceinline__ void sample_record(double2 a, double2 b, double g, double2& lo,
+                                              double2& hi) {
+  double2 c0, c1;
+  hermite_interval(a, b, g, c0, c1);
+  const double ig = 1.0 / g;
+  lo = make_double2(fmod(4.0 * c0.x, 4.0), 4.0 * c0.y * ig);
+  hi = make_double2(4.0 * c1.x * ig * ig, 4.0 * c1.y * ig * ig * ig);
 }
 
 // Resampling kernels.  GROUPED = false: blockIdx.y is a template slot; the
@@ -947,24 +981,15 @@ __device__ __forceinline__ void solve_knots(const PlanConst& P, const TmplParams
       double2 kv = make_double2(0.0, 0.0);
       if (e <= last) {
         bool f;
-        kv = grid_knot<KEP>(P, tp, re, e * G, f);
+        kv = grid_knot<KEP>(P, tp, re, double(e * G), P.max_delay, f);
         far |= f;
       }
       nb[threadIdx.x] = kv;
       __syncthreads();
       if (threadIdx.x < kKnotThreads - 1 && e <= last) {
-        double2 c0, c1;
-        if (e < last) {
-          hermite_interval(kv, nb[threadIdx.x + 1], double(G), c0, c1);
-        } else {
-          c0 = make_double2(kv.x, 0.0);
-          c1 = make_double2(0.0, 0.0);
-        }
-        const double a = d.off + c0.x;
-        const double fa = floor(a);
-        reinterpret_cast<float4*>(kn)[e] =
-            make_float4(float(a - fa), float(c0.y), float(c1.x), float(c1.y));
-        reinterpret_cast<int32_t*>(kn + P.knot_ioff)[e] = int32_t(fa);
+        grid_record(d.off, kv, nb[threadIdx.x + 1], double(G), e == last,
+                    reinterpret_cast<float4*>(kn)[e],
+                    reinterpret_cast<int32_t*>(kn + P.knot_ioff)[e]);
       }
       __syncthreads();
     }
@@ -974,10 +999,11 @@ __device__ __forceinline__ void solve_knots(const PlanConst& P, const TmplParams
       // the tile's middle point is a knot (G divides half a tile)
       const int64_t k = (t << kResTileLog) + kResTile / 2;
       bool far_t;
-      const double2 kv = grid_knot<KEP>(P, tp, re, k, far_t);
+      const double2 kv = grid_knot<KEP>(P, tp, re, double(k), P.max_delay, far_t);
       float c[kTaylorCoef];
-      antenna_taylor(tp, X, tp.alpha_cyc[X] - P.sid_rate_cyc * (P.tau0 + P.dt * double(k) +
-                                                                kv.x * P.dt), c);
+      antenna_taylor(tp.ca[X], tp.cb[X],
+                     tp.alpha_cyc[X] - P.sid_rate_cyc * (P.tau0 + P.dt * double(k) + kv.x * P.dt),
+                     c);
       const double a = d.off + kv.x;
       const double fa = floor(a);
       float* tr = reinterpret_cast<float*>(kn + P.knot_toff + t * kTileRecUnits);
@@ -1003,13 +1029,8 @@ __device__ __forceinline__ void solve_knots(const PlanConst& P, const TmplParams
       nb[threadIdx.x] = kv;
       __syncthreads();
       if (threadIdx.x < kKnotThreads - 1 && m < last) {
-        double2 c0, c1;
-        hermite_interval(kv, nb[threadIdx.x + 1], double(G), c0, c1);
-        // in quarter turns and in t = u G (scalings by powers of two: exact)
-        const double ig = 1.0 / double(G);
         double2* rec = kn + P.knot_soff + 2 * m;
-        rec[0] = make_double2(fmod(4.0 * c0.x, 4.0), 4.0 * c0.y * ig);
-        rec[1] = make_double2(4.0 * c1.x * ig * ig, 4.0 * c1.y * ig * ig * ig);
+        sample_record(kv, nb[threadIdx.x + 1], double(G), rec[0], rec[1]);
       }
       __syncthreads();
     }
@@ -1068,48 +1089,54 @@ __host__ __device__ inline int64_t band_bin_nat(const PlanConst& P, int64_t i) {
 // Single-bin forward path: the whitened transforms Fa'(m), Fb'(m) at one bin
 // m per template as a direct sum over the grid, sum_k y'_k exp(-2 pi i m k/N)
 // (step (vi) restricted to one output bin), reduced per tile into the slot's
-// partials (Fa'.re, Fa'.im, Fb'.re, Fb'.im in FP64).
+// partials (Fa'.re, Fa'.im, Fb'.re, Fb'.im in FP64).  The templates whose
+// timing is solved point by point (the others: k_bin_span); a block walks
+// tiles.
+__device__ bool span_timed(const PlanConst& P, const TmplParams& tp);
 template <int D, bool KEP>
 __global__ __launch_bounds__(kResThreads, 4) void k_resample_bin(PlanConst P, void* ws, ChunkMap map,
                                                              const int64_t* __restrict__ bins) {
   const int slot = blockIdx.y;
   TmplParams* tpp = slot_params(ws, P, slot);
   const TmplParams& tp = *tpp;
-  double* partial = slot_partials(ws, P, slot) + size_t(blockIdx.x) * 8;
-  const int64_t k_s = int64_t(blockIdx.x) * kResTile;
   const int tid = threadIdx.x;
-  if (tp.status != 0) return;
+  if (tp.status != 0 || span_timed(P, tp)) return;
   __shared__ float2 zs[kDetPass * kResWcap];
   __shared__ int32_t blk[kDetPass * kResBlk];
-  float2 acc_a[kResPerThread], acc_b[kResPerThread];
-  if (!resample_tile<D, KEP>(P, tp, &tpp->status, k_s, zs, blk, acc_a, acc_b)) return;
-  const int64_t bin = bins[map.tmpl[slot]];
-  const int64_t nat = band_bin_nat(P, bin);
-  double s[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int i = 0; i < kResPerThread; ++i) {
-    const int64_t k = k_s + tid + i * kResThreads;
-    const float2 e = cmul(spindown_rotation(tp.sd, k),
-                          bin_twiddle(nat, k, P.n_fft));
-    const float2 ya = cmul(acc_a[i], e), yb = cmul(acc_b[i], e);
-    s[0] += double(ya.x);
-    s[1] += double(ya.y);
-    s[2] += double(yb.x);
-    s[3] += double(yb.y);
-  }
   __shared__ double red[kResThreads / 64][4];
-  const int lane = tid & 63, wave = tid >> 6;
+  const int64_t nat = band_bin_nat(P, bins[map.tmpl[slot]]);
+  const int64_t tiles = P.k_pad / kResTile;
+  for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+    double* partial = slot_partials(ws, P, slot) + size_t(t) * 8;
+    const int64_t k_s = t * kResTile;
+    float2 acc_a[kResPerThread], acc_b[kResPerThread];
+    if (!resample_tile<D, KEP>(P, tp, &tpp->status, k_s, zs, blk, acc_a, acc_b)) return;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    double v = s[q];
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    if (lane == 0) red[wave][q] = v;
-  }
-  __syncthreads();
-  if (tid < 4) {
-    double v = 0.0;
-    for (int w = 0; w < kResThreads / 64; ++w) v += red[w][tid];
-    partial[tid] = v;
+    for (int i = 0; i < kResPerThread; ++i) {
+      const int64_t k = k_s + tid + i * kResThreads;
+      const float2 e = cmul(spindown_rotation(tp.sd, k),
+                            bin_twiddle(nat, k, P.n_fft));
+      const float2 ya = cmul(acc_a[i], e), yb = cmul(acc_b[i], e);
+      s[0] += double(ya.x);
+      s[1] += double(ya.y);
+      s[2] += double(yb.x);
+      s[3] += double(yb.y);
+    }
+    const int lane = tid & 63, wave = tid >> 6;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      double v = s[q];
+      for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+      if (lane == 0) red[wave][q] = v;
+    }
+    __syncthreads();
+    if (tid < 4) {
+      double v = 0.0;
+      for (int w = 0; w < kResThreads / 64; ++w) v += red[w][tid];
+      partial[tid] = v;
+    }
+    __syncthreads();
   }
 }
 

@@ -5,12 +5,15 @@ import numpy as np
 import pytest
 
 from oracle import fstat_oracle as O
+from oracle import fstat_oracle_grad as G
 from paper_2201_00451_amd import synth
 
 pytestmark = pytest.mark.gpu
 
 # the forward path's bar against the oracle
 RTOL, ATOL = 1e-4, 1e-3
+# the gradients' bar (that of the finite differences)
+GRAD_RTOL = 1e-3
 
 
 @pytest.fixture(scope="module")
@@ -74,3 +77,68 @@ def test_resampling_spans(torch_dev, ndet, D, porb_d, log_g):
     binding.sync_check()
     assert torch_dev.equal(many, one)
     check_2f(many[17:18], O.oracle_twoF(ds, ds.templates[17:18]))
+
+
+def orbit_case(porb_d, asini, ndet, D, n, ecc=None):
+    """A search whose injection has the given orbit, and a row off it in every
+    parameter."""
+    extra = dict(ecc=ecc, argp=0.6) if ecc is not None else {}
+    ds = synth.small_case(seed=97, n=n, n_fft=1 << 13, ndet=ndet, D=D, binary=True, gaps=True,
+                          ntmpl=1, rho=25, noise_vars=[1.0, 0.7, 1.4, 0.9][:ndet], **extra)
+    inj = ds.injections[0]
+    inj.update(asini=asini, porb=porb_d * synth.DAY)
+    ds.x, _ = synth.make_data(ds.detectors, ds.dt, ds.f_het, 0.0, [inj], 97, gaps=ds.valid)
+    ds.templates[:, 5], ds.templates[:, 6] = asini, inj["porb"]
+    ds = synth.finish(ds)
+    row = ds.templates[0].copy()
+    T = n * ds.dt
+    row[0] += 0.002
+    row[1] -= 0.0015
+    row[2] += 0.3 / T
+    row[3] += 0.5 / T ** 2
+    row[5] *= 1.001
+    row[6] *= 1.0 + 2e-5
+    row[7] += 1.0
+    return ds, row
+
+
+@pytest.mark.parametrize("porb_d,asini,ndet,D,n,ecc,smooth,log_g",
+                         [(0.5, 0.05, 2, 8, 3000, None, True, 6),    # spans of two tiles
+                          (0.14, 0.05, 4, 16, 2700, None, True, 5),  # G = 32, every detector
+                          (0.13, 0.6, 2, 4, 3300, None, True, 4),    # G = 16: tile by tile
+                          (0.5, 0.1, 3, 8, 3000, 0.3, True, 6),      # eccentric, three detectors
+                          (0.05, 0.004, 2, 8, 3000, None, False, 5)])  # solved point by point
+def test_gradients_by_tile_smoothness(torch_dev, porb_d, asini, ndet, D, n, ecc, smooth, log_g):
+    """Both gradient forms against the FP64 oracle for orbits on either side of
+    the rule that decides between quintics per tile and per-point solves, at
+    each knot spacing."""
+    from paper_2201_00451_amd import binding
+    ds, row = orbit_case(porb_d, asini, ndet, D, n, ecc)
+    om = 2 * np.pi / (porb_d * synth.DAY)
+    e2 = (1 - (ecc or 0.0)) ** 2
+    budget = min(2e-7 / ds.f_het, 1e-7 * ds.dt)
+    fits = [(2.0 ** l * ds.dt) ** 4 / 384 * (row[5] * (om / e2) ** 4 + 1e-16) <= budget
+            for l in (2, 3, 4, 5, 6)]
+    assert sum(fits) + 1 == log_g
+    assert (om * 256 * ds.dt <= 0.3 * e2) == smooth
+    dd = binding.DeviceData(ds)
+    tf = O.oracle_twoF(ds, row[None])[0]
+    m = int(np.argmax(tf))
+    w = np.zeros(ds.n_bins)
+    w[m - 2:m + 3] = [0.2, 0.5, 1.0, 0.7, 0.1]
+    one = np.zeros(ds.n_bins)
+    one[m] = 1.0
+    g_bin, tf_bin = binding.compute_2f_grad_bin(dd, row[None], [m])
+    g_gen, tf_gen = binding.compute_2f_grad(dd, row[None], w[None], want_twoF=True)
+    plain = binding.compute_2f(dd, row[None])
+    binding.sync_check()
+    assert torch_dev.equal(tf_gen, plain)
+    check_2f(plain, tf[None])
+    assert abs(float(tf_bin[0]) - tf[m]) <= RTOL * tf[m]
+    for got, weights in ((g_bin, one), (g_gen, w)):
+        _, ref = G.oracle_grad(ds, row, weights)
+        got = got.cpu().numpy()[0]
+        for i, name in enumerate(G.PARAMS):
+            print(f"  {name:6s} gpu {got[i]: .9e} oracle {ref[i]: .9e} "
+                  f"rel {abs(got[i] - ref[i]) / abs(ref[i]):.1e}", flush=True)
+            assert abs(got[i] - ref[i]) <= GRAD_RTOL * abs(ref[i]), name
