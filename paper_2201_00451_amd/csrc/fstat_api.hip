@@ -89,7 +89,13 @@ struct FftVariant {
   int lines;     // columns (column pass) or rows of each array (row pass) per item
 };
 
-// Variant choice of the FFT passes: full or half line counts (512 or 256
+// The row passes' stages have radix at most 16 (kRowsMlr): at lines of 2^9 and
+// 2^10 radix 32 saves a trip through LDS, but its registers allow one workgroup
+// per compute unit (measured per launch, radix 32 against 16: 32 templates of
+// 2^20 points, plain 2F 188 / 133 us, accumulated 901 / 348; of 2^18 42 / 35;
+// four templates of 2^20 28 / 24, of 2^18 10.2 / 11.9).
+constexpr int kRowsMlr = 4;
+// Variant choice of the column pass: full or half line counts (512 or 256
 // threads), largest stage radix 2^mlr (mlr 4 or 5; only line lengths 2^9 and
 // 2^10 have a different stage plan with 2^5).
 struct FftChoice {
@@ -114,8 +120,13 @@ FftVariant cols_half_lds_variant() {
   return {reinterpret_cast<const void*>(&k_fft_cols_half<LOGL, NL, 512, GROUPED, MLR>), 512, lds,
           NL};
 }
+// Lines whose passes have a variant for small launches: short ones.
+template <int LOGL>
+constexpr bool kFewLines = LOGL <= 9;
 template <int LOGL, bool GROUPED, int MLR>
-FftVariant cols_variant(bool half) {
+FftVariant cols_variant(bool half, bool few) {
+  if constexpr (kFewLines<LOGL>)
+    if (half && few) return cols_variant_n<LOGL, GROUPED, MLR, kColsMax<LOGL> / 4, 256>();
   if (half) return cols_variant_n<LOGL, GROUPED, MLR, kColsMax<LOGL> / 2, 256>();
   if constexpr (LOGL >= 11) return cols_half_lds_variant<LOGL, GROUPED, MLR>();
   return cols_variant_n<LOGL, GROUPED, MLR, kColsMax<LOGL>, 512>();
@@ -134,83 +145,66 @@ FftVariant rows_variant_n() {
   }
   return {reinterpret_cast<const void*>(&k_fft_rows<LOGL, RQ, NT, MODE, MLR>), NT, lds, RQ};
 }
-// The plain 2F pass at the full row count holds one array at a time in LDS
-// (k_fft_rows_split), so two 512-thread workgroups share a compute unit; with
-// radix-32 stages that does not fit 128 VGPRs, and with fewer than 4 rows per
-// item (lines of 2^12) the shorter 2F runs cost more than the occupancy
-// gains (measured): there the pass keeps both arrays.
-template <int LOGL, int MLR, int MODE>
+// At the full row count lines of up to 2^11 points hold one array at a time in
+// LDS (k_fft_rows_split), so two 512-thread workgroups share a compute unit.
+template <int LOGL, int MODE>
 FftVariant rows_split_variant() {
-  constexpr int RQ = kRowsMax<LOGL>, R0 = kR0<LOGL, MLR>;
-  return {reinterpret_cast<const void*>(&k_fft_rows_split<LOGL, RQ, 512, MLR, MODE>), 512,
+  constexpr int RQ = kRowsMax<LOGL>, R0 = kR0<LOGL, kRowsMlr>;
+  return {reinterpret_cast<const void*>(&k_fft_rows_split<LOGL, RQ, 512, kRowsMlr, MODE>), 512,
           kLdsBytes<1 << LOGL, R0, RQ, RQ>, RQ};
 }
-// The adjoint, conjugate and extended epilogues of a radix-32 plan exceed 256
-// VGPRs at the full count: they take the half count (the same arithmetic per
-// point, so the same bits as the full-count plain 2F kernel).
-// Candidates and loudest bin only: the split pass where the plain 2F pass
-// takes it (no 2F array is written), else the extended epilogue.
-template <int LOGL, int MODE, int MLR>
-FftVariant rows_variant(bool half) {
-  if constexpr (MODE == kRowCand) {
-    if constexpr (kR0<LOGL, MLR> <= 16 && kRowsMax<LOGL> >= 4) {
-      if (!half) return rows_split_variant<LOGL, MLR, kRowCand>();
-    }
-    // rows of 2^12: the half-LDS pass with the candidate epilogue
-    if constexpr (LOGL >= 12) {
-      if (!half) return rows_variant_n<LOGL, kRowCand, MLR, kRowsMax<LOGL>, 512>();
-    }
-    return rows_variant<LOGL, kRow2FExt, MLR>(half);
-  } else if constexpr (MODE != kRow2F && kR0<LOGL, MLR> == 32) {
-    return rows_variant_n<LOGL, MODE, MLR, kRowsMax<LOGL> / 2, 256>();
-  } else {
-    if (half) return rows_variant_n<LOGL, MODE, MLR, kRowsMax<LOGL> / 2, 256>();
-    if constexpr (MODE == kRow2F && kR0<LOGL, MLR> <= 16 && kRowsMax<LOGL> >= 4)
-      return rows_split_variant<LOGL, MLR, kRow2F>();
-    return rows_variant_n<LOGL, MODE, MLR, kRowsMax<LOGL>, 512>();
-  }
+// Every epilogue of one shape gives the plain 2F pass's bits (the same
+// arithmetic per point).  Candidates and loudest bin without a 2F array have
+// an epilogue of their own at the full row count, else the extended one.
+// few: a launch too small to fill the chip takes a quarter of the rows per
+// item, both arrays at once (k_fft_rows).
+template <int LOGL, int MODE>
+FftVariant rows_variant(bool half, bool few) {
+  if (half)
+    return rows_variant_n<LOGL, MODE == kRowCand ? int(kRow2FExt) : MODE, kRowsMlr,
+                          kRowsMax<LOGL> / 2, 256>();
+  if constexpr (kFewLines<LOGL> && MODE != kRowCand)
+    if (few) return rows_variant_n<LOGL, MODE, kRowsMlr, kRowsMax<LOGL> / 4, 256>();
+  if constexpr (kRowsMax<LOGL> >= 4) return rows_split_variant<LOGL, MODE>();
+  else return rows_variant_n<LOGL, MODE, kRowsMlr, kRowsMax<LOGL>, 512>();
 }
 
 template <bool GROUPED, int MLR>
-FftVariant pick_cols_v(int logl, bool half) {
+FftVariant pick_cols_v(int logl, bool half, bool few) {
   switch (logl) {
-    case 6: return cols_variant<6, GROUPED, 4>(half);
-    case 7: return cols_variant<7, GROUPED, 4>(half);
-    case 8: return cols_variant<8, GROUPED, 4>(half);
-    case 9: return cols_variant<9, GROUPED, MLR>(half);
-    case 10: return cols_variant<10, GROUPED, MLR>(half);
-    case 11: return cols_variant<11, GROUPED, 4>(half);
-    case 12: return cols_variant<12, GROUPED, 4>(half);
+    case 6: return cols_variant<6, GROUPED, 4>(half, few);
+    case 7: return cols_variant<7, GROUPED, 4>(half, few);
+    case 8: return cols_variant<8, GROUPED, 4>(half, few);
+    case 9: return cols_variant<9, GROUPED, MLR>(half, few);
+    case 10: return cols_variant<10, GROUPED, MLR>(half, few);
+    case 11: return cols_variant<11, GROUPED, 4>(half, few);
+    case 12: return cols_variant<12, GROUPED, 4>(half, few);
     default: return {nullptr, 0, 0, 1};
   }
 }
-FftVariant pick_cols(int logl, const FftChoice& c, bool grouped) {
-  if (c.mlr == 5) return grouped ? pick_cols_v<true, 5>(logl, c.half) : pick_cols_v<false, 5>(logl, c.half);
-  return grouped ? pick_cols_v<true, 4>(logl, c.half) : pick_cols_v<false, 4>(logl, c.half);
-}
-template <int MODE, int MLR>
-FftVariant pick_rows_v(int logl, bool half) {
-  switch (logl) {
-    case 6: return rows_variant<6, MODE, 4>(half);
-    case 7: return rows_variant<7, MODE, 4>(half);
-    case 8: return rows_variant<8, MODE, 4>(half);
-    case 9: return rows_variant<9, MODE, MLR>(half);
-    case 10: return rows_variant<10, MODE, MLR>(half);
-    case 11: return rows_variant<11, MODE, 4>(half);
-    case 12: return rows_variant<12, MODE, 4>(half);
-    default: return {nullptr, 0, 0, 1};
-  }
+FftVariant pick_cols(int logl, const FftChoice& c, bool grouped, bool few) {
+  if (c.mlr == 5) return grouped ? pick_cols_v<true, 5>(logl, c.half, few) : pick_cols_v<false, 5>(logl, c.half, few);
+  return grouped ? pick_cols_v<true, 4>(logl, c.half, few) : pick_cols_v<false, 4>(logl, c.half, few);
 }
 template <int MODE>
-FftVariant pick_rows_m(int logl, const FftChoice& c) {
-  return c.mlr == 5 ? pick_rows_v<MODE, 5>(logl, c.half) : pick_rows_v<MODE, 4>(logl, c.half);
+FftVariant pick_rows_m(int logl, bool half, bool few) {
+  switch (logl) {
+    case 6: return rows_variant<6, MODE>(half, few);
+    case 7: return rows_variant<7, MODE>(half, few);
+    case 8: return rows_variant<8, MODE>(half, few);
+    case 9: return rows_variant<9, MODE>(half, few);
+    case 10: return rows_variant<10, MODE>(half, few);
+    case 11: return rows_variant<11, MODE>(half, few);
+    case 12: return rows_variant<12, MODE>(half, few);
+    default: return {nullptr, 0, 0, 1};
+  }
 }
-FftVariant pick_rows(int logl, const FftChoice& c, int mode = kRow2F) {
-  return mode == kRowAdjoint ? pick_rows_m<kRowAdjoint>(logl, c)
-         : mode == kRowConj  ? pick_rows_m<kRowConj>(logl, c)
-         : mode == kRow2FExt ? pick_rows_m<kRow2FExt>(logl, c)
-         : mode == kRowCand  ? pick_rows_m<kRowCand>(logl, c)
-                             : pick_rows_m<kRow2F>(logl, c);
+FftVariant pick_rows(int logl, bool half, int mode, bool few) {
+  return mode == kRowAdjoint ? pick_rows_m<kRowAdjoint>(logl, half, few)
+         : mode == kRowConj  ? pick_rows_m<kRowConj>(logl, half, few)
+         : mode == kRow2FExt ? pick_rows_m<kRow2FExt>(logl, half, few)
+         : mode == kRowCand  ? pick_rows_m<kRowCand>(logl, half, few)
+                             : pick_rows_m<kRow2F>(logl, half, few);
 }
 // The forward epilogue a RowOutput needs: plain 2F stores, candidates and
 // loudest bin without a 2F array, or the extended one.
@@ -221,7 +215,27 @@ int forward_row_mode(const RowOutput& out) {
 }
 
 FftChoice cols_choice(const fstat_plan* p) { return {p->cols_half, p->fft_mlr}; }
-FftChoice rows_choice(const fstat_plan* p) { return {p->rows_half, p->fft_mlr}; }
+
+// The column and the row pass of n templates.  A launch that leaves compute
+// units idle or with one workgroup each lasts as long as one workgroup's chain
+// of load, stages and store, so with the automatic line counts it takes a
+// quarter of the lines of the largest count (the same arithmetic per line, so
+// the same bits): up to two 256-thread workgroups per unit of the column pass,
+// one 512-thread workgroup of the row pass.  Measured, default against small
+// items: 11 templates of 2^17 points columns 13.6 / 11.0 us, rows 10.0 / 8.1; 7
+// of 2^17 with Fa and Fb 9.0 / 7.8 and 11.2 / 7.9; 12 of 2^18 (768 and 384
+// default items) rows 15 / 21.
+constexpr int64_t kFewCols = 512, kFewRows = 256;
+FftVariant cols_for(const fstat_plan* p, bool grouped, int64_t n) {
+  const int64_t items = ((int64_t(1) << p->log_c) / p->cols_lines) * 2 * n;
+  return pick_cols(p->log_rr, cols_choice(p), grouped,
+                   p->desc.tune_col_lines == 0 && items <= kFewCols);
+}
+FftVariant rows_for(const fstat_plan* p, int mode, int64_t n) {
+  const int64_t items = ((int64_t(1) << p->log_rr) / p->rows_lines) * n;
+  return pick_rows(p->log_c, p->rows_half, mode,
+                   p->desc.tune_row_lines == 0 && items <= kFewRows);
+}
 
 fstat_status check_hip(hipError_t e, const char* what) {
   if (e != hipSuccess) return fail(FSTAT_EHIP, "%s: %s", what, hipGetErrorString(e));
@@ -531,8 +545,8 @@ fstat_status launch_chunk(const fstat_plan* p, const PlanConst& P, const double*
                      map.tmpl[0] == 0);
   }
   const int n_res = grouped ? map.n_grp : n;
-  const FftVariant cv = pick_cols(p->log_rr, cols_choice(p), grouped);
-  const FftVariant rv = pick_rows(p->log_c, rows_choice(p), forward_row_mode(out));
+  const FftVariant cv = cols_for(p, grouped, n);
+  const FftVariant rv = rows_for(p, forward_row_mode(out), n);
   if (!resample_kernel(p, grouped) || !timing_kernel(p, grouped) || !cv.fn || !rv.fn)
     return fail(FSTAT_EINTERNAL, "no kernel for D=%d, FFT lines 2^%d x 2^%d",
                 p->desc.sinc_halfwidth, p->log_rr, p->log_c);
@@ -586,18 +600,19 @@ fstat_status finish_timer(KernelTimer& tm, hipStream_t st, float* kernel_ms, int
 
 fstat_status set_lds_limits(const fstat_plan* p) {
   hipError_t e = hipSuccess;
-  for (bool grouped : {false, true}) {
-    const FftVariant v = pick_cols(p->log_rr, cols_choice(p), grouped);
+  for (int k = 0; k < 4; ++k) {
+    const FftVariant v = pick_cols(p->log_rr, cols_choice(p), (k & 1) != 0, (k & 2) != 0);
     if (!v.fn) return fail(FSTAT_EINTERNAL, "no column kernel for lines of 2^%d", p->log_rr);
     e = hipFuncSetAttribute(v.fn, hipFuncAttributeMaxDynamicSharedMemorySize, int(v.lds));
     if (e != hipSuccess) return check_hip(e, "hipFuncSetAttribute(cols)");
   }
-  for (int mode : {int(kRow2F), int(kRowAdjoint), int(kRowConj), int(kRow2FExt), int(kRowCand)}) {
-    const FftVariant v = pick_rows(p->log_c, rows_choice(p), mode);
-    if (!v.fn) return fail(FSTAT_EINTERNAL, "no row kernel for lines of 2^%d", p->log_c);
-    e = hipFuncSetAttribute(v.fn, hipFuncAttributeMaxDynamicSharedMemorySize, int(v.lds));
-    if (e != hipSuccess) return check_hip(e, "hipFuncSetAttribute(rows)");
-  }
+  for (bool few : {false, true})
+    for (int mode : {int(kRow2F), int(kRowAdjoint), int(kRowConj), int(kRow2FExt), int(kRowCand)}) {
+      const FftVariant v = pick_rows(p->log_c, p->rows_half, mode, few);
+      if (!v.fn) return fail(FSTAT_EINTERNAL, "no row kernel for lines of 2^%d", p->log_c);
+      e = hipFuncSetAttribute(v.fn, hipFuncAttributeMaxDynamicSharedMemorySize, int(v.lds));
+      if (e != hipSuccess) return check_hip(e, "hipFuncSetAttribute(rows)");
+    }
   return FSTAT_OK;
 }
 
@@ -747,11 +762,11 @@ fstat_status launch_grad_chunk(const fstat_plan* p, const PlanConst& P, const do
                      map.tmpl[0] == 0);
   launch_timing(p, P, map, slots, false, n, ws, st);
   launch_resample(p, P, map, slots, false, n, ws, st);
-  const FftVariant cv = pick_cols(p->log_rr, cols_choice(p), false);
+  const FftVariant cv = cols_for(p, false, n);
   const ColsFn cols = reinterpret_cast<ColsFn>(const_cast<void*>(cv.fn));
   const dim3 cgrid(fft_grid(cv, cols_items(p, cv, n)));
-  const FftVariant ra = pick_rows(p->log_c, rows_choice(p), kRowAdjoint);
-  const FftVariant rc = pick_rows(p->log_c, rows_choice(p), kRowConj);
+  const FftVariant ra = rows_for(p, kRowAdjoint, n);
+  const FftVariant rc = rows_for(p, kRowConj, n);
   const dim3 rgrid_a(fft_grid(ra, rows_items(p, ra, n))),
       rgrid_c(fft_grid(rc, rows_items(p, rc, n)));
   hipLaunchKernelGGL(cols, cgrid, dim3(cv.threads), cv.lds, st, P, ws, map, slots, 0,

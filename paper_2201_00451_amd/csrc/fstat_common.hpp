@@ -377,7 +377,11 @@ __device__ __forceinline__ void buf_store2(float2 x, __amdgpu_buffer_rsrc_t r, u
   using V = decltype(__builtin_amdgcn_raw_buffer_load_b64(r, 0, 0, 0));
   __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(V, x), r, voff, soff, 0);
 }
-// One float; an offset at or past the descriptor's end drops the store.
+// One float; an offset at or past the descriptor's end reads zero, or drops
+// the store.
+__device__ __forceinline__ float buf_load1(__amdgpu_buffer_rsrc_t r, uint32_t voff) {
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, voff, 0, 0));
+}
 __device__ __forceinline__ void buf_store1(float x, __amdgpu_buffer_rsrc_t r, uint32_t voff) {
   __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), r, voff, 0, 0);
 }

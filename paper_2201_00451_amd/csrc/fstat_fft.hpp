@@ -901,16 +901,18 @@ k_fft_rows_half(
   }
 }
 
-// Plain 2F row pass holding one array at a time: the RQ rows of y_a' are
-// transformed and |Fa'|^2 of every bin the thread owns is kept in registers,
-// then the same rows of y_b' reuse the LDS lines and the thread writes
-// 2F = 2 (|Fa'|^2 + |Fb'|^2) (the same arithmetic, so the same bits, as
-// k_fft_rows), or, with MODE kRowCand, keeps the bins above the threshold and
-// the loudest bin instead of writing 2F.  With RQ lines of LDS instead of 2 RQ, two workgroups share a
-// compute unit (the launch bound asks for registers to match) while the 2F
-// runs stay RQ floats long.  At lines of 2^11 the compiler keeps two LDS
-// offsets in scratch; recomputing the offsets in each pass instead measured
-// 3 % slower.
+// Row pass holding one array at a time, every epilogue: the RQ rows of the
+// first array are transformed and the thread keeps what its bins need of them
+// (|Fa'|^2, or Fa' where the caller asked for it), then the same rows of the
+// second array reuse the LDS lines and the thread writes 2F = 2 (|Fa'|^2 +
+// |Fb'|^2) (the same arithmetic, so the same bits, as k_fft_rows), keeps the
+// bins above the threshold and the loudest bin (kRowCand), adds to 2F and
+// writes Fa, Fb (kRow2FExt), or writes each array's adjoint spectrum or
+// conjugate transform as it comes (kRowAdjoint, kRowConj).  With RQ lines of
+// LDS instead of 2 RQ, two workgroups share a compute unit (the launch bound
+// asks for registers to match) while the 2F runs stay RQ floats long.  At
+// lines of 2^11 the compiler keeps two LDS offsets in scratch; recomputing the
+// offsets in each pass instead measured 3 % slower.
 template <int LOGL, int RQ, int NT, int MLR, int MODE>
 __global__ __launch_bounds__(NT, NT / 128) void k_fft_rows_split(PlanConst P, void* ws,
                                                                   ChunkMap map, int slots,
@@ -935,18 +937,26 @@ __global__ __launch_bounds__(NT, NT / 128) void k_fft_rows_split(PlanConst P, vo
   }
   const RowItem it =
       rows_item<MODE>(P, ws, map, int(xcd_remap(blockIdx.x, gridDim.x)), int(Rr / RQ), RQ);
-  if (it.flagged) rows_flagged<LOGL, RQ, NT>(P, ws, it, Rr, out);
+  if (it.flagged && MODE != kRowConj) rows_flagged<LOGL, RQ, NT>(P, ws, it, Rr, out);
   if (!it.live) return;
-  const auto tf = buf_rsrc(MODE == kRow2F ? out.twoF + it.tmpl * P.n_bins : nullptr,
-                           MODE == kRow2F ? uint32_t(P.n_bins * int64_t(sizeof(float))) : 0u);
+  // band offsets o = ((nat + N/2) mod N) - bin_lo in 32 bits; the descriptors
+  // span this template's n_bins values, so the store of a bin outside the band
+  // (o >= n_bins, also when the subtraction wraps) is dropped and its load
+  // gives zero; an absent output has an empty descriptor
+  constexpr bool kHas2F = MODE == kRow2F || MODE == kRow2FExt || MODE == kRowAdjoint;
+  const uint32_t band = uint32_t(P.n_bins * int64_t(sizeof(float)));
+  const auto tf = buf_rsrc(kHas2F && out.twoF ? out.twoF + it.tmpl * P.n_bins : nullptr,
+                           kHas2F && out.twoF ? band : 0u);
   const uint32_t nmask = uint32_t(P.n_fft - 1), lo = uint32_t(P.bin_lo);
   const uint32_t ostep = uint32_t(Rr * PL);
-  float pa[PER][RL];
+  constexpr bool kKeepF = MODE == kRow2FExt;
+  float pa[kKeepF ? 1 : PER][kKeepF ? 1 : RL];
+  float2 fa[kKeepF ? PER : 1][kKeepF ? RL : 1];
 #pragma unroll
   for (int arr = 0; arr < 2; ++arr) {
     // the a pass's last stage has finished reading the lines
     if (arr == 1) __syncthreads();
-    const auto rs = buf_rsrc(slot_buf(ws, P, it.g, arr),
+    const auto rs = buf_rsrc(slot_buf(ws, P, it.g, (MODE == kRowConj ? 2 : 0) + arr),
                              uint32_t(P.n_fft * int64_t(sizeof(float2))));
     float2 v[PER0][R0];
 #pragma unroll
@@ -981,19 +991,77 @@ __global__ __launch_bounds__(NT, NT / 128) void k_fft_rows_split(PlanConst P, vo
 #pragma unroll
         for (int j = 0; j < RL; ++j) u[j] = lds[Lay::template at_step<PL>(i, j, ql)];
         twiddle_dft<RL, PL, L>(u, i, twl);
+        const uint32_t n0 = uint32_t(it.q0 + ql + Rr * i);
+        const uint32_t o0 = n0 + uint32_t(P.n_fft / 2);
+        if constexpr (MODE == kRowConj) {
+          // the transform itself, conjugated, at the natural index below k_pad
+          const auto wr = buf_rsrc(slot_buf(ws, P, it.g, arr),
+                                   uint32_t(P.k_pad * int64_t(sizeof(float2))));
+#pragma unroll
+          for (int m = 0; m < RL; ++m)
+            buf_store2(make_float2(u[m].x, -u[m].y), wr,
+                       (n0 + uint32_t(m) * ostep) * uint32_t(sizeof(float2)), 0);
+          continue;
+        }
+        if constexpr (MODE == kRowAdjoint) {
+          // H = g conj(F') at every natural index, zero outside the band
+          const auto wr = buf_rsrc(slot_buf(ws, P, it.g, 2 + arr),
+                                   uint32_t(P.n_fft * int64_t(sizeof(float2))));
+          const auto gr = buf_rsrc(out.gin + it.tmpl * P.n_bins, band);
+          float gv[RL];
+#pragma unroll
+          for (int m = 0; m < RL; ++m)
+            gv[m] = buf_load1(gr, (((o0 + uint32_t(m) * ostep) & nmask) - lo) *
+                                      uint32_t(sizeof(float)));
+#pragma unroll
+          for (int m = 0; m < RL; ++m)
+            buf_store2(make_float2(gv[m] * u[m].x, -gv[m] * u[m].y), wr,
+                       (n0 + uint32_t(m) * ostep) * uint32_t(sizeof(float2)), 0);
+        }
+        if constexpr (kKeepF) {
+          if (out.fafb) {
+            // undo the whitening: Fa = l11 Fa', Fb = l21 Fa' + l22 Fb'
+            const auto ab = buf_rsrc(out.fafb + (it.tmpl * 2 + arr) * P.n_bins, 2 * band);
+#pragma unroll
+            for (int m = 0; m < RL; ++m) {
+              const uint32_t o = ((o0 + uint32_t(m) * ostep) & nmask) - lo;
+              const float2 f = arr == 0 ? cscale(u[m], it.l11)
+                                        : make_float2(it.l21 * fa[s][m].x + it.l22 * u[m].x,
+                                                      it.l21 * fa[s][m].y + it.l22 * u[m].y);
+              // (an offset past the band wraps only beyond 2^29 bins)
+              buf_store2(f, ab, o * uint32_t(sizeof(float2)), 0);
+            }
+          }
+        }
         if (arr == 0) {
 #pragma unroll
-          for (int m = 0; m < RL; ++m) pa[s][m] = fmaf(u[m].x, u[m].x, u[m].y * u[m].y);
+          for (int m = 0; m < RL; ++m) {
+            if constexpr (kKeepF) fa[s][m] = u[m];
+            else pa[s][m] = fmaf(u[m].x, u[m].x, u[m].y * u[m].y);
+          }
         } else {
-          const uint32_t o0 = uint32_t(it.q0 + ql + Rr * i) + uint32_t(P.n_fft / 2);
+          float old[RL];
+          if constexpr (kKeepF) {
+            // (every load before the first store)
+#pragma unroll
+            for (int m = 0; m < RL; ++m)
+              old[m] = out.acc ? buf_load1(tf, (((o0 + uint32_t(m) * ostep) & nmask) - lo) *
+                                                   uint32_t(sizeof(float)))
+                               : 0.0f;
+          }
 #pragma unroll
           for (int m = 0; m < RL; ++m) {
             const uint32_t o = ((o0 + uint32_t(m) * ostep) & nmask) - lo;
-            const float v2 = 2.0f * (pa[s][m] + fmaf(u[m].x, u[m].x, u[m].y * u[m].y));
-            if constexpr (MODE == kRow2F) {
-              buf_store1(v2, tf, o * uint32_t(sizeof(float)));
-            } else {
+            float p;
+            if constexpr (kKeepF) p = fmaf(fa[s][m].x, fa[s][m].x, fa[s][m].y * fa[s][m].y);
+            else p = pa[s][m];
+            const float v2 = 2.0f * (p + fmaf(u[m].x, u[m].x, u[m].y * u[m].y));
+            if constexpr (MODE == kRowCand) {
               pa[s][m] = v2;
+            } else if constexpr (kKeepF) {
+              buf_store1(out.acc ? old[m] + v2 : v2, tf, o * uint32_t(sizeof(float)));
+            } else {
+              buf_store1(v2, tf, o * uint32_t(sizeof(float)));
             }
           }
         }

@@ -142,3 +142,35 @@ def test_gradients_by_tile_smoothness(torch_dev, porb_d, asini, ndet, D, n, ecc,
             print(f"  {name:6s} gpu {got[i]: .9e} oracle {ref[i]: .9e} "
                   f"rel {abs(got[i] - ref[i]) / abs(ref[i]):.1e}", flush=True)
             assert abs(got[i] - ref[i]) <= GRAD_RTOL * abs(ref[i]), name
+
+
+@pytest.mark.parametrize("log_n", [12, 15, 17, 18, 19, 21])
+def test_fft_items_of_small_and_large_launches(torch_dev, log_n):
+    """The passes' small-launch items, the default ones and the largest line
+    counts give the same bits in every epilogue (plain, Fa and Fb, summed,
+    the adjoint's 2F) on a ragged band, at row lengths 2^6 to 2^11; one template
+    against the oracle."""
+    from paper_2201_00451_amd import binding
+    n_fft = 1 << log_n
+    lo, nb = n_fft // 5 + 1, n_fft // 2 + 3
+    ds = synth.small_case(seed=98, n=2500, n_fft=n_fft, ndet=2, gaps=True, ntmpl=32, rho=20,
+                          bin_lo=lo, n_bins=nb)
+    dd = binding.DeviceData(ds, batch=32)
+    one, ab = binding.compute_2f(dd, ds.templates, fafb=True)
+    many, ab_many = binding.compute_2f_batched(dd, ds.templates, fafb=True)
+    plain = binding.compute_2f_batched(dd, ds.templates)
+    search = binding.Search(dd, ds.templates, slots=32, accumulate=True)
+    total = torch_dev.full((32, nb), 3.0, device="cuda:0")
+    search.run(out=total)
+    w = torch_dev.linspace(0.0, 1.0, nb, device="cuda:0")[None].repeat(3, 1)
+    g1, tf1 = binding.compute_2f_grad(dd, ds.templates[:3], w, want_twoF=True, batch=1)
+    g3, tf3 = binding.compute_2f_grad(dd, ds.templates[:3], w, want_twoF=True, batch=3)
+    lr = log_n // 2
+    wide = binding.DeviceData(ds, batch=32, tune=dict(
+        tune_col_lines=min(64, 16384 >> lr), tune_row_lines=min(32, 8192 >> (log_n - lr))))
+    full, ab_full = binding.compute_2f_batched(wide, ds.templates, fafb=True)
+    binding.sync_check()
+    for a, b in ((one, many), (one, plain), (one, full), (ab, ab_many), (ab, ab_full),
+                 (one + 3.0, total), (one[:3], tf1), (one[:3], tf3), (g1, g3)):
+        assert torch_dev.equal(a, b)
+    check_2f(one[5:6], O.oracle_twoF(ds, ds.templates[5:6]))
