@@ -120,6 +120,19 @@ FftVariant cols_half_lds_variant() {
   return {reinterpret_cast<const void*>(&k_fft_cols_half<LOGL, NL, 512, GROUPED, MLR>), 512, lds,
           NL};
 }
+constexpr int kSplitMinLogRr = 11;
+// The blocked intermediate (inter_at), for searches, whose column pass reads the
+// group buffers and writes the template slots (the other paths transform a slot
+// in place, so an item may write only what it read), where an item has eight columns
+// (of 2^10 points at the half line count, of 2^11 at the full one), with rows of
+// at least 2^11.  Measured, row-major / blocked, us a call: columns x rows
+// 2^11 x 2^12 (32 templates, plain 2F) columns 2050 / 1705 and rows 1655 /
+// 1725; 2^11 x 2^11 with candidates, the whole search 1462 / 1372; 2^10 x 2^11
+// 1682 / 1625.  2^10 x 2^10 gains nothing (columns 100 / 97, rows 75 / 79), and
+// items of sixteen columns write whole lines row-major already.
+bool blocked_inter(const fstat_plan* p) {
+  return p->cols_lines == 1 << kColBlock && p->log_c >= kBlockMinLogC && p->log_rr >= 10;
+}
 // Lines whose passes have a variant for small launches: short ones.
 template <int LOGL>
 constexpr bool kFewLines = LOGL <= 9;
@@ -128,8 +141,8 @@ FftVariant cols_variant(bool half, bool few) {
   if constexpr (kFewLines<LOGL>)
     if (half && few) return cols_variant_n<LOGL, GROUPED, MLR, kColsMax<LOGL> / 4, 256>();
   if (half) return cols_variant_n<LOGL, GROUPED, MLR, kColsMax<LOGL> / 2, 256>();
-  if constexpr (LOGL >= 11) return cols_half_lds_variant<LOGL, GROUPED, MLR>();
-  return cols_variant_n<LOGL, GROUPED, MLR, kColsMax<LOGL>, 512>();
+  if constexpr (LOGL >= kSplitMinLogRr) return cols_half_lds_variant<LOGL, GROUPED, MLR>();
+  else return cols_variant_n<LOGL, GROUPED, MLR, kColsMax<LOGL>, 512>();
 }
 template <int LOGL, int MODE, int MLR, int RQ, int NT>
 FftVariant rows_variant_n() {
@@ -142,8 +155,9 @@ FftVariant rows_variant_n() {
     constexpr int RH = kR0<LOGL - 1, MLR>;
     return {reinterpret_cast<const void*>(&k_fft_rows_half<LOGL, RQ, NT, MODE, MLR>), NT,
             kLdsBytes<1 << (LOGL - 1), RH, RQ, 2 * RQ>, RQ};
+  } else {
+    return {reinterpret_cast<const void*>(&k_fft_rows<LOGL, RQ, NT, MODE, MLR>), NT, lds, RQ};
   }
-  return {reinterpret_cast<const void*>(&k_fft_rows<LOGL, RQ, NT, MODE, MLR>), NT, lds, RQ};
 }
 // At the full row count lines of up to 2^11 points hold one array at a time in
 // LDS (k_fft_rows_split), so two 512-thread workgroups share a compute unit.
@@ -876,6 +890,8 @@ fstat_status search_launch(fstat_search* sr, const fstat_inputs* in, const doubl
   P.slot_stride = int64_t(slot_bytes(p->desc.n_fft));
   P.knot_offset = 0;
   P.params = static_cast<char*>(ws) + search_params_offset(sr);
+  P.col_block = blocked_inter(p) ? kColBlock : 0;
+  P.row_split = P.col_block != 0 && p->log_rr >= kSplitMinLogRr;
   fstat_status s0 = tm.open(0);
   if (s0 != FSTAT_OK) return s0;
   const int64_t nt = std::max<int64_t>(sr->ntmpl, sr->slots);

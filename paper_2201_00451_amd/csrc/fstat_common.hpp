@@ -134,6 +134,7 @@ struct DetConst {
 struct PlanConst {
   int32_t ndet, D;
   int32_t tmpl_stride;  // doubles per template row (8, or 10 for Keplerian orbits)
+  int32_t col_block;    // FFT intermediate: log2 of a block's columns, 0: row-major
   double dt, inv_dt, f_het, t_ref, tau0, max_delay;
   double sid_rate_cyc;  // sidereal rate / 2 pi (cycles per s)
   int64_t n_fft, bin_lo, n_bins;
@@ -144,6 +145,7 @@ struct PlanConst {
   int64_t knot_gcap;    // grid intervals of a detector's area
   int64_t knot_ioff, knot_soff, knot_toff;  // units to the integers, sample intervals, tiles
   int32_t res_taylor;   // the tiles take the antenna patterns' Taylor form
+  int32_t row_split;    // blocked, and a block's even rows come before its odd ones
   int64_t knot_bytes;   // bytes of a knot area (each group buffer holds one)
   int64_t knot_offset;  // plain path: bytes from a slot's start to its knot area;
                         // 0: the slots have none (the tiles solve their knots)

@@ -244,6 +244,11 @@ constexpr int kPer0 = (NL * ((1 << LOGL) / kR0<LOGL, MLR>) + NT - 1) / NT;
 // RQ floats per row group; neighbouring groups complete each other's cache
 // lines in that XCD's L2 before write-back).
 
+// log2 of the columns of a block of the blocked intermediate, and of the
+// shortest rows that have it (their first-stage butterflies are a multiple of
+// a block).
+constexpr int kColBlock = 3, kBlockMinLogC = 11;
+
 struct ColItem {
   int live, g, arr;
   int64_t cg;  // column group: columns cg * NL .. cg * NL + NL - 1
@@ -347,7 +352,8 @@ __device__ __forceinline__ void cols_stage0(const ColItem& it, int64_t C, int64_
 
 // Middle stages in LDS, then the last stage: LDS -> DFT -> x W_N^{q c} -> HBM.
 // The line's outputs k go to rows q = QS k + h (QS = 2: one half of a column
-// split in two, see k_fft_cols_half).
+// split in two, see k_fft_cols_half), in the row-major or the blocked
+// intermediate (inter_at).
 template <int LOGL, int NL, int NT, int MLR, int QS = 1>
 __device__ __forceinline__ void cols_finish(const PlanConst& P, void* ws, int arr_base,
                                             int64_t C, const ColItem& it, float2* lds,
@@ -362,6 +368,14 @@ __device__ __forceinline__ void cols_finish(const PlanConst& P, void* ws, int ar
   const int64_t c0 = it.cg * NL;
   const auto wr = buf_rsrc(slot_buf(ws, P, it.g, arr_base + it.arr),
                            uint32_t(P.n_fft * int64_t(sizeof(float2))));
+  // bytes from k to k + 1 of a line and to the first line's k = 0 (uniform)
+  constexpr bool kMayBlock = NL == 1 << kColBlock && QS * L >= 1024;
+  uint32_t rstep = uint32_t(QS * C * int64_t(sizeof(float2)));
+  uint32_t base = uint32_t((h * C + c0) * int64_t(sizeof(float2)));
+  if (kMayBlock && P.col_block != 0) {
+    rstep = uint32_t(NL * sizeof(float2));
+    base = uint32_t((it.cg * (QS * L) + h * L) * NL * int64_t(sizeof(float2)));
+  }
   constexpr int PER = (NBL + NT - 1) / NT;
 #pragma unroll
   for (int s = 0; s < PER; ++s) {
@@ -377,11 +391,13 @@ __device__ __forceinline__ void cols_finish(const PlanConst& P, void* ws, int ar
       const int64_t q0 = int64_t(QS) * i + h;
       float2 w = tw_n((q0 * c) & nmask, P.n_fft);
       const float2 step = tw_n((int64_t(QS) * PL * c) & nmask, P.n_fft);
-      const uint32_t voff = uint32_t((q0 * C + c) * int64_t(sizeof(float2)));
+      const uint32_t voff = kMayBlock
+                                ? uint32_t(i) * rstep + uint32_t(line * int(sizeof(float2)))
+                                : uint32_t((q0 * C + c) * int64_t(sizeof(float2)));
 #pragma unroll
       for (int m = 0; m < RL; ++m) {
         buf_store2(cmul(u[m], w), wr, voff,
-                   uint32_t(int64_t(m) * QS * PL * C * int64_t(sizeof(float2))));
+                   (kMayBlock ? base : 0u) + uint32_t(m) * PL * rstep);
         w = cmul(w, step);
       }
     }
@@ -529,11 +545,64 @@ __device__ __forceinline__ float two_f(float2 fa, float2 fb) {
   return 2.0f * (fmaf(fa.x, fa.x, fa.y * fa.y) + fmaf(fb.x, fb.x, fb.y * fb.y));
 }
 
+// The item's RQ rows are q0 + qs l, l < RQ, at positions pos0 + l of the
+// intermediate's row order.
 struct RowItem {
   int live, flagged, g;
   int64_t q0, tmpl;
+  int64_t pos0, qs;
   float l11, l21, l22;
 };
+
+template <int LOGL>
+constexpr bool kRowIlv = LOGL >= kBlockMinLogC;
+
+// Where a row's first-stage inputs lie: element c of the row at position pos
+// is element inter_at(...) of its array, and elements c + S for S a multiple
+// of a block's columns are S inter_step(...) further on.
+//
+// Row-major (col_block = 0): pos C + c with pos the row.  Blocked: a column
+// item's 2^col_block columns are one contiguous block of all Rr rows,
+// ((c >> col_block) Rr + pos) 2^col_block + (c mod 2^col_block).  An item of
+// eight columns writes 64-byte runs row-major, half a cache line, C elements
+// apart; blocked it writes whole lines one after the other, and the row pass
+// reads its RQ rows as runs of RQ 64 bytes.  With columns split in two
+// (row_split) a block holds the even rows, then the odd ones, so that each half
+// writes whole lines too.
+template <int LOGL>
+__device__ __forceinline__ int64_t inter_at(const PlanConst& P, int64_t Rr, int64_t pos, int64_t c) {
+  const int lb = kRowIlv<LOGL> ? P.col_block : 0;
+  if (lb == 0) return (pos << LOGL) + c;
+  return (((c >> lb) * Rr + pos) << lb) + (c & ((1 << lb) - 1));
+}
+template <int LOGL>
+__device__ __forceinline__ uint32_t inter_step(const PlanConst& P, int64_t Rr) {
+  return kRowIlv<LOGL> && P.col_block != 0 ? uint32_t(Rr) : 1u;
+}
+// Row ql of the item.
+template <int LOGL>
+__device__ __forceinline__ int64_t row_q(const RowItem& it, int ql) {
+  return it.q0 + (kRowIlv<LOGL> ? it.qs * ql : ql);
+}
+
+// First-stage butterfly bb of NLN lines of NBL butterflies -> (line, i).  Rows
+// of at least 2^11 points: eight consecutive butterflies of each of the RQ
+// rows of an array in turn (rows l and l + RQ/2 side by side: their LDS lines
+// start eight bank pairs apart), so that a wavefront's load of a blocked
+// intermediate covers whole cache lines.  Shorter rows, which have no blocked
+// form: one row's butterflies in order.
+template <int RQ, int NBL, bool ILV>
+__device__ __forceinline__ void row_butterfly(int bb, int& line, int& i) {
+  if constexpr (ILV && RQ > 1) {
+    static_assert(NBL % 8 == 0, "eight butterflies of a row together");
+    const int x = (bb >> 3) % RQ, y = bb / (8 * RQ);
+    i = ((y % (NBL / 8)) << 3) | (bb & 7);
+    line = (y / (NBL / 8)) * RQ + (x & 1) * (RQ / 2) + (x >> 1);
+  } else {
+    i = bb % NBL;
+    line = bb / NBL;
+  }
+}
 
 // A bin above the threshold joins the candidate list (slots past the
 // capacity are counted, not stored).
@@ -569,13 +638,22 @@ __device__ __forceinline__ void best_to_global(const RowOutput& out, int64_t tmp
   }
 }
 
-template <int MODE>
+template <int LOGL>
 __device__ __forceinline__ RowItem rows_item(const PlanConst& P, void* ws, const ChunkMap& map,
                                              int item, int n_gx, int RQ) {
   RowItem it;
   it.live = it.flagged = 0;
-  it.q0 = int64_t(item % n_gx) * RQ;
+  const int t = item % n_gx;
   it.g = item / n_gx;
+  it.qs = 1;
+  it.q0 = it.pos0 = int64_t(t) * RQ;
+  if (kRowIlv<LOGL> && P.row_split) {
+    // the even rows come first: neighbouring items take the even and the odd
+    // rows of one run of 2 RQ, so that together they fill its part of the output
+    it.qs = 2;
+    it.pos0 = int64_t(t >> 1) * RQ + (t & 1) * (int64_t(n_gx) * RQ / 2);
+    it.q0 = int64_t(t >> 1) * (2 * RQ) + (t & 1);
+  }
   it.tmpl = map.tmpl[it.g];
   const TmplParams& tp = *tmpl_params(ws, P, map, it.g);
   if (tp.status != 0) {
@@ -590,9 +668,10 @@ __device__ __forceinline__ RowItem rows_item(const PlanConst& P, void* ws, const
 }
 
 // First-stage inputs of butterflies s = S0 .. S0 + NSB - 1 (b = tid + s NT;
-// line b / (L / R0): lines 0..RQ-1 are the a rows, RQ..2RQ-1 the b rows).
+// lines 0..RQ-1 are the a rows, RQ..2RQ-1 the b rows).
 template <int LOGL, int RQ, int NT, int MODE, int MLR, int S0, int NSB>
 __device__ __forceinline__ void rows_load(const PlanConst& P, void* ws, const RowItem& it,
+                                          int64_t Rr,
                                           float2 (&v)[NSB][kR0<LOGL, MLR>]) {
   constexpr int L = 1 << LOGL;
   constexpr int NL = 2 * RQ;
@@ -601,18 +680,21 @@ __device__ __forceinline__ void rows_load(const PlanConst& P, void* ws, const Ro
   const auto rs = buf_rsrc(slot_buf(ws, P, it.g, MODE == kRowConj ? 2 : 0),
                            uint32_t(2 * P.n_fft * int64_t(sizeof(float2))));
   const int tid = threadIdx.x;
+  const uint32_t step = inter_step<LOGL>(P, Rr);
 #pragma unroll
   for (int s = 0; s < NSB; ++s) {
     const int b = tid + (S0 + s) * NT;
     if (NB0 % NT == 0 || b < NB0) {
-      const int i = b % NBL0, line = b / NBL0;
-      const int64_t e0 = (line < RQ ? 0 : P.n_fft) + (it.q0 + line % RQ) * L + i;
+      int line, i;
+      row_butterfly<RQ, NBL0, kRowIlv<LOGL>>(b, line, i);
+      const int64_t e0 =
+          (line < RQ ? 0 : P.n_fft) + inter_at<LOGL>(P, Rr, it.pos0 + line % RQ, i);
       const uint32_t voff = uint32_t(e0 * int64_t(sizeof(float2)));
       // streaming reads pay off with the plain 2F epilogue (its partial 2F
       // lines stay in L2); with the extended epilogue they cost 2 % (measured)
 #pragma unroll
       for (int j = 0; j < R0; ++j) {
-        const uint32_t soff = uint32_t(j * NBL0 * int(sizeof(float2)));
+        const uint32_t soff = uint32_t(j * NBL0 * int(sizeof(float2))) * step;
         v[s][j] = MODE == kRow2F ? buf_load2_stream(rs, voff, soff) : buf_load2(rs, voff, soff);
       }
     }
@@ -670,7 +752,7 @@ __device__ __forceinline__ void rows_flagged(const PlanConst& P, void* ws, const
   if (out.best && threadIdx.x == 0) atomicMax(out.best + it.tmpl, ~0ull);
   for (int e = threadIdx.x; e < L * RQ; e += NT) {
     const int ql = e % RQ, p = e / RQ;
-    const int64_t i = (it.q0 + ql + Rr * p + N / 2) & (N - 1);
+    const int64_t i = (row_q<LOGL>(it, ql) + Rr * p + N / 2) & (N - 1);
     if (i < P.bin_lo || i >= P.bin_lo + P.n_bins) continue;
     const int64_t o = i - P.bin_lo;
     if (out.twoF) out.twoF[it.tmpl * P.n_bins + o] = qnan;
@@ -694,7 +776,8 @@ __device__ __forceinline__ void rows_stage0(float2* lds, int tid,
   for (int s = 0; s < PER0; ++s) {
     const int b = tid + s * NT;
     if ((NL * NBL0) % NT == 0 || b < NL * NBL0) {
-      const int i = b % NBL0, line = b / NBL0;
+      int line, i;
+      row_butterfly<RQ, NBL0, kRowIlv<LOGL>>(b, line, i);
       dft<R0>(v[s]);
 #pragma unroll
       for (int m = 0; m < R0; ++m) lds[Lay::at_block(i, m, line)] = v[s][m];
@@ -740,7 +823,7 @@ __device__ __forceinline__ void rows_finish(const PlanConst& P, void* ws, const 
       twiddle_dft<RL, PL, L>(va, i, twl);
       twiddle_dft<RL, PL, L>(vb, i, twl);
       if (MODE == kRow2F) {
-        const uint32_t o0 = uint32_t(it.q0 + ql + Rr * (QS * i + h)) + uint32_t(P.n_fft / 2);
+        const uint32_t o0 = uint32_t(row_q<LOGL>(it, ql) + Rr * (QS * i + h)) + uint32_t(P.n_fft / 2);
 #pragma unroll
         for (int m = 0; m < RL; ++m) {
           const uint32_t o = ((o0 + uint32_t(m) * ostep) & nmask) - lo;
@@ -756,7 +839,7 @@ __device__ __forceinline__ void rows_finish(const PlanConst& P, void* ws, const 
       }
 #pragma unroll
       for (int m = 0; m < RL; ++m) {
-        const int64_t nat = it.q0 + ql + Rr * (int64_t(QS) * (i + m * PL) + h);
+        const int64_t nat = row_q<LOGL>(it, ql) + Rr * (int64_t(QS) * (i + m * PL) + h);
         const float v2 = rows_out<MODE>(P, ws, it, nat, va[m], vb[m], out);
         if (v2 >= 0.0f) {
           const unsigned long long key =
@@ -772,7 +855,7 @@ __device__ __forceinline__ void rows_finish(const PlanConst& P, void* ws, const 
       const int b = tid + s * NT;
       if (NBL % NT == 0 || b < NBL) {
         const int ql = b % RQ, i = b / RQ;
-        const uint32_t o0 = uint32_t(it.q0 + ql + Rr * (QS * i + h)) + uint32_t(P.n_fft / 2);
+        const uint32_t o0 = uint32_t(row_q<LOGL>(it, ql) + Rr * (QS * i + h)) + uint32_t(P.n_fft / 2);
 #pragma unroll
         for (int m = 0; m < RL; ++m) {
           const uint32_t o = ((o0 + uint32_t(m) * ostep) & nmask) - lo;
@@ -808,11 +891,11 @@ __global__ __launch_bounds__(NT) void k_fft_rows(PlanConst P, void* ws, ChunkMap
     for (int e = tid; e < L / 2; e += NT) twl[e] = tws[e * (kTwLen / L)];
   }
   const RowItem it =
-      rows_item<MODE>(P, ws, map, int(xcd_remap(blockIdx.x, gridDim.x)), int(Rr / RQ), RQ);
+      rows_item<LOGL>(P, ws, map, int(xcd_remap(blockIdx.x, gridDim.x)), int(Rr / RQ), RQ);
   if (it.flagged && MODE != kRowConj) rows_flagged<LOGL, RQ, NT>(P, ws, it, Rr, out);
   if (!it.live) return;
   float2 v[PER0][R0];
-  rows_load<LOGL, RQ, NT, MODE, MLR, 0, PER0>(P, ws, it, v);
+  rows_load<LOGL, RQ, NT, MODE, MLR, 0, PER0>(P, ws, it, Rr, v);
   rows_stage0<LOGL, RQ, NT, MLR, NL>(lds, tid, v);
   __syncthreads();
   rows_finish<LOGL, RQ, NT, MODE, MLR>(P, ws, it, out, Rr, lds, twl, tid);
@@ -843,24 +926,27 @@ k_fft_rows_half(
   const float2* __restrict__ tws = tw_stage();
   for (int e = tid; e < H / 2; e += NT) twl[e] = tws[e * (kTwLen / H)];
   const RowItem it =
-      rows_item<MODE>(P, ws, map, int(xcd_remap(blockIdx.x, gridDim.x)), int(Rr / RQ), RQ);
+      rows_item<LOGL>(P, ws, map, int(xcd_remap(blockIdx.x, gridDim.x)), int(Rr / RQ), RQ);
   if (it.flagged && MODE != kRowConj) rows_flagged<LOGL, RQ, NT>(P, ws, it, Rr, out);
   if (!it.live) return;
   float2 a[PER0][R0], b[PER0][R0];
   {
     const auto rs = buf_rsrc(slot_buf(ws, P, it.g, MODE == kRowConj ? 2 : 0),
                              uint32_t(2 * P.n_fft * int64_t(sizeof(float2))));
+    const uint32_t step = inter_step<LOGL>(P, Rr);
 #pragma unroll
     for (int s = 0; s < PER0; ++s) {
       const int bb = tid + s * NT;
       if (NB0 % NT == 0 || bb < NB0) {
-        const int i = bb % S0, line = bb / S0;
-        const int64_t e0 = (line < RQ ? 0 : P.n_fft) + (it.q0 + line % RQ) * L + i;
+        int line, i;
+        row_butterfly<RQ, S0, kRowIlv<LOGL>>(bb, line, i);
+        const int64_t e0 =
+            (line < RQ ? 0 : P.n_fft) + inter_at<LOGL>(P, Rr, it.pos0 + line % RQ, i);
         const uint32_t voff = uint32_t(e0 * int64_t(sizeof(float2)));
 #pragma unroll
         for (int j = 0; j < R0; ++j) {
-          const uint32_t soff = uint32_t(j * S0 * int(sizeof(float2)));
-          const uint32_t soff2 = uint32_t((j * S0 + H) * int(sizeof(float2)));
+          const uint32_t soff = uint32_t(j * S0 * int(sizeof(float2))) * step;
+          const uint32_t soff2 = uint32_t((j * S0 + H) * int(sizeof(float2))) * step;
           a[s][j] = MODE == kRow2F ? buf_load2_stream(rs, voff, soff) : buf_load2(rs, voff, soff);
           b[s][j] = MODE == kRow2F ? buf_load2_stream(rs, voff, soff2)
                                    : buf_load2(rs, voff, soff2);
@@ -872,7 +958,8 @@ k_fft_rows_half(
   for (int s = 0; s < PER0; ++s) {
     const int bb = tid + s * NT;
     if (NB0 % NT == 0 || bb < NB0) {
-      const int i = bb % S0;
+      int line, i;
+      row_butterfly<RQ, S0, kRowIlv<LOGL>>(bb, line, i);
 #pragma unroll
       for (int j = 0; j < R0; ++j) {
         const int c = i + j * S0;
@@ -888,7 +975,8 @@ k_fft_rows_half(
     for (int s = 0; s < PER0; ++s) {
       const int bb = tid + s * NT;
       if (NB0 % NT == 0 || bb < NB0) {
-        const int i = bb % S0, line = bb / S0;
+        int line, i;
+        row_butterfly<RQ, S0, kRowIlv<LOGL>>(bb, line, i);
         float2(&v)[R0] = h ? b[s] : a[s];
         dft<R0>(v);
 #pragma unroll
@@ -936,7 +1024,7 @@ __global__ __launch_bounds__(NT, NT / 128) void k_fft_rows_split(PlanConst P, vo
     for (int e = tid; e < L / 2; e += NT) twl[e] = tws[e * (kTwLen / L)];
   }
   const RowItem it =
-      rows_item<MODE>(P, ws, map, int(xcd_remap(blockIdx.x, gridDim.x)), int(Rr / RQ), RQ);
+      rows_item<LOGL>(P, ws, map, int(xcd_remap(blockIdx.x, gridDim.x)), int(Rr / RQ), RQ);
   if (it.flagged && MODE != kRowConj) rows_flagged<LOGL, RQ, NT>(P, ws, it, Rr, out);
   if (!it.live) return;
   // band offsets o = ((nat + N/2) mod N) - bin_lo in 32 bits; the descriptors
@@ -949,6 +1037,7 @@ __global__ __launch_bounds__(NT, NT / 128) void k_fft_rows_split(PlanConst P, vo
                            kHas2F && out.twoF ? band : 0u);
   const uint32_t nmask = uint32_t(P.n_fft - 1), lo = uint32_t(P.bin_lo);
   const uint32_t ostep = uint32_t(Rr * PL);
+  const uint32_t step = inter_step<LOGL>(P, Rr);
   constexpr bool kKeepF = MODE == kRow2FExt;
   float pa[kKeepF ? 1 : PER][kKeepF ? 1 : RL];
   float2 fa[kKeepF ? PER : 1][kKeepF ? RL : 1];
@@ -963,18 +1052,21 @@ __global__ __launch_bounds__(NT, NT / 128) void k_fft_rows_split(PlanConst P, vo
     for (int s = 0; s < PER0; ++s) {
       const int b = tid + s * NT;
       if (NB0 % NT == 0 || b < NB0) {
-        const int i = b % NBL0, line = b / NBL0;
-        const uint32_t voff = uint32_t(((it.q0 + line) * L + i) * int64_t(sizeof(float2)));
+        int line, i;
+        row_butterfly<RQ, NBL0, kRowIlv<LOGL>>(b, line, i);
+        const uint32_t voff =
+            uint32_t(inter_at<LOGL>(P, Rr, it.pos0 + line, i) * int64_t(sizeof(float2)));
 #pragma unroll
         for (int j = 0; j < R0; ++j)
-          v[s][j] = buf_load2_stream(rs, voff, uint32_t(j * NBL0 * int(sizeof(float2))));
+          v[s][j] = buf_load2_stream(rs, voff, uint32_t(j * NBL0 * int(sizeof(float2))) * step);
       }
     }
 #pragma unroll
     for (int s = 0; s < PER0; ++s) {
       const int b = tid + s * NT;
       if (NB0 % NT == 0 || b < NB0) {
-        const int i = b % NBL0, line = b / NBL0;
+        int line, i;
+        row_butterfly<RQ, NBL0, kRowIlv<LOGL>>(b, line, i);
         dft<R0>(v[s]);
 #pragma unroll
         for (int m = 0; m < R0; ++m) lds[Lay::at_block(i, m, line)] = v[s][m];
@@ -991,7 +1083,7 @@ __global__ __launch_bounds__(NT, NT / 128) void k_fft_rows_split(PlanConst P, vo
 #pragma unroll
         for (int j = 0; j < RL; ++j) u[j] = lds[Lay::template at_step<PL>(i, j, ql)];
         twiddle_dft<RL, PL, L>(u, i, twl);
-        const uint32_t n0 = uint32_t(it.q0 + ql + Rr * i);
+        const uint32_t n0 = uint32_t(row_q<LOGL>(it, ql) + Rr * i);
         const uint32_t o0 = n0 + uint32_t(P.n_fft / 2);
         if constexpr (MODE == kRowConj) {
           // the transform itself, conjugated, at the natural index below k_pad
@@ -1077,7 +1169,7 @@ __global__ __launch_bounds__(NT, NT / 128) void k_fft_rows_split(PlanConst P, vo
       const int b = tid + s * NT;
       if (NBL % NT == 0 || b < NBL) {
         const int ql = b % RQ, i = b / RQ;
-        const uint32_t o0 = uint32_t(it.q0 + ql + Rr * i) + uint32_t(P.n_fft / 2);
+        const uint32_t o0 = uint32_t(row_q<LOGL>(it, ql) + Rr * i) + uint32_t(P.n_fft / 2);
 #pragma unroll
         for (int m = 0; m < RL; ++m) {
           const uint32_t o = ((o0 + uint32_t(m) * ostep) & nmask) - lo;

@@ -174,3 +174,33 @@ def test_fft_items_of_small_and_large_launches(torch_dev, log_n):
                  (one + 3.0, total), (one[:3], tf1), (one[:3], tf3), (g1, g3)):
         assert torch_dev.equal(a, b)
     check_2f(one[5:6], O.oracle_twoF(ds, ds.templates[5:6]))
+
+
+@pytest.mark.parametrize("log_n,col,row_lines", [(20, 10, 0), (21, 10, 0), (21, 10, 2),
+                                                 (22, 11, 0), (22, 11, 2), (23, 11, 0),
+                                                 (23, 11, 1)])
+def test_fft_intermediate_in_column_blocks(torch_dev, log_n, col, row_lines):
+    """Searches whose column pass writes blocks of eight columns (and, at 2^20,
+    the shortest plan that does not) give the bits of the in-place transforms
+    with a row-major intermediate: plain, summed, and candidates with the
+    loudest bin, on a ragged band, every row kernel that reads blocks; one
+    template against the oracle."""
+    from paper_2201_00451_amd import binding
+    n_fft = 1 << log_n
+    lo, nb = n_fft // 5 + 1, n_fft // 2 + 3
+    ds = synth.small_case(seed=97, n=2500, n_fft=n_fft, ndet=2, gaps=True, ntmpl=5, rho=20,
+                          bin_lo=lo, n_bins=nb)
+    dd = binding.DeviceData(ds, batch=5, tune=dict(tune_col_log_len=col, tune_col_lines=8,
+                                                   tune_row_lines=row_lines))
+    want = binding.compute_2f_batched(dd, ds.templates)
+    got = torch_dev.empty_like(want)
+    binding.Search(dd, ds.templates, slots=5).run(out=got)
+    total = torch_dev.full_like(want, 3.0)
+    binding.Search(dd, ds.templates, slots=5, accumulate=True).run(out=total)
+    level = float(want.max()) * 0.9
+    rep = binding.Search(dd, ds.templates, slots=5).run_candidates(level)
+    binding.sync_check()
+    assert torch_dev.equal(got, want) and torch_dev.equal(total, want + 3.0)
+    assert rep["count"] == int((want > level).sum()) > 0
+    assert torch_dev.equal(rep["best_twoF"], want.max(dim=1).values)
+    check_2f(want[1:2], O.oracle_twoF(ds, ds.templates[1:2]))
