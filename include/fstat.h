@@ -94,7 +94,7 @@ typedef struct {
    *   tune_row_lines: rows per workgroup of the row pass (the a and b rows
    *     together): the largest count (512 threads: the automatic choice) or
    *     half of it (256 threads);
-   *   tune_fft_radix: largest radix of a Stockham stage, 16 or 32 (automatic:
+   *   tune_fft_radix: largest radix of a column-pass stage, 16 or 32 (automatic:
    *     32, so lines of 2^9 and 2^10 points take two stages). */
   int32_t tune_col_log_len;
   int32_t tune_col_lines;
@@ -344,7 +344,7 @@ FSTAT_API fstat_status fstat_sinc_halfwidth_for(double band_fraction, double tol
 /* Launch-shape autotuner: for the set-up *desc (its tune fields ignored),
  * times every FFT launch shape the plan accepts (both column/row splits of
  * n_fft around its square root, full or half line counts for each pass,
- * radix-16 or radix-32 stage plans) by running the batched path
+ * radix-16 or radix-32 stage plans of the column pass) by running the batched path
  * on the given sample of templates (device [ntmpl][8], ntmpl >= 1; twoF a
  * device [ntmpl][n_bins] scratch output) with the given workspace, once
  * untimed and once timed with HIP events, and returns the fastest
