@@ -34,24 +34,20 @@
 
 namespace fstat {
 
-// Tap constants of half-width D, built at compile time into constant memory
-// (read with uniform indices, whether or not the tap loop is unrolled):
-//   A_t, B_t, C_t as above; Ct_t = cos(pi c_t / D), St_t = sin(pi c_t / D).
+// Window constants of half-width D for the point-by-point gradient tiles,
+// built at compile time into constant memory (read with uniform indices,
+// whether or not the tap loop is unrolled): with c_t = D - 1 - t,
+// Ct_t = cos(pi c_t / D), St_t = sin(pi c_t / D).
 struct TapConst {
-  float A[64], B[64], C[64], Ct[64], St[64];
+  float Ct[32], St[32];
 };
 template <int D>
 __host__ __device__ constexpr TapConst make_taps() {
   TapConst k{};
   for (int t = 0; t < 2 * D; ++t) {
     const int c = D - 1 - t;
-    const double sgn = (c & 1) ? -1.0 : 1.0;
-    const double cc = ct_cospi(c, D), ss = ct_sinpi(c, D);
-    k.A[t] = float(sgn * cc / (2.0 * kPi));
-    k.B[t] = float(-sgn * ss / (2.0 * kPi));
-    k.C[t] = float(sgn / (2.0 * kPi));
-    k.Ct[t] = float(cc);
-    k.St[t] = float(ss);
+    k.Ct[t] = float(ct_cospi(c, D));
+    k.St[t] = float(ct_sinpi(c, D));
   }
   return k;
 }
