@@ -329,7 +329,7 @@ template <int D, bool ONEHOT, bool KEP>
 __global__ __launch_bounds__(kResThreads, 2) void k_grad(PlanConst P, void* ws) {
   const int slot = blockIdx.y;
   const TmplParams& tp = *slot_params(ws, P, slot);
-  if (tp.status != 0 || span_timed(P, tp)) return;
+  if (tp.status != 0 || tp.tile_form != kTilePoints) return;
   const int64_t tiles = P.k_pad / kResTile;
   for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
     grad_tile<D, ONEHOT, KEP>(P, ws, slot, t);

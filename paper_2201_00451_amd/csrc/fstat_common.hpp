@@ -165,6 +165,7 @@ struct TmplParams {
   // Keplerian orbit (kepler != 0): eccentricity, sin and cos of the argument
   // of periapsis, sqrt(1 - ecc^2)
   int32_t kepler;
+  int32_t tile_form;  // gradients and single-bin transforms: kTilePoints and on
   double ecc, sin_w, cos_w, sq_e;
   // spin-down and sub-bin phase in quarter turns (4 x cycles) as a cubic in
   // the grid index k: 4 Phi(k) = sd[0] + k (sd[1] + k (sd[2] + k sd[3]))
@@ -196,6 +197,14 @@ struct TmplParams {
   int64_t bin_nat;
   double hbin[4];
 };
+
+// How the gradient and single-bin kernels take a template's timing: solved at
+// every point (k_grad, k_resample_bin), or from quantities smooth over a tile
+// (k_grad_span, k_bin_span), with the curvature of the delay derivatives over
+// the taps or without it.
+constexpr int32_t kTilePoints = 0;
+constexpr int32_t kTileSmooth = 1;
+constexpr int32_t kTileCurved = 2;
 
 // Status bits of a template (any bit: NaN in every output bin).
 constexpr int32_t kStatusTiming = 1;    // non-finite or invalid sky / orbit parameters

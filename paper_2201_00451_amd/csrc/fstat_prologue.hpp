@@ -122,6 +122,35 @@ __host__ __device__ inline Jks jks_coeffs(const DetConst& d, double sd, double c
   return k;
 }
 
+constexpr double kSpanOrbit = 0.3;    // orbital phase of half a tile, radians
+constexpr double kSpanAngle = 0.05;   // sidereal angle of half a tile, radians
+constexpr double kSpanCurve = 1.5e-3;  // phase over the taps of one side, radians
+
+// The form in which the gradient and single-bin kernels take a template: spans
+// of tiles where knots lie at least 16 points apart and half a tile covers at
+// most 0.05 rad of the Earth's rotation and 0.3 rad of the orbit (its angular
+// rate at periapsis, om / (1 - ecc)^2), so that quintics per tile carry the
+// timing's derivatives; else point by point.
+//
+// Within a span the sum over taps with the samples' delay derivatives d,
+// sum_j h(u - j) d(j) z_j, is expanded about the point u.  The term of second
+// order is (w dt)^2 / 2 of d times sum_j h (j - u)^2 z_j, and that sum is at most
+// about D^2 / 20 of |z|: it is the curvature of the interpolation's response
+// over frequency, so it vanishes well inside the band and is largest near the
+// band's edge, where the response falls off within 1 / (2 D) cycles per
+// sample.  Below w dt D = 1.5e-3 the term is under 6e-8, the rounding of the
+// FP32 sums; above, it is carried (kTileCurved), and the one of third order is
+// under 2e-8 up to the 0.3 rad and D = 16.
+__host__ __device__ inline int32_t tile_form(const PlanConst& P, double om_b, double ecc,
+                                             int32_t knot_log2) {
+  const double half = 0.5 * kResTile * P.dt;
+  const double sid = 2.0 * kPi * P.sid_rate_cyc;
+  const double w = om_b / ((1.0 - ecc) * (1.0 - ecc));
+  if (knot_log2 < kKnotLogGlobal || !(sid * half <= kSpanAngle) || !(w * half <= kSpanOrbit))
+    return kTilePoints;
+  return fmax(w, sid) * P.dt * double(P.D) <= kSpanCurve ? kTileSmooth : kTileCurved;
+}
+
 // A template's row: orbit, knot spacing, spin-down phase, sky vector and its
 // derivatives, and the status bits these give.
 __host__ __device__ inline void row_params(const PlanConst& P, const double* row, TmplParams& tp) {
@@ -181,6 +210,7 @@ __host__ __device__ inline void row_params(const PlanConst& P, const double* row
       }
     }
   }
+  tp.tile_form = tile_form(P, tp.om_b, tp.ecc, tp.knot_log2);
   spindown_coefficients(P, tp.f1dot, tp.f2dot, tp.df, tp.sd);
   double sa, ca_, sd, cdl;
   sincos(alpha, &sa, &ca_);

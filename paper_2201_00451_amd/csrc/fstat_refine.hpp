@@ -1,5 +1,5 @@
 // The single-bin transform and the gradient sums of templates whose timing is
-// smooth over a tile (span_timed): the same quantities as k_resample_bin and
+// smooth over a tile (tile_form): the same quantities as k_resample_bin and
 // k_grad, which solve the timing of every point and sample, from timing solved
 // at knots inside the block.  No knot area exists on these paths (their
 // workspace is a parameter block and 64 bytes per tile), so each block of
@@ -19,11 +19,12 @@
 // forward path, here up to 0.05 rad.
 //
 // The sum over taps with the samples' own delay derivatives,
-// S_q = sum_t h_t d_q(j_t) z_j, follows from two sums: d_q is linear over the 2D
-// taps to (2 pi 2D dt / P)^2 / 2 of its range times the second moment of the
-// interpolation kernel (zero but for its pass-band ripple), so
-//   S_q = d_q(u) sum h z + d_q'(u) sum h (j - u) z.
-// A tap then costs three accumulations instead of seven.
+// S_q = sum_t h_t d_q(j_t) z_j, follows from the expansion of d_q about the point,
+//   S_q = d_q(u) sum h z + d_q'(u) sum h (j - u) z + d_q''(u) / 2 sum h (j - u)^2 z,
+// the last term only for templates that need it (tile_form says which).  A tap
+// then costs three or four accumulations instead of seven.  Without the last
+// term the gradients of the fastest orbits were off by up to 3e-4 (D = 16, a
+// bin at 0.49 of the sampling rate; 3e-6 with every sample's own derivative).
 //
 // Bound by VALU issue and, in the solves, by their latency.  Measured on 32
 // templates of 2.6 M points and two detectors: the single-bin transform 2360 to
@@ -36,21 +37,8 @@
 
 namespace fstat {
 
-constexpr double kSpanOrbit = 0.3;   // orbital phase of half a tile, radians
-constexpr double kSpanAngle = 0.05;  // sidereal angle of half a tile, radians
 constexpr int kNodes = 6;            // Chebyshev nodes per tile
 constexpr int kNodeFns = 6;          // five delay derivatives and dt/dt_src
-
-// Whether a template takes the kernels of this file (else k_resample_bin and
-// k_grad): knots at least 16 points apart and a tile smooth enough for the
-// quintics.  Each of the two kernels of a pair returns at once for the
-// templates of the other.
-__device__ inline bool span_timed(const PlanConst& P, const TmplParams& tp) {
-  const double half = 0.5 * kResTile * P.dt;
-  const double ecc = 1.0 - tp.ecc;
-  return tp.knot_log2 >= kKnotLogGlobal && 2.0 * kPi * P.sid_rate_cyc * half <= kSpanAngle &&
-         tp.om_b * half <= kSpanOrbit * ecc * ecc;
-}
 
 // Monomial coefficients in v in [-1, 1] of the interpolant through the values
 // at the Chebyshev nodes x_n = cos(pi (2 n + 1) / (2 kNodes)): c_j = sum_n
@@ -322,7 +310,7 @@ __device__ __forceinline__ double block_sum(const double (&s)[NQ]) {
   return v;
 }
 
-// k_resample_bin for the templates of span_timed: kSpanTiles tiles per block
+// k_resample_bin for the templates of tile_form: kSpanTiles tiles per block
 // (one tile at a time at a knot spacing of 16); the block's sums go to its
 // first tile's partials, zeros to the others'.
 template <int D, bool KEP>
@@ -333,7 +321,7 @@ __global__ __launch_bounds__(kResThreads, 4) void k_bin_span(PlanConst P, void* 
   const int slot = blockIdx.y;
   TmplParams* tpp = slot_params(ws, P, slot);
   const TmplParams& tp = *tpp;
-  if (tp.status != 0 || !span_timed(P, tp)) return;
+  if (tp.status != 0 || tp.tile_form == kTilePoints) return;
   SpanRec* recs = reinterpret_cast<SpanRec*>(zs + P.ndet * kSpanCap);
   const int tid = threadIdx.x, lane = tid & 63;
   const int kl = uniform_i32(tp.knot_log2);
@@ -403,12 +391,12 @@ __global__ __launch_bounds__(kResThreads, 4) void k_bin_span(PlanConst P, void* 
   }
 }
 
-// The sums of the gradient over one point's taps: sum h z, sum h' z and
-// sum h (j - u) z.
+// The sums of the gradient over one point's taps: sum h z, sum h' z,
+// sum h (j - u) z and (CURVED) sum h (j - u)^2 z.
 struct TapSums {
-  float2 z, dz, jz;
+  float2 z, dz, jz, jjz;
 };
-template <int D, int M>
+template <int D, int M, bool CURVED>
 __device__ __forceinline__ void grad_pair(float g, float u, const float2* zp, TapSums& s) {
   float hp, hm;
   tap_pair<D, M>(g, u, hp, hm);
@@ -432,14 +420,24 @@ __device__ __forceinline__ void grad_pair(float g, float u, const float2* zp, Ta
   // h (s - g) z, s = u - j: +(M + 1/2) on the left, -(M + 1/2) on the right
   s.jz.x = fmaf(-cm, zr.x, fmaf(cp, zl.x, s.jz.x));
   s.jz.y = fmaf(-cm, zr.y, fmaf(cp, zl.y, s.jz.y));
+  if constexpr (CURVED) {
+    const float ccp = cp * c, ccm = cm * c;
+    s.jjz.x = fmaf(ccm, zr.x, fmaf(ccp, zl.x, s.jjz.x));
+    s.jjz.y = fmaf(ccm, zr.y, fmaf(ccp, zl.y, s.jjz.y));
+  }
 }
-template <int D, int... M>
+template <int D, bool CURVED, int... M>
 __device__ __forceinline__ TapSums grad_taps(std::integer_sequence<int, M...>, float f,
                                              const float2* zp) {
   const float g = f - 0.5f, u = g * g;
   TapSums s;
-  s.z = s.dz = s.jz = make_float2(0.f, 0.f);
-  (grad_pair<D, D - 1 - M>(g, u, zp, s), ...);
+  s.z = s.dz = s.jz = s.jjz = make_float2(0.f, 0.f);
+  (grad_pair<D, D - 1 - M, CURVED>(g, u, zp, s), ...);
+  // sum h (j - u)^2 z = sum h s^2 z, s = g + (s - g)
+  if constexpr (CURVED) {
+    s.jjz.x = fmaf(g, fmaf(g, s.z.x, 2.0f * s.jz.x), s.jjz.x);
+    s.jjz.y = fmaf(g, fmaf(g, s.z.y, 2.0f * s.jz.y), s.jjz.y);
+  }
   // sum h (j - u) z = -sum h s z
   s.jz.x = -fmaf(g, s.z.x, s.jz.x);
   s.jz.y = -fmaf(g, s.z.y, s.jz.y);
@@ -466,14 +464,21 @@ __device__ __forceinline__ void taylor_slope(const float* c, float d, float& a, 
   }
 }
 
-// k_grad for the templates of span_timed (see the head of this file).
-template <int D, bool ONEHOT, bool KEP>
-__global__ __launch_bounds__(kResThreads, 3) void k_grad_span(PlanConst P, void* ws) {
-  extern __shared__ float2 zs[];
-  __shared__ SpanSolve sv;
-  __shared__ double nodes[kMaxDet][kSpanTiles * kNodes][kNodeFns];
-  __shared__ float dpoly[kMaxDet][kSpanTiles][kNodeFns][kNodes];
-  __shared__ float dant[kMaxDet][kSpanTiles][2][kTaylorCoef + 2];
+// Per-block tables of k_grad_span besides the windows and their records.
+struct GradLds {
+  SpanSolve sv;
+  double nodes[kMaxDet][kSpanTiles * kNodes][kNodeFns];
+  float dpoly[kMaxDet][kSpanTiles][kNodeFns][kNodes];
+  float dant[kMaxDet][kSpanTiles][2][kTaylorCoef + 2];
+};
+// The spans of one block (see the head of this file), with the curvature of the
+// delay derivatives over the taps or without it.
+template <int D, bool ONEHOT, bool KEP, bool CURVED>
+__device__ __forceinline__ void grad_span(const PlanConst& P, void* ws, float2* zs, GradLds& lds) {
+  SpanSolve& sv = lds.sv;
+  auto& nodes = lds.nodes;
+  auto& dpoly = lds.dpoly;
+  auto& dant = lds.dant;
   const int slot = blockIdx.y;
   TmplParams* tpp = slot_params(ws, P, slot);
   const TmplParams& tp = *tpp;
@@ -487,7 +492,7 @@ __global__ __launch_bounds__(kResThreads, 3) void k_grad_span(PlanConst P, void*
       for (int t = t_b; t < t_e; ++t) partial[(t - t_b) * 8 + tid] = 0.0;
     return;
   }
-  if (!span_timed(P, tp)) return;
+  if (tp.tile_form == kTilePoints) return;
   SpanRec* recs = reinterpret_cast<SpanRec*>(zs + P.ndet * kSpanCap);
   const int kl = uniform_i32(tp.knot_log2);
   const int step = kl > kKnotLogGlobal ? kSpanTiles : 1;
@@ -588,8 +593,8 @@ __global__ __launch_bounds__(kResThreads, 3) void k_grad_span(PlanConst P, void*
           const SpanPoint p = span_point<D>(rec, mask, kl, h * kResTile + kk,
                                             k_t + kk - jx - (D - 1));
           if (!p.live) continue;
-          const TapSums s = grad_taps<D>(std::make_integer_sequence<int, D>{}, p.f,
-                                         zs + X * kSpanCap + p.base);
+          const TapSums s = grad_taps<D, CURVED>(std::make_integer_sequence<int, D>{}, p.f,
+                                                  zs + X * kSpanCap + p.base);
           const float dx = (float(kk - kResTile / 2 + (p.im - i_r)) + (p.th - th_r)) * dstep;
           const float2 wa = Wa[i], wb = Wb[i];
           // W = X (a', b') and its derivatives in the angle, alpha and delta
@@ -624,18 +629,24 @@ __global__ __launch_bounds__(kResThreads, 3) void k_grad_span(PlanConst P, void*
           const float q0 = two_pi_fh * i0;
           // d_q' per sample: d/dv over half a tile of grid steps, dt_src/dt
           // steps per sample (1 / inv_tau, first order)
-          const float q1 = two_pi_fh * i1 * ((2.0f / float(kResTile)) * (2.0f - inv_tau));
+          const float vj = (2.0f / float(kResTile)) * (2.0f - inv_tau);
+          const float q1 = two_pi_fh * i1 * vj;
+          float q2 = 0.0f;
+          if constexpr (CURVED)  // Im(W sum h (j - u)^2 z)
+            q2 = two_pi_fh * fmaf(wr, s.jjz.y, wi * s.jjz.x) * (vj * vj);
 #pragma unroll
           for (int q = 0; q < 5; ++q) {
             const float* c = dpoly[X][h][q];
-            float dv = c[kNodes - 1], ds = 0.0f;
+            // value, slope and half the second derivative
+            float dv = c[kNodes - 1], ds = 0.0f, dc = 0.0f;
 #pragma unroll
             for (int n = kNodes - 2; n >= 0; --n) {
+              if constexpr (CURVED) dc = fmaf(dc, v, ds);
               ds = fmaf(ds, v, dv);
               dv = fmaf(dv, v, c[n]);
             }
             const float full = q == 0 ? dv + shift0 : q == 1 ? dv + shift1 : dv;
-            float m = fmaf(full, pt, fmaf(dv, q0, ds * q1));
+            float m = fmaf(full, pt, fmaf(dv, q0, CURVED ? fmaf(ds, q1, dc * q2) : ds * q1));
             if (q == 0) m += rx + ral;
             if (q == 1) m += rde;
             acc[2 + q] += double(m);
@@ -654,6 +665,21 @@ __global__ __launch_bounds__(kResThreads, 3) void k_grad_span(PlanConst P, void*
     partial[tid] = v;
     for (int t = t_b + 1; t < t_e; ++t) partial[(t - t_b) * 8 + tid] = 0.0;
   }
+}
+
+// k_grad for the templates of tile_form.  The choice between the two forms is
+// taken once per block, around the whole body: taken per tile the registers of
+// both were live at once (32 templates of 2.6 M points, smooth ones: 4380 us a
+// call with the smooth form alone, 4400 so, 4420 per span, 4495 per tile, 4610
+// with every template in the curved form).
+template <int D, bool ONEHOT, bool KEP>
+__global__ __launch_bounds__(kResThreads, 3) void k_grad_span(PlanConst P, void* ws) {
+  extern __shared__ float2 zs[];
+  __shared__ GradLds lds;
+  if (uniform_i32(slot_params(ws, P, blockIdx.y)->tile_form) == kTileCurved)
+    grad_span<D, ONEHOT, KEP, true>(P, ws, zs, lds);
+  else
+    grad_span<D, ONEHOT, KEP, false>(P, ws, zs, lds);
 }
 
 }  // namespace fstat

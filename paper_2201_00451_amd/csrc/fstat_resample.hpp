@@ -1088,7 +1088,6 @@ __host__ __device__ inline int64_t band_bin_nat(const PlanConst& P, int64_t i) {
 // partials (Fa'.re, Fa'.im, Fb'.re, Fb'.im in FP64).  The templates whose
 // timing is solved point by point (the others: k_bin_span); a block walks
 // tiles.
-__device__ bool span_timed(const PlanConst& P, const TmplParams& tp);
 template <int D, bool KEP>
 __global__ __launch_bounds__(kResThreads, 4) void k_resample_bin(PlanConst P, void* ws, ChunkMap map,
                                                              const int64_t* __restrict__ bins) {
@@ -1096,7 +1095,7 @@ __global__ __launch_bounds__(kResThreads, 4) void k_resample_bin(PlanConst P, vo
   TmplParams* tpp = slot_params(ws, P, slot);
   const TmplParams& tp = *tpp;
   const int tid = threadIdx.x;
-  if (tp.status != 0 || span_timed(P, tp)) return;
+  if (tp.status != 0 || tp.tile_form != kTilePoints) return;
   __shared__ float2 zs[kDetPass * kResWcap];
   __shared__ int32_t blk[kDetPass * kResBlk];
   __shared__ double red[kResThreads / 64][4];

@@ -204,3 +204,36 @@ def test_fft_intermediate_in_column_blocks(torch_dev, log_n, col, row_lines):
     assert rep["count"] == int((want > level).sum()) > 0
     assert torch_dev.equal(rep["best_twoF"], want.max(dim=1).values)
     check_2f(want[1:2], O.oracle_twoF(ds, ds.templates[1:2]))
+
+
+@pytest.mark.parametrize("D,share", [(8, 0.46), (16, 0.46), (16, 0.49)])
+def test_gradients_near_the_band_edge(torch_dev, D, share):
+    """The orbit's gradients of a signal at 0.46 and 0.49 of the sampling rate,
+    where the interpolation's response falls off and the sums over its taps
+    feel the curvature of the delay derivatives, for an orbit at the limit of
+    the quintics per tile (0.297 rad per half tile), against the FP64 oracle.
+    Tolerance: ten FP32 roundings (6e-8) per term, times 16 for terms that
+    cancel."""
+    from paper_2201_00451_amd import binding
+    dt, n = 2.0, 3300
+    ds = synth.small_case(seed=304, n=n, dt=dt, n_fft=1 << 13, ndet=2, D=D, binary=True, gaps=True,
+                          ntmpl=1, rho=25, f_inj=share / dt, noise_vars=[1.0, 0.7])
+    inj = ds.injections[0]
+    inj.update(asini=0.6, porb=2 * np.pi * 256 * dt / 0.297)
+    ds.x, _ = synth.make_data(ds.detectors, dt, ds.f_het, 0.0, [inj], 304, gaps=ds.valid)
+    ds.templates[:, 5], ds.templates[:, 6] = inj["asini"], inj["porb"]
+    ds = synth.finish(ds)
+    row = ds.templates[0] + np.array([0.002, -0.0015, 0.3 / (n * dt), 0.5 / (n * dt) ** 2, 0, 6e-4,
+                                      0.2, 1.0])
+    dd = binding.DeviceData(ds)
+    m = int(np.argmax(O.oracle_twoF(ds, row[None])[0]))
+    w = np.zeros(ds.n_bins)
+    w[m] = 1.0
+    _, ref = G.oracle_grad(ds, row, w)
+    g_bin, _ = binding.compute_2f_grad_bin(dd, row[None], [m])
+    g_gen = binding.compute_2f_grad(dd, row[None], w[None])
+    binding.sync_check()
+    for got in (g_bin, g_gen):
+        err = np.abs(got.cpu().numpy()[0] - ref) / np.abs(ref)
+        print("  ", dict(zip(G.PARAMS, err)), flush=True)
+        assert np.all(err[4:] <= 10 * 6e-8 * 16)
