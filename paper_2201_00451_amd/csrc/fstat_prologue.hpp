@@ -122,15 +122,19 @@ __host__ __device__ inline Jks jks_coeffs(const DetConst& d, double sd, double c
   return k;
 }
 
-constexpr double kSpanOrbit = 0.3;    // orbital phase of half a tile, radians
-constexpr double kSpanAngle = 0.05;   // sidereal angle of half a tile, radians
-constexpr double kSpanCurve = 1.5e-3;  // phase over the taps of one side, radians
+constexpr double kSpanOrbit = 0.3;         // circular orbit: phase of half a tile, radians
+constexpr double kSpanOrbitKepler = 0.18;  // eccentric: the same, at periapsis
+constexpr double kSpanAngle = 0.05;        // sidereal angle of half a tile, radians
+constexpr double kSpanCurve = 1.5e-3;      // phase over the taps of one side, radians
 
 // The form in which the gradient and single-bin kernels take a template: spans
 // of tiles where knots lie at least 16 points apart and half a tile covers at
-// most 0.05 rad of the Earth's rotation and 0.3 rad of the orbit (its angular
-// rate at periapsis, om / (1 - ecc)^2), so that quintics per tile carry the
-// timing's derivatives; else point by point.
+// most 0.05 rad of the Earth's rotation and 0.3 rad of a circular orbit, 0.18 of
+// an eccentric one (its angular rate at periapsis, om / (1 - ecc)^2), so that
+// quintics per tile carry the timing's derivatives; else point by point.  At
+// these limits the quintics of the orbit's delay and rate are within 3.3e-8 of
+// their amplitudes (0.3^6 / 23040 for a circle; eccentric orbits carry
+// harmonics: at 0.3 rad they were off by up to 5.4e-7, at ecc = 0.4).
 //
 // Within a span the sum over taps with the samples' delay derivatives d,
 // sum_j h(u - j) d(j) z_j, is expanded about the point u.  The term of second
@@ -146,7 +150,8 @@ __host__ __device__ inline int32_t tile_form(const PlanConst& P, double om_b, do
   const double half = 0.5 * kResTile * P.dt;
   const double sid = 2.0 * kPi * P.sid_rate_cyc;
   const double w = om_b / ((1.0 - ecc) * (1.0 - ecc));
-  if (knot_log2 < kKnotLogGlobal || !(sid * half <= kSpanAngle) || !(w * half <= kSpanOrbit))
+  if (knot_log2 < kKnotLogGlobal || !(sid * half <= kSpanAngle) ||
+      !(w * half <= (ecc > 0.0 ? kSpanOrbitKepler : kSpanOrbit)))
     return kTilePoints;
   return fmax(w, sid) * P.dt * double(P.D) <= kSpanCurve ? kTileSmooth : kTileCurved;
 }

@@ -13,8 +13,8 @@
 // and they vary on the scales of the Earth's rotation and of the orbit, which a
 // tile covers a fraction of.  Per tile and detector they are evaluated exactly
 // (FP64) at six Chebyshev nodes and taken as quintics in between (FP32, after
-// the constant of the block's dshift is off): with half a tile at most 0.3 rad of
-// orbital phase the truncation is below 0.3^6 / 23040 = 3e-8 of their range.  The
+// the constant of the block's dshift is off): within the limits of tile_form the
+// truncation is below 3.3e-8 of their amplitude.  The
 // antenna patterns and their sky derivatives are the quintic Taylor forms of the
 // forward path, here up to 0.05 rad.
 //
