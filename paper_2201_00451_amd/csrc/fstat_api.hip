@@ -14,6 +14,7 @@
 
 #include "fstat_common.hpp"
 #include "fstat_fft.hpp"
+#include "fstat_launch.hpp"
 #include "fstat_prologue.hpp"
 #include "fstat_resample.hpp"
 #include "fstat_adjoint.hpp"
@@ -679,7 +680,8 @@ size_t grad_slot_bytes(const fstat_plan* p) {
 // The gradient kernels and the single-bin transforms come in pairs, one for
 // the templates whose timing is smooth over a tile (span) and one that solves
 // every point; which one a template takes is known on the device only, so both
-// are launched and each skips the other's templates.
+// are launched and each skips the other's templates (a plan that admits no
+// spans launches none).
 using GradFn = void (*)(PlanConst, void*);
 template <bool ONEHOT, bool KEP>
 GradFn grad_kernel_o(int D, bool span) {
@@ -701,35 +703,62 @@ GradFn grad_kernel(const fstat_plan* p, bool onehot, bool span) {
 }
 
 using BinFn = void (*)(PlanConst, void*, ChunkMap, const int64_t*);
-template <bool KEP>
-BinFn bin_kernel_k(int D, bool span) {
+template <bool KEP, bool WALK>
+BinFn bin_kernel_k(int D) {
   switch (D) {
-    case 4: return span ? &k_bin_span<4, KEP> : &k_resample_bin<4, KEP>;
-    case 6: return span ? &k_bin_span<6, KEP> : &k_resample_bin<6, KEP>;
-    case 8: return span ? &k_bin_span<8, KEP> : &k_resample_bin<8, KEP>;
-    case 10: return span ? &k_bin_span<10, KEP> : &k_resample_bin<10, KEP>;
-    case 12: return span ? &k_bin_span<12, KEP> : &k_resample_bin<12, KEP>;
-    case 16: return span ? &k_bin_span<16, KEP> : &k_resample_bin<16, KEP>;
+    case 4: return &k_resample_bin<4, KEP, WALK>;
+    case 6: return &k_resample_bin<6, KEP, WALK>;
+    case 8: return &k_resample_bin<8, KEP, WALK>;
+    case 10: return &k_resample_bin<10, KEP, WALK>;
+    case 12: return &k_resample_bin<12, KEP, WALK>;
+    case 16: return &k_resample_bin<16, KEP, WALK>;
     default: return nullptr;
   }
 }
-BinFn bin_kernel(const fstat_plan* p, bool span) {
-  return kepler_plan(p) ? bin_kernel_k<true>(p->desc.sinc_halfwidth, span)
-                        : bin_kernel_k<false>(p->desc.sinc_halfwidth, span);
+template <bool KEP>
+BinFn bin_span_kernel_k(int D) {
+  switch (D) {
+    case 4: return &k_bin_span<4, KEP>;
+    case 6: return &k_bin_span<6, KEP>;
+    case 8: return &k_bin_span<8, KEP>;
+    case 10: return &k_bin_span<10, KEP>;
+    case 12: return &k_bin_span<12, KEP>;
+    case 16: return &k_bin_span<16, KEP>;
+    default: return nullptr;
+  }
 }
-// Blocks per template of a pair's kernels: spans of kSpanTiles tiles, and at
-// most 256 blocks that walk the tiles.
+BinFn bin_kernel(const fstat_plan* p, bool walk) {
+  const int D = p->desc.sinc_halfwidth;
+  if (kepler_plan(p)) return walk ? bin_kernel_k<true, true>(D) : bin_kernel_k<true, false>(D);
+  return walk ? bin_kernel_k<false, true>(D) : bin_kernel_k<false, false>(D);
+}
+BinFn bin_span_kernel(const fstat_plan* p) {
+  const int D = p->desc.sinc_halfwidth;
+  return kepler_plan(p) ? bin_span_kernel_k<true>(D) : bin_span_kernel_k<false>(D);
+}
+// Blocks per template of the span kernels.
 unsigned span_blocks(const fstat_plan* p) {
   return unsigned((p->k_pad / kResTile + kSpanTiles - 1) / kSpanTiles);
 }
-unsigned walk_blocks(const fstat_plan* p) {
-  return unsigned(std::min<int64_t>(p->k_pad / kResTile, 256));
+void launch_bin(const fstat_plan* p, const PlanConst& P, const ChunkMap& map, const int64_t* bins,
+                void* ws, hipStream_t st) {
+  const int n = map.n_tmpl;
+  const int64_t tiles = p->k_pad / kResTile;
+  if (spans_possible(P))
+    hipLaunchKernelGGL(bin_span_kernel(p), dim3(span_blocks(p), n), dim3(kResThreads),
+                       span_lds_bytes(p->desc.ndet), st, P, ws, map, bins);
+  const unsigned blocks = point_blocks(tiles, n, spans_possible(P));
+  hipLaunchKernelGGL(bin_kernel(p, blocks < tiles), dim3(blocks, n), dim3(kResThreads), 0, st, P,
+                     ws, map, bins);
 }
 void launch_grad(const fstat_plan* p, const PlanConst& P, bool onehot, int n, void* ws,
                  hipStream_t st) {
-  hipLaunchKernelGGL(grad_kernel(p, onehot, true), dim3(span_blocks(p), n), dim3(kResThreads),
-                     span_lds_bytes(p->desc.ndet), st, P, ws);
-  hipLaunchKernelGGL(grad_kernel(p, onehot, false), dim3(walk_blocks(p), n), dim3(kResThreads), 0,
+  const bool spans = spans_possible(P);
+  if (spans)
+    hipLaunchKernelGGL(grad_kernel(p, onehot, true), dim3(span_blocks(p), n), dim3(kResThreads),
+                       span_lds_bytes(p->desc.ndet), st, P, ws);
+  hipLaunchKernelGGL(grad_kernel(p, onehot, false),
+                     dim3(point_blocks(p->k_pad / kResTile, n, spans), n), dim3(kResThreads), 0,
                      st, P, ws);
 }
 
@@ -751,10 +780,7 @@ fstat_status launch_grad_bin_chunk(const fstat_plan* p, const PlanConst& P,
   const unsigned tiles = unsigned(p->k_pad / kResTile);
   hipLaunchKernelGGL(k_prologue, dim3(n), dim3(kParamThreads), 0, st, P, templates, map, ws,
                      map.tmpl[0] == 0);
-  hipLaunchKernelGGL(bin_kernel(p, true), dim3(span_blocks(p), n), dim3(kResThreads),
-                     span_lds_bytes(p->desc.ndet), st, P, ws, map, bins);
-  hipLaunchKernelGGL(bin_kernel(p, false), dim3(walk_blocks(p), n), dim3(kResThreads), 0, st, P,
-                     ws, map, bins);
+  launch_bin(p, P, map, bins, ws, st);
   hipLaunchKernelGGL(k_bin_final, dim3(n), dim3(kFinalThreads), 0, st, P, ws, map,
                      int64_t(tiles), bins, twoF);
   launch_grad(p, P, true, n, ws, st);

@@ -145,12 +145,17 @@ constexpr double kSpanCurve = 1.5e-3;      // phase over the taps of one side, r
 // sample.  Below w dt D = 1.5e-3 the term is under 6e-8, the rounding of the
 // FP32 sums; above, it is carried (kTileCurved), and the one of third order is
 // under 2e-8 up to the 0.3 rad and D = 16.
+// spans_possible: what the plan alone decides (no template of a plan with more
+// than 0.05 rad of rotation per half tile takes spans, so none are launched).
+__host__ __device__ inline bool spans_possible(const PlanConst& P) {
+  return 2.0 * kPi * P.sid_rate_cyc * 0.5 * kResTile * P.dt <= kSpanAngle;
+}
 __host__ __device__ inline int32_t tile_form(const PlanConst& P, double om_b, double ecc,
                                              int32_t knot_log2) {
   const double half = 0.5 * kResTile * P.dt;
   const double sid = 2.0 * kPi * P.sid_rate_cyc;
   const double w = om_b / ((1.0 - ecc) * (1.0 - ecc));
-  if (knot_log2 < kKnotLogGlobal || !(sid * half <= kSpanAngle) ||
+  if (knot_log2 < kKnotLogGlobal || !spans_possible(P) ||
       !(w * half <= (ecc > 0.0 ? kSpanOrbitKepler : kSpanOrbit)))
     return kTilePoints;
   return fmax(w, sid) * P.dt * double(P.D) <= kSpanCurve ? kTileSmooth : kTileCurved;

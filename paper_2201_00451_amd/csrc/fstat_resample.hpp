@@ -1086,9 +1086,11 @@ __host__ __device__ inline int64_t band_bin_nat(const PlanConst& P, int64_t i) {
 // m per template as a direct sum over the grid, sum_k y'_k exp(-2 pi i m k/N)
 // (step (vi) restricted to one output bin), reduced per tile into the slot's
 // partials (Fa'.re, Fa'.im, Fb'.re, Fb'.im in FP64).  The templates whose
-// timing is solved point by point (the others: k_bin_span); a block walks
-// tiles.
-template <int D, bool KEP>
+// timing is solved point by point (the others: k_bin_span).
+// One tile per block unless WALK: in a loop the kernel spills 28 registers
+// instead of 16 and takes 1096 us where it took 993 (32 templates of 1 M
+// points).
+template <int D, bool KEP, bool WALK>
 __global__ __launch_bounds__(kResThreads, 4) void k_resample_bin(PlanConst P, void* ws, ChunkMap map,
                                                              const int64_t* __restrict__ bins) {
   const int slot = blockIdx.y;
@@ -1101,7 +1103,8 @@ __global__ __launch_bounds__(kResThreads, 4) void k_resample_bin(PlanConst P, vo
   __shared__ double red[kResThreads / 64][4];
   const int64_t nat = band_bin_nat(P, bins[map.tmpl[slot]]);
   const int64_t tiles = P.k_pad / kResTile;
-  for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+  int64_t t = blockIdx.x;
+  do {
     double* partial = slot_partials(ws, P, slot) + size_t(t) * 8;
     const int64_t k_s = t * kResTile;
     float2 acc_a[kResPerThread], acc_b[kResPerThread];
@@ -1131,8 +1134,8 @@ __global__ __launch_bounds__(kResThreads, 4) void k_resample_bin(PlanConst P, vo
       for (int w = 0; w < kResThreads / 64; ++w) v += red[w][tid];
       partial[tid] = v;
     }
-    __syncthreads();
-  }
+    if constexpr (WALK) __syncthreads();
+  } while (WALK && (t += gridDim.x) < tiles);
 }
 
 // Per-template totals of per-tile partials (8 doubles per tile, the first

@@ -237,3 +237,24 @@ def test_gradients_near_the_band_edge(torch_dev, D, share):
         err = np.abs(got.cpu().numpy()[0] - ref) / np.abs(ref)
         print("  ", dict(zip(G.PARAMS, err)), flush=True)
         assert np.all(err[4:] <= 10 * 6e-8 * 16)
+
+
+def test_point_by_point_launches(torch_dev):
+    """Single-bin gradients of templates solved point by point (an orbit of 24
+    minutes): a launch of many templates, whose blocks walk the tiles, gives the
+    bits of one template at a time, a block per tile."""
+    from paper_2201_00451_amd import binding
+    ds = synth.small_case(seed=61, n=530001, dt=2.0, n_fft=1 << 20, ndet=2, binary=True, ntmpl=32,
+                          n_bins=4096, bin_lo=1 << 19)
+    ds.templates[:, 5] = 0.001 * (1 + 1e-4 * np.arange(32))
+    ds.templates[:, 6] = 1440.0
+    ds = synth.finish(ds)
+    assert 2 * np.pi / 1440.0 * 256 * ds.dt > 0.3
+    dd = binding.DeviceData(ds)
+    assert dd.plan.info()[0] // 512 > 32768 // 32
+    bins = [100 * i for i in range(32)]
+    many, tf_many = binding.compute_2f_grad_bin(dd, ds.templates, bins, batch=32)
+    one, tf_one = binding.compute_2f_grad_bin(dd, ds.templates, bins, batch=1)
+    binding.sync_check()
+    assert torch_dev.isfinite(many).all()
+    assert torch_dev.equal(many, one) and torch_dev.equal(tf_many, tf_one)

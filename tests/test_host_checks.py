@@ -32,3 +32,7 @@ def test_prologue_sky_derivatives(tmp_path):
 
 def test_span_rule_bounds_the_quintics(tmp_path):
     run_host(tmp_path, "span_rule")
+
+
+def test_launch_rules(tmp_path):
+    run_host(tmp_path, "launch_rules")
