@@ -921,8 +921,11 @@ fstat_status search_launch(fstat_search* sr, const fstat_inputs* in, const doubl
   fstat_status s0 = tm.open(0);
   if (s0 != FSTAT_OK) return s0;
   const int64_t nt = std::max<int64_t>(sr->ntmpl, sr->slots);
-  hipLaunchKernelGGL(k_params, dim3(unsigned(nt)), dim3(kParamThreads), 0, st, P, templates,
+  const ParamGrid pg = param_grid(nt);
+  hipLaunchKernelGGL(k_params, dim3(pg.x, pg.y), dim3(kParamThreads), 0, st, P, templates,
                      sr->ntmpl, ws, sr->slots, out);
+  // no chunk may read parameter blocks that were not written
+  if ((s0 = check_hip(hipGetLastError(), "parameter launch")) != FSTAT_OK) return s0;
   for (const ChunkMap& map : sr->chunks) {
     fstat_status s = launch_chunk(p, P, templates, map, sr->slots, true, out, nullptr, ws, st, tm);
     if (s != FSTAT_OK) return s;

@@ -23,4 +23,16 @@ inline unsigned point_blocks(int64_t tiles, int64_t n, bool spans) {
   return unsigned(std::min(tiles, std::max<int64_t>(256, kPointBlocks / std::max<int64_t>(n, 1))));
 }
 
+// Grid of k_params for n templates (and status words), one block each: a
+// dimension of a launch holds fewer than 2^32 threads, which blocks of 128 pass
+// at 2^25 templates, so the second one carries on from 2^16 on.  (A walk of the
+// templates in a loop took 206 registers instead of 110.)
+struct ParamGrid {
+  unsigned x, y;
+};
+inline ParamGrid param_grid(int64_t n) {
+  const int64_t x = std::max<int64_t>(1, std::min<int64_t>(n, 1 << 16));
+  return {unsigned(x), unsigned(std::max<int64_t>(1, (n + x - 1) / x))};
+}
+
 }  // namespace fstat

@@ -465,12 +465,12 @@ __global__ __launch_bounds__(kParamThreads) void k_prologue(PlanConst P,
 // per-template array P.params, the status words of the group buffers cleared
 // for the first chunk, and the flagged-template counter, the candidate count
 // and the per-template maxima of the run cleared (in a kernel, so that a
-// captured graph needs no memset).
+// captured graph needs no memset).  One block per template (param_grid).
 __global__ __launch_bounds__(kParamThreads) void k_params(PlanConst P,
                                                           const double* __restrict__ templates,
                                                           int64_t ntmpl, void* ws, int slots,
                                                           RowOutput out) {
-  const int64_t t = blockIdx.x;
+  const int64_t t = int64_t(blockIdx.y) * gridDim.x + blockIdx.x;
   if (threadIdx.x == 0) {
     if (t < slots) *group_status(ws, P, slots, int(t)) = 0;
     if (t == 0) *flag_counter(ws) = 0ull;

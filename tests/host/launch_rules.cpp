@@ -1,8 +1,11 @@
 // Host-only checks of the launch rules (fstat_launch.hpp).  Built and run by
 // tests/test_host_checks.py; no GPU is touched.
+#include <hip/hip_runtime.h>
+
 #include <cstdio>
 
 #include "fstat_launch.hpp"
+#include "fstat_prologue.hpp"
 
 using namespace fstat;
 
@@ -28,8 +31,21 @@ static void point_launch() {
     }
 }
 
+// The parameter launch has a block for every template of any bank, and each of
+// its dimensions stays below 2^32 threads (65535 blocks in the second one).
+static void param_launch() {
+  for (int64_t n : {int64_t(0), int64_t(1), int64_t(11), int64_t(65536), int64_t(65537),
+                    (int64_t(1) << 25) - 1, int64_t(1) << 25, int64_t(3000000001)}) {
+    const ParamGrid g = param_grid(n);
+    check(g.x >= 1 && int64_t(g.x) * g.y >= n, "a block per template");
+    check(int64_t(g.x) * kParamThreads < int64_t(1) << 32 && g.y <= 65535, "launch limits");
+    if (n > 0) check(int64_t(g.x) * (g.y - 1) < n, "no empty row of blocks");
+  }
+}
+
 int main() {
   point_launch();
+  param_launch();
   printf(fails ? "FAIL\n" : "OK\n");
   return fails != 0;
 }

@@ -258,3 +258,23 @@ def test_point_by_point_launches(torch_dev):
     binding.sync_check()
     assert torch_dev.isfinite(many).all()
     assert torch_dev.equal(many, one) and torch_dev.equal(tf_many, tf_one)
+
+
+def test_parameter_blocks_of_a_large_bank(torch_dev):
+    """A bank of more templates than the first dimension of the parameter launch
+    holds: every template's loudest bin is the one of a search of its own few
+    neighbours."""
+    from paper_2201_00451_amd import binding
+    ds = synth.small_case(seed=71, n=2000, n_fft=1 << 12, ndet=1, ntmpl=1, f1dot=0.0)
+    n = (1 << 16) + 300
+    rows = np.repeat(ds.templates, n, axis=0)
+    rows[:, 3] = 1e-9 * (np.arange(n) - n // 2) / n
+    dd = binding.DeviceData(ds)
+    many = binding.Search(dd, rows, slots=32).run_candidates(60.0, capacity=16)
+    binding.sync_check()
+    assert many["best_twoF"].numel() == n and torch_dev.isfinite(many["best_twoF"]).all()
+    for lo, hi in ((0, 64), ((1 << 16) - 32, (1 << 16) + 32), (n - 33, n)):
+        few = binding.Search(dd, rows[lo:hi], slots=32).run_candidates(60.0, capacity=16)
+        binding.sync_check()
+        assert torch_dev.equal(many["best_twoF"][lo:hi], few["best_twoF"])
+        assert torch_dev.equal(many["best_bin"][lo:hi], few["best_bin"])
