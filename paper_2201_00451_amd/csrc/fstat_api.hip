@@ -221,13 +221,6 @@ FftVariant pick_rows(int logl, bool half, int mode, bool few) {
          : mode == kRowCand  ? pick_rows_m<kRowCand>(logl, half, few)
                              : pick_rows_m<kRow2F>(logl, half, few);
 }
-// The forward epilogue a RowOutput needs: plain 2F stores, candidates and
-// loudest bin without a 2F array, or the extended one.
-int forward_row_mode(const RowOutput& out) {
-  if (out.twoF && !out.fafb && !out.cand && !out.best && !out.acc) return kRow2F;
-  if (!out.twoF && !out.fafb && !out.acc && (out.cand || out.best)) return kRowCand;
-  return kRow2FExt;
-}
 
 FftChoice cols_choice(const fstat_plan* p) { return {p->cols_half, p->fft_mlr}; }
 
@@ -553,6 +546,9 @@ fstat_status launch_chunk(const fstat_plan* p, const PlanConst& P, const double*
                           float2* y_out, void* ws, hipStream_t st, KernelTimer& tm) {
   fstat_status s;
   const int n = map.n_tmpl;
+  const int mode = forward_row_mode(out);
+  if (mode < 0)
+    return fail(FSTAT_EINTERNAL, "no row pass both writes arrays and keeps candidates");
   if (!grouped) {
     // the grouped (search) path computed every parameter block up front
     if ((s = tm.open(0)) != FSTAT_OK) return s;
@@ -561,7 +557,7 @@ fstat_status launch_chunk(const fstat_plan* p, const PlanConst& P, const double*
   }
   const int n_res = grouped ? map.n_grp : n;
   const FftVariant cv = cols_for(p, grouped, n);
-  const FftVariant rv = rows_for(p, forward_row_mode(out), n);
+  const FftVariant rv = rows_for(p, mode, n);
   if (!resample_kernel(p, grouped) || !timing_kernel(p, grouped) || !cv.fn || !rv.fn)
     return fail(FSTAT_EINTERNAL, "no kernel for D=%d, FFT lines 2^%d x 2^%d",
                 p->desc.sinc_halfwidth, p->log_rr, p->log_c);

@@ -216,6 +216,17 @@ constexpr int32_t kStatusBin = 32;      // single-bin path: bin outside the band
 // Bits that concern the resampled series of a sky/orbit group.
 constexpr int32_t kStatusGroupMask = kStatusTiming | kStatusCoverage | kStatusWindow | kStatusNodes;
 
+// Row-pass epilogues.  kRow2F: 2F only (the plain full-band output).
+// kRow2FExt: 2F stored or summed, Fa and Fb.  kRowCand: candidates and loudest
+// bin, no array.  kRowAdjoint: the adjoint spectrum H = g conj(F') of both
+// arrays at every natural FFT index m (zero outside the band), written to
+// arrays 2 and 3 of the slot, with 2F if twoF is not null.  kRowConj: the
+// complex transform itself, conjugated, written to arrays 0 and 1 at the
+// natural index for indices below k_pad (the inverse transform of the adjoint).
+// (At the half line count kRowCand runs k_fft_rows in its kRow2FExt form, which
+// serves whatever outputs are there.)
+enum RowMode { kRow2F = 0, kRowAdjoint = 1, kRowConj = 2, kRow2FExt = 3, kRowCand = 4 };
+
 // Where the row pass puts its results (passed by value).  twoF: full band
 // (stored, or added when acc is set); fafb: Fa and Fb; gin: adjoint weights;
 // cand/count/cap/threshold: bins with 2F above the threshold appended to a

@@ -11,9 +11,10 @@
 // Inside a pass, lines are transformed in LDS by a mixed-radix Stockham
 // autosort: every thread holds whole radix-R butterflies (R <= 32) in
 // registers; the first stage reads HBM and the last one writes it.  Stage
-// twiddles come from a constant FP32 table copied to LDS; the four-step twiddles from the exact quarter-turn split of
-// their exponent and the rotation polynomials.  The HBM traffic is one read
-// and one write of the series per pass.
+// twiddles come from a constant FP32 table copied to LDS; the four-step
+// twiddles from the exact quarter-turn split of their exponent and the
+// rotation polynomials.  The HBM traffic is one read and one write of the
+// series per pass.
 #pragma once
 
 #include "fstat_common.hpp"
@@ -526,18 +527,7 @@ __global__ __launch_bounds__(NT, NT / 128) void k_fft_cols_half(PlanConst P, voi
 // the last stage leaves the a and b values of the same bins in one thread,
 // which writes 2F (rows fastest across threads: RQ-element runs of the
 // output).  Items: (Rr / RQ) row groups x template slots.
-// Row-pass epilogues: 2F (forward); the adjoint spectrum H = g conj(F') of
-// both arrays at every natural FFT index m (zero outside the band), written to
-// arrays 2 and 3 of the slot, with 2F if twoF is not null; or the complex
-// transform itself, conjugated, written to arrays 0 and 1 at the natural
-// index for indices below k_pad (the inverse transform of the adjoint).
-// kRow2F stores 2F only (the plain full-band output); kRow2FExt is the same
-// transform with every optional output of RowOutput (Fa/Fb, accumulation,
-// candidates, loudest bin).
-// Row epilogues: plain 2F stores; the adjoint's two; the extended forward one
-// (Fa/Fb, accumulation, candidates, loudest bin); candidates and loudest bin
-// only (no 2F array).
-enum RowMode { kRow2F = 0, kRowAdjoint = 1, kRowConj = 2, kRow2FExt = 3, kRowCand = 4 };
+// RowMode (fstat_common.hpp) names the epilogues.
 
 // 2F = 2 (|Fa'|^2 + |Fb'|^2) with explicit FMA, so that every epilogue gives
 // the same bits.

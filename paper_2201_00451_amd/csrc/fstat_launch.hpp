@@ -5,6 +5,8 @@
 #include <algorithm>
 #include <cstdint>
 
+#include "fstat_common.hpp"
+
 namespace fstat {
 
 // Blocks per template of the kernels that solve every point (k_resample_bin,
@@ -33,6 +35,15 @@ struct ParamGrid {
 inline ParamGrid param_grid(int64_t n) {
   const int64_t x = std::max<int64_t>(1, std::min<int64_t>(n, 1 << 16));
   return {unsigned(x), unsigned(std::max<int64_t>(1, (n + x - 1) / x))};
+}
+
+// The forward epilogue a RowOutput needs: plain 2F stores; candidates and
+// loudest bin; Fa and Fb or sums (and nothing at all).  No row pass writes
+// arrays and keeps candidates in one transform: -1, which the launch refuses.
+inline int forward_row_mode(const RowOutput& out) {
+  const bool keeps = out.cand || out.best, stores = out.twoF || out.fafb || out.acc;
+  if (keeps) return stores ? -1 : int(kRowCand);
+  return out.twoF && !out.fafb && !out.acc ? kRow2F : kRow2FExt;
 }
 
 }  // namespace fstat

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
+#include <cstring>
 
 #include "fstat_launch.hpp"
 #include "fstat_prologue.hpp"
@@ -43,9 +44,32 @@ static void param_launch() {
   }
 }
 
+// Every set of outputs goes to an epilogue that writes all of them.
+static void row_modes() {
+  float f;
+  float2 f2;
+  fstat_candidate c;
+  unsigned long long u;
+  for (int m = 0; m < 32; ++m) {
+    RowOutput o;
+    std::memset(&o, 0, sizeof o);
+    if (m & 1) o.twoF = &f;
+    if (m & 2) o.fafb = &f2;
+    if (m & 4) o.cand = &c;
+    if (m & 8) o.best = &u;
+    if (m & 16) o.acc = 1;
+    const int mode = forward_row_mode(o);
+    const bool stores = m & 19, keeps = m & 12;
+    if (stores && keeps) check(mode == -1, "arrays and candidates in one transform");
+    else if (keeps) check(mode == kRowCand, "candidates");
+    else check(mode == (m == 1 ? kRow2F : kRow2FExt), "arrays");
+  }
+}
+
 int main() {
   point_launch();
   param_launch();
+  row_modes();
   printf(fails ? "FAIL\n" : "OK\n");
   return fails != 0;
 }
