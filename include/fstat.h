@@ -90,10 +90,13 @@ typedef struct {
    *     log2(n_fft) - tune_col_log_len; both must lie in [6, 12];
    *   tune_col_lines: columns per workgroup of the column pass: the largest
    *     count that fits 128 KiB of LDS (512 threads, one workgroup per compute
-   *     unit) or half of it (256 threads, two per unit: the automatic choice);
+   *     unit) or half of it (256 threads, two per unit).  Automatic: half while
+   *     that leaves 8 columns, else the largest; for columns of up to 2^9
+   *     points a quarter of it in launches too small to fill the chip;
    *   tune_row_lines: rows per workgroup of the row pass (the a and b rows
-   *     together): the largest count (512 threads: the automatic choice) or
-   *     half of it (256 threads);
+   *     together): the largest count (512 threads) or half of it (256 threads).
+   *     Automatic: the largest; for rows of up to 2^9 points a quarter of it
+   *     in launches too small to fill the chip;
    *   tune_fft_radix: largest radix of a column-pass stage, 16 or 32 (automatic:
    *     32, so lines of 2^9 and 2^10 points take two stages). */
   int32_t tune_col_log_len;
@@ -342,9 +345,11 @@ FSTAT_API fstat_status fstat_sinc_halfwidth_for(double band_fraction, double tol
                                                 double* err_2f);
 
 /* Launch-shape autotuner: for the set-up *desc (its tune fields ignored),
- * times every FFT launch shape the plan accepts (both column/row splits of
- * n_fft around its square root, full or half line counts for each pass,
- * radix-16 or radix-32 stage plans of the column pass) by running the batched path
+ * times the FFT launch shapes worth telling apart (both column/row splits of
+ * n_fft around its square root; for each pass the full and the half line count,
+ * where lines have up to 2^9 points the automatic count, 0, in place of the one
+ * it would otherwise take; radix-16 and radix-32 stage plans for columns of 2^9
+ * and 2^10 points) by running the batched path
  * on the given sample of templates (device [ntmpl][8], ntmpl >= 1; twoF a
  * device [ntmpl][n_bins] scratch output) with the given workspace, once
  * untimed and once timed with HIP events, and returns the fastest

@@ -68,13 +68,6 @@ int ilog2(int64_t v) {
   return l;
 }
 
-// Lines per workgroup of the column pass (NL) and rows per workgroup of the
-// row pass (RQ): at most as many as fit 128 KiB of LDS, capped for
-// coalescing, with 512 threads; or half of that with 256 threads, so that two
-// workgroups share a compute unit.
-int cols_lines_max(int log_rr) { return std::min(64, 16384 >> log_rr); }
-int rows_lines_max(int log_c) { return std::min(32, 8192 >> log_c); }
-
 using ColsFn = void (*)(PlanConst, void*, ChunkMap, int, int, int, int64_t);
 using RowsFn = void (*)(PlanConst, void*, ChunkMap, int, int, RowOutput);
 
@@ -134,9 +127,8 @@ constexpr int kSplitMinLogRr = 11;
 bool blocked_inter(const fstat_plan* p) {
   return p->cols_lines == 1 << kColBlock && p->log_c >= kBlockMinLogC && p->log_rr >= 10;
 }
-// Lines whose passes have a variant for small launches: short ones.
 template <int LOGL>
-constexpr bool kFewLines = LOGL <= 9;
+constexpr bool kFewLines = LOGL <= kFewMaxLog;
 template <int LOGL, bool GROUPED, int MLR>
 FftVariant cols_variant(bool half, bool few) {
   if constexpr (kFewLines<LOGL>)
@@ -220,6 +212,16 @@ FftVariant pick_rows(int logl, bool half, int mode, bool few) {
          : mode == kRow2FExt ? pick_rows_m<kRow2FExt>(logl, half, few)
          : mode == kRowCand  ? pick_rows_m<kRowCand>(logl, half, few)
                              : pick_rows_m<kRow2F>(logl, half, few);
+}
+
+// *desc with the launch shape of an autotuner's candidate.
+fstat_plan_desc shaped(const fstat_plan_desc* desc, const TuneShape& shape) {
+  fstat_plan_desc d = *desc;
+  d.tune_col_log_len = shape.col_log_len;
+  d.tune_col_lines = shape.col_lines;
+  d.tune_row_lines = shape.row_lines;
+  d.tune_fft_radix = shape.radix;
+  return d;
 }
 
 FftChoice cols_choice(const fstat_plan* p) { return {p->cols_half, p->fft_mlr}; }
@@ -1398,50 +1400,35 @@ fstat_status fstat_autotune(const fstat_plan_desc* desc, const fstat_inputs* in,
     (void)hipEventDestroy(e0);
     return s;
   }
-  const int log_n = ilog2(desc->n_fft);
-  const int splits[2] = {log_n / 2, (log_n + 1) / 2};
   float best_t = INFINITY;
   fstat_plan_desc cand_best = *desc;
   fstat_status last = FSTAT_OK;
   std::string last_msg;
-  for (int si = 0; si < 2; ++si) {
-    if (si == 1 && splits[1] == splits[0]) break;
-    const int lr = splits[si], lc = log_n - lr;
-    if (lr < 6 || lr > 12 || lc < 6 || lc > 12) continue;
-    for (int ch = 0; ch < 2; ++ch)
-      for (int rh = 0; rh < 2; ++rh)
-        for (int radix = 16; radix <= 32; radix *= 2) {
-          fstat_plan_desc d = *desc;
-          d.tune_col_log_len = lr;
-          d.tune_col_lines = ch ? cols_lines_max(lr) / 2 : cols_lines_max(lr);
-          d.tune_row_lines = rh ? rows_lines_max(lc) / 2 : rows_lines_max(lc);
-          d.tune_fft_radix = radix;
-          if (d.tune_col_lines < 1 || d.tune_row_lines < 1) continue;
-          fstat_plan* p = nullptr;
-          if (fstat_plan_create(&d, &p) != FSTAT_OK) continue;
-          float ms = INFINITY;
-          // one untimed run, then one timed with events on the stream
-          fstat_status r = run(p, in, templates, ntmpl, twoF, nullptr, nullptr, workspace,
-                               ws_bytes, stream, int64_t(1) << 40);
-          if (r == FSTAT_OK) r = check_hip(hipEventRecord(e0, st), "event record");
-          if (r == FSTAT_OK)
-            r = run(p, in, templates, ntmpl, twoF, nullptr, nullptr, workspace, ws_bytes,
-                    stream, int64_t(1) << 40);
-          if (r == FSTAT_OK) r = check_hip(hipEventRecord(e1, st), "event record");
-          if (r == FSTAT_OK) r = check_hip(hipEventSynchronize(e1), "event synchronise");
-          if (r == FSTAT_OK) r = check_hip(hipEventElapsedTime(&ms, e0, e1), "event time");
-          fstat_plan_destroy(p);
-          if (r != FSTAT_OK) {
-            last = r;
-            last_msg = g_err;
-            if (r == FSTAT_EHIP) break;
-            continue;
-          }
-          if (ms < best_t) {
-            best_t = ms;
-            cand_best = d;
-          }
-        }
+  for (const TuneShape& shape : tune_shapes(ilog2(desc->n_fft))) {
+    const fstat_plan_desc d = shaped(desc, shape);
+    fstat_plan* p = nullptr;
+    if (fstat_plan_create(&d, &p) != FSTAT_OK) continue;
+    float ms = INFINITY;
+    // one untimed run, then one timed with events on the stream
+    fstat_status r = run(p, in, templates, ntmpl, twoF, nullptr, nullptr, workspace, ws_bytes,
+                         stream, int64_t(1) << 40);
+    if (r == FSTAT_OK) r = check_hip(hipEventRecord(e0, st), "event record");
+    if (r == FSTAT_OK)
+      r = run(p, in, templates, ntmpl, twoF, nullptr, nullptr, workspace, ws_bytes, stream,
+              int64_t(1) << 40);
+    if (r == FSTAT_OK) r = check_hip(hipEventRecord(e1, st), "event record");
+    if (r == FSTAT_OK) r = check_hip(hipEventSynchronize(e1), "event synchronise");
+    if (r == FSTAT_OK) r = check_hip(hipEventElapsedTime(&ms, e0, e1), "event time");
+    fstat_plan_destroy(p);
+    if (r != FSTAT_OK) {
+      last = r;
+      last_msg = g_err;
+      continue;
+    }
+    if (ms < best_t) {
+      best_t = ms;
+      cand_best = d;
+    }
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
@@ -1588,39 +1575,24 @@ fstat_status fstat_autotune_search(const fstat_plan_desc* desc, const fstat_inpu
   }
   if (!in) return fail(FSTAT_EINVAL, "inputs is NULL");
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const int log_n = ilog2(desc->n_fft);
-  const int splits[2] = {log_n / 2, (log_n + 1) / 2};
   float best_t = INFINITY;
   fstat_plan_desc cand_best = *desc;
   fstat_status last = FSTAT_OK;
   std::string last_msg;
-  for (int si = 0; si < 2; ++si) {
-    if (si == 1 && splits[1] == splits[0]) break;
-    const int lr = splits[si], lc = log_n - lr;
-    if (lr < 6 || lr > 12 || lc < 6 || lc > 12) continue;
-    for (int ch = 0; ch < 2; ++ch)
-      for (int rh = 0; rh < 2; ++rh)
-        for (int radix = 16; radix <= 32; radix *= 2) {
-          fstat_plan_desc d = *desc;
-          d.tune_col_log_len = lr;
-          d.tune_col_lines = ch ? cols_lines_max(lr) / 2 : cols_lines_max(lr);
-          d.tune_row_lines = rh ? rows_lines_max(lc) / 2 : rows_lines_max(lc);
-          d.tune_fft_radix = radix;
-          if (d.tune_col_lines < 1 || d.tune_row_lines < 1) continue;
-          fstat_status r;
-          const float ms = time_search_shape(d, in, templates_host, templates, ntmpl, slots,
-                                             repeats, twoF, st, &r);
-          if (r != FSTAT_OK) {
-            last = r;
-            last_msg = g_err;
-            if (r == FSTAT_EHIP) break;
-            continue;
-          }
-          if (ms < best_t) {
-            best_t = ms;
-            cand_best = d;
-          }
-        }
+  for (const TuneShape& shape : tune_shapes(ilog2(desc->n_fft))) {
+    const fstat_plan_desc d = shaped(desc, shape);
+    fstat_status r;
+    const float ms = time_search_shape(d, in, templates_host, templates, ntmpl, slots, repeats,
+                                       twoF, st, &r);
+    if (r != FSTAT_OK) {
+      last = r;
+      last_msg = g_err;
+      continue;
+    }
+    if (ms < best_t) {
+      best_t = ms;
+      cand_best = d;
+    }
   }
   if (!(best_t < INFINITY))
     return fail(last != FSTAT_OK ? last : FSTAT_EINVAL, "autotune: no launch shape ran (%s)",

@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <vector>
 
 #include "fstat_common.hpp"
 
@@ -44,6 +45,44 @@ inline int forward_row_mode(const RowOutput& out) {
   const bool keeps = out.cand || out.best, stores = out.twoF || out.fafb || out.acc;
   if (keeps) return stores ? -1 : int(kRowCand);
   return out.twoF && !out.fafb && !out.acc ? kRow2F : kRow2FExt;
+}
+
+// Lines per workgroup of the column pass (NL) and rows per workgroup of the
+// row pass (RQ): at most as many as fit 128 KiB of LDS, capped for
+// coalescing, with 512 threads; or half of that with 256 threads, so that two
+// workgroups share a compute unit.
+inline int cols_lines_max(int log_rr) { return std::min(64, 16384 >> log_rr); }
+inline int rows_lines_max(int log_c) { return std::min(32, 8192 >> log_c); }
+
+// Lines of up to 2^9 points have a variant for launches that leave the chip
+// idle (cols_for, rows_for), which only the automatic line count takes.
+constexpr int kFewMaxLog = 9;
+
+// The launch shapes the autotuners time for transforms of 2^log_n points: both
+// splits around the square root, for each pass two line counts, and both
+// column stage plans where they differ (2^9 and 2^10 points).  The line counts
+// are the automatic one and the one it does not take where lines are short (a
+// fixed count never takes the small items of a small launch), else the full
+// and the half count.
+struct TuneShape {
+  int col_log_len, col_lines, row_lines, radix;
+};
+inline std::vector<TuneShape> tune_shapes(int log_n) {
+  std::vector<TuneShape> out;
+  for (int lr = log_n / 2; lr <= (log_n + 1) / 2; ++lr) {
+    const int lc = log_n - lr;
+    if (lr < 6 || lr > 12 || lc < 6 || lc > 12) continue;
+    const int cmax = cols_lines_max(lr), rmax = rows_lines_max(lc);
+    const int cols[2] = {lr <= kFewMaxLog ? 0 : cmax / 2, cmax};
+    const int rows[2] = {lc <= kFewMaxLog ? 0 : rmax, rmax / 2};
+    for (int c : cols)
+      for (int r : rows)
+        for (int radix : {32, 16}) {
+          if (radix == 16 && lr != 9 && lr != 10) continue;
+          out.push_back({lr, c, r, radix});
+        }
+  }
+  return out;
 }
 
 }  // namespace fstat

@@ -66,10 +66,40 @@ static void row_modes() {
   }
 }
 
+// The autotuners time every shape once, and the automatic line counts wherever
+// those have small-launch items of their own.
+static void autotuned_shapes() {
+  for (int log_n = 12; log_n <= 24; ++log_n) {
+    const auto shapes = tune_shapes(log_n);
+    check(!shapes.empty(), "shapes to time");
+    for (int lr = log_n / 2; lr <= (log_n + 1) / 2; ++lr) {
+      const int lc = log_n - lr, cmax = cols_lines_max(lr), rmax = rows_lines_max(lc);
+      bool automatic = false, full = false;
+      for (size_t i = 0; i < shapes.size(); ++i) {
+        const TuneShape& a = shapes[i];
+        if (a.col_log_len != lr) continue;
+        check(a.col_lines == 0 || a.col_lines == cmax || a.col_lines == cmax / 2, "column lines");
+        check(a.row_lines == 0 || a.row_lines == rmax || a.row_lines == rmax / 2, "row lines");
+        check(a.radix == 32 || (a.radix == 16 && (lr == 9 || lr == 10)), "stage plan");
+        automatic |= a.col_lines == (lr <= 9 ? 0 : cmax / 2) && a.row_lines == (lc <= 9 ? 0 : rmax);
+        full |= a.col_lines == cmax && a.row_lines == rmax / 2;
+        for (size_t j = 0; j < i; ++j) {
+          const TuneShape& b = shapes[j];
+          check(a.col_log_len != b.col_log_len || a.col_lines != b.col_lines ||
+                    a.row_lines != b.row_lines || a.radix != b.radix,
+                "a shape timed twice");
+        }
+      }
+      check(automatic && full, "the default shape and the opposite one");
+    }
+  }
+}
+
 int main() {
   point_launch();
   param_launch();
   row_modes();
+  autotuned_shapes();
   printf(fails ? "FAIL\n" : "OK\n");
   return fails != 0;
 }
