@@ -333,40 +333,72 @@ __host__ __device__ inline void whitened_coef(const DetConst& d, const Jks& k, c
   }
 }
 
-// Per template, serially (the kernels spread the same pieces over a block):
-// the row's parameters, A, B, C of eq. Fstat and their sky derivatives, the
-// whitened coefficients.
-__host__ __device__ inline void template_params(const PlanConst& P, const double* row,
-                                                TmplParams& tp) {
-  row_params(P, row, tp);
-  double sa, ca, sd, cdl;
-  sincos(row[0], &sa, &ca);
-  sincos(row[1], &sd, &cdl);
-  double m[kMatrixTerms] = {0.0};
-  for (int X = 0; X < P.ndet; ++X)
-    for (int t = 0; t < kMatrixTerms; ++t)
-      m[t] += matrix_term(P.det[X], P.moments + X * 10, jks_coeffs(P.det[X], sd, cdl), sa, ca, t);
+// The first wave's share of a parameter block (block_params), in two phases with
+// every lane's term[][] written between them.  matrix_lane: one matrix term per
+// lane (detector x term).  coef_lane: every lane sums the terms over the
+// detectors and whitens; lane 0 writes the factor and its status bit, and each
+// lane one coefficient (detector x coefficient; zeros past the last detector).
+constexpr int kParamLanes = 64;
+static_assert(kMaxDet * kMatrixTerms <= kParamLanes && kMaxDet * 5 <= kParamLanes,
+              "one wave holds the terms and the coefficients");
+struct SkyAngles {
+  double sa, ca, sd, cd;  // sin and cos of alpha and delta
+};
+__host__ __device__ inline SkyAngles sky_angles(const double* row) {
+  SkyAngles s;
+  sincos(row[0], &s.sa, &s.ca);
+  sincos(row[1], &s.sd, &s.cd);
+  return s;
+}
+__host__ __device__ inline void matrix_lane(const PlanConst& P, const SkyAngles& s, int lane,
+                                            double (&term)[kMaxDet][kMatrixTerms]) {
+  const int X = lane / kMatrixTerms, t = lane % kMatrixTerms;
+  if (X < P.ndet)
+    term[X][t] = matrix_term(P.det[X], P.moments + X * 10, jks_coeffs(P.det[X], s.sd, s.cd), s.sa,
+                             s.ca, t);
+}
+__host__ __device__ inline void coef_lane(const PlanConst& P, const SkyAngles& s, int lane,
+                                          const double (&term)[kMaxDet][kMatrixTerms],
+                                          TmplParams& tp) {
+  double m[kMatrixTerms];
+#pragma unroll
+  for (int t = 0; t < kMatrixTerms; ++t) {
+    m[t] = 0.0;
+    for (int X = 0; X < P.ndet; ++X) m[t] += term[X][t];
+  }
   const Whitening w = whiten(m);
-  if (!w.valid) tp.status |= kStatusTiming;
-  tp.l11 = static_cast<float>(w.l11);
-  tp.l21 = static_cast<float>(w.l21);
-  tp.l22 = static_cast<float>(w.l22);
-  for (int X = 0; X < kMaxDet; ++X)
-    for (int q = 0; q < 5; ++q) {
-      tp.ca[X][q] = tp.cb[X][q] = 0.0f;
-      tp.dca[0][X][q] = tp.dcb[0][X][q] = tp.dca[1][X][q] = tp.dcb[1][X][q] = 0.0f;
-      if (X < P.ndet)
-        whitened_coef(P.det[X], jks_coeffs(P.det[X], sd, cdl), w, X, q, tp);
-    }
+  if (lane == 0) {
+    tp.status |= w.valid ? 0 : kStatusTiming;
+    tp.l11 = static_cast<float>(w.l11);
+    tp.l21 = static_cast<float>(w.l21);
+    tp.l22 = static_cast<float>(w.l22);
+  }
+  const int X = lane / 5, q = lane % 5;
+  if (X < P.ndet) {
+    whitened_coef(P.det[X], jks_coeffs(P.det[X], s.sd, s.cd), w, X, q, tp);
+  } else if (X < kMaxDet) {
+    tp.ca[X][q] = tp.cb[X][q] = 0.0f;
+    tp.dca[0][X][q] = tp.dcb[0][X][q] = tp.dca[1][X][q] = tp.dcb[1][X][q] = 0.0f;
+  }
+}
+
+// A parameter block on the host (without the coverage check and the sky shift,
+// which read the trajectory): the row's parameters, then the lanes in turn.
+inline void template_params(const PlanConst& P, const double* row, TmplParams& tp) {
+  row_params(P, row, tp);
+  const SkyAngles s = sky_angles(row);
+  double term[kMaxDet][kMatrixTerms];
+  for (int lane = 0; lane < kParamLanes; ++lane) matrix_lane(P, s, lane, term);
+  for (int lane = 0; lane < kParamLanes; ++lane) coef_lane(P, s, lane, term, tp);
 }
 
 // Everything the kernels need about one template, by one block of
-// kParamThreads: template_params plus the coverage check of the source-frame
-// grid and the adjoint's sky shift.  The work is a chain of dependent FP64
+// kParamThreads: the row's parameters, the whitened coefficients, the coverage
+// check of the source-frame grid and the adjoint's sky shift.  The work is a chain of dependent FP64
 // operations (about 2000 per detector in one thread), so it is bound by their
 // latency and is split by what is independent: the first wave takes the
-// matrix terms, one per lane (detector x term), then the coefficients, one per
-// lane (detector x coefficient); the second wave solves the grid's ends, one
+// matrix terms and then the coefficients (matrix_lane, coef_lane), the second
+// solves the grid's ends, one
 // lane per detector and end, and projects the sky shift.  Measured, one
 // thread per template against one block: 1 template of 1 detector 11.0 to 6.5
 // us, 7 of 3 detectors 26.7 to 10.4 us, 16 eccentric ones of 2 detectors 30.7
@@ -376,7 +408,7 @@ __host__ __device__ inline void template_params(const PlanConst& P, const double
 // the interpolation taps of the last sample end before the last computed
 // point, so grid points beyond k_pad are exactly zero.
 constexpr int kParamThreads = 128;
-static_assert(kMaxDet * kMatrixTerms <= 64 && kMaxDet * 5 <= 64, "one wave holds the terms");
+static_assert(kParamThreads == 2 * kParamLanes, "two waves");
 static_assert(sizeof(TmplParams) % sizeof(uint64_t) == 0, "copied in 8-byte words");
 __device__ inline void block_params(const PlanConst& P, const double* __restrict__ row,
                                     TmplParams* __restrict__ out) {
@@ -385,15 +417,10 @@ __device__ inline void block_params(const PlanConst& P, const double* __restrict
   __shared__ double shift[2];
   const int lane = threadIdx.x & 63;
   const bool first = threadIdx.x < 64;
-  double sd = 0.0, cdl = 0.0;
+  SkyAngles sky{};
   if (first) {
-    double sa, ca;
-    sincos(row[0], &sa, &ca);
-    sincos(row[1], &sd, &cdl);
-    const int X = lane / kMatrixTerms, t = lane % kMatrixTerms;
-    if (X < P.ndet)
-      term[X][t] = matrix_term(P.det[X], P.moments + X * 10, jks_coeffs(P.det[X], sd, cdl), sa,
-                               ca, t);
+    sky = sky_angles(row);
+    matrix_lane(P, sky, lane, term);
   } else {
     TmplParams rp;
     row_params(P, row, rp);
@@ -422,27 +449,8 @@ __device__ inline void block_params(const PlanConst& P, const double* __restrict
   }
   __syncthreads();
   if (first) {
-    double m[kMatrixTerms];
-#pragma unroll
-    for (int t = 0; t < kMatrixTerms; ++t) {
-      m[t] = 0.0;
-      for (int X = 0; X < P.ndet; ++X) m[t] += term[X][t];
-    }
-    const Whitening w = whiten(m);
-    if (lane == 0) {
-      tp.status |= w.valid ? 0 : kStatusTiming;
-      tp.l11 = static_cast<float>(w.l11);
-      tp.l21 = static_cast<float>(w.l21);
-      tp.l22 = static_cast<float>(w.l22);
-    }
     if (lane < 2) tp.dshift[lane] = shift[lane];
-    const int X = lane / 5, q = lane % 5;
-    if (X < P.ndet) {
-      whitened_coef(P.det[X], jks_coeffs(P.det[X], sd, cdl), w, X, q, tp);
-    } else if (X < kMaxDet) {
-      tp.ca[X][q] = tp.cb[X][q] = 0.0f;
-      tp.dca[0][X][q] = tp.dcb[0][X][q] = tp.dca[1][X][q] = tp.dcb[1][X][q] = 0.0f;
-    }
+    coef_lane(P, sky, lane, term, tp);
   }
   __syncthreads();
   const uint64_t* src = reinterpret_cast<const uint64_t*>(&tp);

@@ -36,3 +36,7 @@ def test_span_rule_bounds_the_quintics(tmp_path):
 
 def test_launch_rules(tmp_path):
     run_host(tmp_path, "launch_rules")
+
+
+def test_parameter_block_lanes(tmp_path):
+    run_host(tmp_path, "parameter_lanes")
