@@ -278,3 +278,66 @@ def test_parameter_blocks_of_a_large_bank(torch_dev):
         binding.sync_check()
         assert torch_dev.equal(many["best_twoF"][lo:hi], few["best_twoF"])
         assert torch_dev.equal(many["best_bin"][lo:hi], few["best_bin"])
+
+
+@pytest.mark.parametrize("log_n,col,row_lines", [(21, 10, 0), (22, 11, 0), (23, 11, 1)])
+def test_flagged_template_and_fafb_with_column_blocks(torch_dev, log_n, col, row_lines):
+    """Searches with a blocked intermediate, plain and with its rows split: a
+    template with a spin-down that is no number is NaN in every bin of 2F, Fa
+    and Fb, counted once, and leaves its neighbours' bits alone."""
+    from paper_2201_00451_amd import binding
+    n_fft = 1 << log_n
+    lo, nb = n_fft // 3 + 1, n_fft // 3 + 7
+    ds = synth.small_case(seed=96, n=2500, n_fft=n_fft, ndet=2, gaps=True, ntmpl=5, rho=20,
+                          bin_lo=lo, n_bins=nb)
+    ds.templates[3, 3] = np.nan
+    dd = binding.DeviceData(ds, batch=5, tune=dict(tune_col_log_len=col, tune_col_lines=8,
+                                                   tune_row_lines=row_lines))
+    search = binding.Search(dd, ds.templates, slots=5)
+    got, ab = search.run(fafb=True)
+    plain = search.run()
+    flagged = binding.flagged_count(search.ws)
+    rep = search.run_candidates(1e9)
+    want, ab_want = binding.compute_2f_batched(dd, ds.templates, fafb=True)
+    binding.sync_check()
+    ok = [0, 1, 2, 4]
+    assert flagged == 1
+    for x, y in ((got, want), (plain, want), (ab, ab_want)):
+        assert torch_dev.equal(x[ok], y[ok]) and torch_dev.isfinite(torch_dev.abs(x[ok])).all()
+        assert torch_dev.isnan(torch_dev.abs(x[3])).all()
+    assert torch_dev.equal(rep["best_twoF"][ok], want[ok].max(dim=1).values)
+    assert torch_dev.isnan(rep["best_twoF"][3]) and rep["count"] == 0
+
+
+def test_spans_flag_windows_and_pass_bad_samples(torch_dev):
+    """The gradient kernels' spans: an orbit whose delay drifts by a fifth of a
+    tile, more than a tile's 616 staged samples hold (512 (1 + 0.2) + 2 D), is
+    flagged (NaN 2F and gradients), a neighbour is not touched by it; an infinite
+    and a NaN sample reach the results."""
+    from paper_2201_00451_amd import binding
+    ds = synth.small_case(seed=62, n=4001, n_fft=1 << 13, ndet=2, f_het=1.0, binary=True, ntmpl=2)
+    om = 5.5e-4
+    ds.templates[:, 5], ds.templates[:, 6] = [0.05, 0.2 / om], 2 * np.pi / om
+    ds.templates[:, 7] = 4000.0  # the largest rate in the middle of the data
+    ds = synth.finish(ds)
+    # the spans' conditions: knots at least 16 points apart, 0.3 rad per half tile
+    assert 32.0 ** 4 / 384 * (0.2 / om) * om ** 4 <= 2e-7 and om * 512 <= 0.3
+    ds.tau0 = synth.grid_origin(0.0, ds.dt, ds.max_delay)
+    dd = binding.DeviceData(ds)
+    bins = [4000, 4000]
+    w = np.zeros((2, ds.n_bins))
+    w[:, 4000] = 1.0
+    plain = binding.compute_2f(dd, ds.templates)
+    g_bin, tf_bin = binding.compute_2f_grad_bin(dd, ds.templates, bins)
+    g_gen = binding.compute_2f_grad(dd, ds.templates, w)
+    binding.sync_check()
+    for x in (plain, g_bin, tf_bin, g_gen):
+        assert torch_dev.isfinite(x[0]).all() and torch_dev.isnan(x[1]).all()
+    for bad in (np.nan, np.inf):
+        ds.x[1][1500] = bad
+        dd = binding.DeviceData(ds)
+        plain = binding.compute_2f(dd, ds.templates[:1])
+        g_bin, tf_bin = binding.compute_2f_grad_bin(dd, ds.templates[:1], bins[:1])
+        binding.sync_check()
+        for x in (plain, g_bin, tf_bin):
+            assert not torch_dev.isfinite(x).any()
