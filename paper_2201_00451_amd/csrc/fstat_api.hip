@@ -345,6 +345,7 @@ PlanConst make_const(const fstat_plan* p, const fstat_inputs* in) {
   P.n_bins = d.n_bins;
   P.k_pad = p->k_pad;
   P.knot_stride = knot_stride(p);
+  P.knot_gcap = knot_gcap(p);
   P.knot_ioff = knot_ioff(p);
   P.knot_soff = knot_soff(p);
   P.knot_toff = knot_toff(p);

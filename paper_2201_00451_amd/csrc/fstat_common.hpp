@@ -142,6 +142,7 @@ struct PlanConst {
   int64_t slot_stride;  // bytes per template slot of the workspace (path dependent)
   int64_t part_offset;  // adjoint paths: bytes from a slot's start to its tile partials
   int64_t knot_stride;  // 16-byte units per detector of a knot area
+  int64_t knot_gcap;    // grid intervals of a detector's area
   int64_t knot_ioff, knot_soff, knot_toff;  // units to the integers, sample intervals, tiles
   int32_t res_taylor;   // the tiles take the antenna patterns' Taylor form
   int32_t row_split;    // blocked, and a block's even rows come before its odd ones
@@ -259,19 +260,19 @@ struct ChunkMap {
 
 constexpr size_t kParamBytes = 1024;
 static_assert(sizeof(TmplParams) <= kParamBytes, "param block");
-// Workspace header: moment partials, then one page.
+// Workspace header: moment partials, then reserved space.
+constexpr int kTwLen = 4096;
 constexpr size_t kMomentBytes = size_t(kMaxDet) * kMomBlocks * 10 * sizeof(double);
-constexpr size_t kHeaderBytes = kMomentBytes + 4096;
-static_assert(kHeaderBytes % 256 == 0, "slots stay aligned");
-// In that page: the number of templates of the current call whose
+constexpr size_t kHeaderBytes = kMomentBytes + 3 * kTwLen * sizeof(float2) + 4096;
+// In the reserved space: the number of templates of the current call whose
 // outputs are NaN (cleared by the first kernel of every call, counted once
 // per template by the row pass or the single-bin reduction).
-constexpr size_t kFlagOffset = kMomentBytes;
+constexpr size_t kFlagOffset = kMomentBytes + 3 * kTwLen * sizeof(float2);
 __host__ __device__ inline unsigned long long* flag_counter(void* ws) {
   return reinterpret_cast<unsigned long long*>(static_cast<char*>(ws) + kFlagOffset);
 }
 
-// Workspace: header, then template slots of
+// Workspace: header (moment partials, twiddles), then template slots of
 // [TmplParams | narr arrays of n_fft float2 | extra bytes], narr = 2 for the
 // forward paths (y_a / Z_a, y_b / Z_b) and 4 plus per-tile gradient partials
 // for the adjoint.

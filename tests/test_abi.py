@@ -446,10 +446,3 @@ def test_sinc_halfwidth_for_accuracy_bound(lib):
             assert worst(smaller, frac) > tol
     with pytest.raises(B.FstatError):
         B.sinc_halfwidth_for(0.95, 1e-6)
-
-
-def test_workspace_header_holds_what_is_used(lib):
-    """Every workspace starts with the partial sums of the antenna moments
-    (four detectors, 256 blocks, ten FP64 sums) and one page, nothing else."""
-    p = B.Plan(good_desc()[1])
-    assert 2 * p.workspace_size(1) - p.workspace_size(2) == 4 * 256 * 10 * 8 + 4096
