@@ -84,10 +84,13 @@ static_assert(kMaxDet * 64 <= kResThreads, "one wave per detector");
 // (all detectors), as resample_span leaves them: zsa, recs, and the windows'
 // first samples ja.  node(X, lane, tau, re) is called by the lanes from
 // kNodeLane on with the source time of their derivative node.  False (uniform)
-// after flagging the template.
+// after flagging the template: also where a delay exceeds the plan's max_delay
+// by more than `reach` samples and one trajectory interval (the general kernels
+// stage the trajectory that far: k_resample_bin D + 2 + 64 samples, k_grad D + 2).
 template <int D, bool KEP, class Node>
 __device__ __forceinline__ bool span_solve(const PlanConst& P, const TmplParams& tp, int kl,
-                                           int32_t* status_word, int32_t t0, int n_t, float2* zsa,
+                                           int reach, int32_t* status_word, int32_t t0, int n_t,
+                                           float2* zsa,
                                            SpanRec* recs, SpanSolve& sv, int32_t (&ja)[kMaxDet],
                                            Node&& node) {
   const int tid = threadIdx.x;
@@ -96,10 +99,7 @@ __device__ __forceinline__ bool span_solve(const PlanConst& P, const TmplParams&
   const int G = 1 << kl;
   const int32_t k_s = t0 << kResTileLog;
   const int ng = ((n_t << kResTileLog) >> kl) + 1;
-  // a delay beyond what the ephemeris checks of the plan allow for (the
-  // tiles that solve every point flag one that leaves their staged nodes)
-  const double limit =
-      P.max_delay + double(D + 2 + (1 << kKnotLogMax)) * P.dt + P.eph_dt;
+  const double limit = P.max_delay + double(reach) * P.dt + P.eph_dt;
   if (tid == 0) sv.bad = 0;
   __syncthreads();
   const int X = w0 >> 6;
@@ -337,8 +337,8 @@ __global__ __launch_bounds__(kResThreads, 4) void k_bin_span(PlanConst P, void* 
   for (int32_t t0 = t_b; t0 < t_e; t0 += step) {
     const int n_t = t_e - t0 < step ? t_e - t0 : step;
     int32_t ja[kMaxDet];
-    if (!span_solve<D, KEP>(P, tp, kl, &tpp->status, t0, n_t, zs, recs, sv, ja,
-                            [](int, int, double, double2) {}))
+    if (!span_solve<D, KEP>(P, tp, kl, D + 2 + (1 << kKnotLogMax), &tpp->status, t0, n_t, zs, recs,
+                            sv, ja, [](int, int, double, double2) {}))
       return;
     {
       const int X = tid >> 6;
@@ -533,7 +533,7 @@ __device__ __forceinline__ void grad_span(const PlanConst& P, void* ws, float2* 
       o[4] = rbp * invb;
       o[5] = (1.0 + rbp) / (1.0 + rd);
     };
-    if (!span_solve<D, KEP>(P, tp, kl, &tpp->status, t0, n_t, zs, recs, sv, ja, node)) {
+    if (!span_solve<D, KEP>(P, tp, kl, D + 2, &tpp->status, t0, n_t, zs, recs, sv, ja, node)) {
       if (tid < 8)
         for (int t = t_b; t < t_e; ++t) partial[(t - t_b) * 8 + tid] = __builtin_nan("");
       return;

@@ -341,3 +341,29 @@ def test_spans_flag_windows_and_pass_bad_samples(torch_dev):
         binding.sync_check()
         for x in (plain, g_bin, tf_bin):
             assert not torch_dev.isfinite(x).any()
+
+
+@pytest.mark.parametrize("porb_d", [0.5, 0.016])  # spans; solved point by point
+def test_gradients_refuse_delays_beyond_the_bound(torch_dev, porb_d):
+    """Single-bin gradients of a template whose delays exceed max_delay by 145 s,
+    more than the taps (20 s at D = 8 and 2 s a sample) and two intervals of the
+    trajectory (60 s): NaN, in both forms of the kernels; at the bound: finite."""
+    from paper_2201_00451_amd import binding
+    ds = synth.small_case(seed=12, n=3000, n_fft=1 << 13, ndet=1, binary=True, ntmpl=1)
+    ds.templates[:, 5], ds.templates[:, 6] = 0.001, porb_d * synth.DAY
+    for excess in (0.0, 145.0):
+        ds = synth.finish(ds)
+        det = ds.detectors[0]
+        pos = synth.detector_pos_vel(ds.ephem_model, det, np.arange(-600.0, 7000.0, 10.0))[0]
+        # the sky position of the longest delays, opposite the Earth
+        mid = -pos[:, pos.shape[1] // 2]
+        row = ds.templates[0].copy()
+        row[0] = np.arctan2(mid[1], mid[0])
+        row[1] = np.arcsin(mid[2] / np.linalg.norm(mid))
+        longest = np.abs(synth.sky_unit(row[0], row[1]) @ pos).max() + row[5]
+        ds.max_delay = longest + 1.0 - excess
+        dd = binding.DeviceData(ds)
+        g, _ = binding.compute_2f_grad_bin(dd, row[None], [4000])
+        binding.sync_check()
+        assert bool(torch_dev.isfinite(g).all()) == (excess == 0.0)
+        assert bool(torch_dev.isnan(g).all()) == (excess > 0.0)
