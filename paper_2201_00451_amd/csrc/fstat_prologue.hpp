@@ -220,7 +220,6 @@ __host__ __device__ inline void row_params(const PlanConst& P, const double* row
       }
     }
   }
-  tp.tile_form = tile_form(P, tp.om_b, tp.ecc, tp.knot_log2);
   spindown_coefficients(P, tp.f1dot, tp.f2dot, tp.df, tp.sd);
   double sa, ca_, sd, cdl;
   sincos(alpha, &sa, &ca_);
@@ -386,6 +385,7 @@ __host__ __device__ inline void coef_lane(const PlanConst& P, const SkyAngles& s
 // which read the trajectory): the row's parameters, then the lanes in turn.
 inline void template_params(const PlanConst& P, const double* row, TmplParams& tp) {
   row_params(P, row, tp);
+  tp.tile_form = tile_form(P, tp.om_b, tp.ecc, tp.knot_log2);
   const SkyAngles s = sky_angles(row);
   double term[kMaxDet][kMatrixTerms];
   for (int lane = 0; lane < kParamLanes; ++lane) matrix_lane(P, s, lane, term);
@@ -451,6 +451,10 @@ __device__ inline void block_params(const PlanConst& P, const double* __restrict
   if (first) {
     if (lane < 2) tp.dshift[lane] = shift[lane];
     coef_lane(P, sky, lane, term, tp);
+  } else if (lane == 0) {
+    // (beside the first wave's coefficients; in row_params it delayed the grid's
+    // ends, 0.4 us of 9.5 with three detectors)
+    tp.tile_form = tile_form(P, tp.om_b, tp.ecc, tp.knot_log2);
   }
   __syncthreads();
   const uint64_t* src = reinterpret_cast<const uint64_t*>(&tp);
