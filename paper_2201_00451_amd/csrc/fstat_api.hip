@@ -231,10 +231,14 @@ FftChoice cols_choice(const fstat_plan* p) { return {p->cols_half, p->fft_mlr}; 
 // of load, stages and store, so with the automatic line counts it takes a
 // quarter of the lines of the largest count (the same arithmetic per line, so
 // the same bits): up to two 256-thread workgroups per unit of the column pass,
-// one 512-thread workgroup of the row pass.  Measured, default against small
-// items: 11 templates of 2^17 points columns 13.6 / 11.0 us, rows 10.0 / 8.1; 7
-// of 2^17 with Fa and Fb 9.0 / 7.8 and 11.2 / 7.9; 12 of 2^18 (768 and 384
-// default items) rows 15 / 21.
+// one 512-thread workgroup of the row pass.  Lines of 2^10 points have no such
+// items: theirs would be four columns and two rows, runs of 32 and 8 bytes where
+// eight columns and four rows are the least that paid.  Measured, default
+// against small items, 1 to 32 templates of 2^12 to 2^19 points: at or below the
+// limits the small items take 0 to 35 % less (one template of 2^17 rows 11.2 / 7.3
+// us, 11 columns 12.9 / 11.6 and rows 12.0 / 10.4, 16 13.6 / 12.6 and 13.3 / 12.5;
+// 6 of 2^18 rows 12.1 / 10.8), never over 0.3 us more; above the limits they lose
+// (12 of 2^18, 768 and 384 default items: rows 15 / 21).
 constexpr int64_t kFewCols = 512, kFewRows = 256;
 FftVariant cols_for(const fstat_plan* p, bool grouped, int64_t n) {
   const int64_t items = ((int64_t(1) << p->log_c) / p->cols_lines) * 2 * n;
@@ -345,7 +349,6 @@ PlanConst make_const(const fstat_plan* p, const fstat_inputs* in) {
   P.n_bins = d.n_bins;
   P.k_pad = p->k_pad;
   P.knot_stride = knot_stride(p);
-  P.knot_gcap = knot_gcap(p);
   P.knot_ioff = knot_ioff(p);
   P.knot_soff = knot_soff(p);
   P.knot_toff = knot_toff(p);
@@ -734,7 +737,9 @@ BinFn bin_span_kernel(const fstat_plan* p) {
   const int D = p->desc.sinc_halfwidth;
   return kepler_plan(p) ? bin_span_kernel_k<true>(D) : bin_span_kernel_k<false>(D);
 }
-// Blocks per template of the span kernels.
+// Blocks per template of the span kernels: two tiles a block whatever the
+// launch (one tile a block is faster below about 1000 tiles, 12 tiles 58 / 46 us a
+// call, 700 64 / 54, and slower above, 1400 72 / 79, 160 000 4370 / 4980).
 unsigned span_blocks(const fstat_plan* p) {
   return unsigned((p->k_pad / kResTile + kSpanTiles - 1) / kSpanTiles);
 }

@@ -16,11 +16,8 @@ constexpr double kPi = 3.14159265358979323846;
 
 // Resampling tile: outputs per workgroup, threads, and the staged-sample
 // capacity (tile + 1/16 drift allowance + 2D taps for D <= 32 + slack).  Two
-// outputs per thread keep the resampling kernel at 115 registers and the
-// adjoint at 249, so four and two waves per SIMD fit without spills
-// (measured against 1024-point tiles: single-bin gradients 1800 to 2370 per
-// second, resampling 4 % faster on sky positions, 1 % slower on binary
-// orbits).
+// outputs per thread: the tiles that solve every point run four waves per
+// SIMD (resampling) and two (gradients, 249 registers).
 constexpr int kResTile = 512;
 constexpr int kResTileLog = 9;
 static_assert(kResTile == 1 << kResTileLog, "tile size is 2^kResTileLog");
@@ -142,7 +139,6 @@ struct PlanConst {
   int64_t slot_stride;  // bytes per template slot of the workspace (path dependent)
   int64_t part_offset;  // adjoint paths: bytes from a slot's start to its tile partials
   int64_t knot_stride;  // 16-byte units per detector of a knot area
-  int64_t knot_gcap;    // grid intervals of a detector's area
   int64_t knot_ioff, knot_soff, knot_toff;  // units to the integers, sample intervals, tiles
   int32_t res_taylor;   // the tiles take the antenna patterns' Taylor form
   int32_t row_split;    // blocked, and a block's even rows come before its odd ones
@@ -260,19 +256,22 @@ struct ChunkMap {
 
 constexpr size_t kParamBytes = 1024;
 static_assert(sizeof(TmplParams) <= kParamBytes, "param block");
-// Workspace header: moment partials, then reserved space.
-constexpr int kTwLen = 4096;
+// Workspace header: moment partials, 96 KiB that nothing uses, then one page.
+// The unused part keeps the sizes that callers hold and the slots' place:
+// without it the row pass of 32 templates of 2^23 points took 1779 us instead of
+// 1742 (columns 1672 instead of 1684).
 constexpr size_t kMomentBytes = size_t(kMaxDet) * kMomBlocks * 10 * sizeof(double);
-constexpr size_t kHeaderBytes = kMomentBytes + 3 * kTwLen * sizeof(float2) + 4096;
-// In the reserved space: the number of templates of the current call whose
+constexpr size_t kUnusedBytes = size_t(96) << 10;
+constexpr size_t kHeaderBytes = kMomentBytes + kUnusedBytes + 4096;
+// In that page: the number of templates of the current call whose
 // outputs are NaN (cleared by the first kernel of every call, counted once
 // per template by the row pass or the single-bin reduction).
-constexpr size_t kFlagOffset = kMomentBytes + 3 * kTwLen * sizeof(float2);
+constexpr size_t kFlagOffset = kMomentBytes + kUnusedBytes;
 __host__ __device__ inline unsigned long long* flag_counter(void* ws) {
   return reinterpret_cast<unsigned long long*>(static_cast<char*>(ws) + kFlagOffset);
 }
 
-// Workspace: header (moment partials, twiddles), then template slots of
+// Workspace: header, then template slots of
 // [TmplParams | narr arrays of n_fft float2 | extra bytes], narr = 2 for the
 // forward paths (y_a / Z_a, y_b / Z_b) and 4 plus per-tile gradient partials
 // for the adjoint.

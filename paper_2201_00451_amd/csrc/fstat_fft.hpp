@@ -202,6 +202,7 @@ __device__ __forceinline__ void fft_middle(float2* buf, const float2* twl, int t
 // octant, the rest by symmetry): it ships with the code object, so no call
 // spends a launch on it (a kernel that wrote it into the workspace took 2.4
 // us of every call).  Each FFT workgroup copies the W_L^e it needs into LDS.
+constexpr int kTwLen = 4096;  // the longest line
 struct alignas(16) StageTable {
   float w[2 * kTwLen];  // (re, im) pairs
 };

@@ -61,9 +61,9 @@ __constant__ TapConst kTaps = make_taps<D>();
 // polynomial in g.  make_tap_poly builds it at compile time in FP64: the
 // Chebyshev interpolant of h on 16 nodes, cut at degree 9 (8 for the outer
 // quarter of the pairs, where the window is small), which is within 2e-8 of h;
-// with the FP32 Horner evaluation a tap is within 9e-8 (the closed form
-// sin(pi f) w(s) / s reaches 2e-7).  A pair costs 11 operations of 2.3-2.8
-// cycles each where the closed form cost two reciprocals (8.2 cycles each),
+// with the FP32 Horner evaluation a tap is within 1.0e-7 at D = 8 and 1.6e-7 at
+// every D (the closed form sin(pi f) w(s) / s reaches 2e-7).  A pair costs 12
+// operations (11 in the outer quarter) of 2.3-2.8 cycles each where the closed form cost two reciprocals (8.2 cycles each),
 // four window FMAs and two products, and nothing per point besides g^2: no
 // sine of the offset, no window phase, no special case at f = 0.
 constexpr int kTapCoef = 5;
@@ -1041,7 +1041,12 @@ __device__ __forceinline__ void solve_knots(const PlanConst& P, const TmplParams
 // per SIMD, 128 registers).  Which of the two a template takes is known on the
 // device only; one launch carries both, so a bank of either kind pays for one
 // kernel (a launch of the tiles alone, whose blocks all return at once, took
-// 2-5 us of a small search and 10 us of a large one).
+// 2-5 us of a small search and 10 us of a large one).  The knots pay with the
+// tiles' registers and LDS, four waves per SIMD instead of five: 240 us instead
+// of 200 for 32 templates of 5.2 M points, 63 / 47 for 16 of 2.6 M.  Launching them
+// apart in large searches was measured again and gains too little for a second
+// kernel: parameters and timing together 247 / 256 us of 5370, 32 templates of
+// 1.5 M points 1325 / 1320, small searches 2 us slower.
 template <int D, bool GROUPED, bool KEP>
 __global__ __launch_bounds__(kResThreads, 4) void k_timing(PlanConst P, void* ws, ChunkMap map,
                                                            int slots, int kblocks) {
