@@ -355,6 +355,7 @@ PlanConst make_const(const fstat_plan* p, const fstat_inputs* in) {
   P.knot_bytes = int64_t(knot_area_bytes(p));
   P.res_taylor = std::fabs(2.0 * M_PI * P.sid_rate_cyc * d.dt) * double(kResTile / 2 + 1) <=
                  kTaylorMaxAngle;
+  tile_limits(P);
   // the plain forward path's slot layout; the search and the adjoint paths
   // set their own
   P.slot_stride = int64_t(plain_slot_bytes(p));

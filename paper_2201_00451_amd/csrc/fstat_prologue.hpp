@@ -145,20 +145,25 @@ constexpr double kSpanCurve = 1.5e-3;      // phase over the taps of one side, r
 // sample.  Below w dt D = 1.5e-3 the term is under 6e-8, the rounding of the
 // FP32 sums; above, it is carried (kTileCurved), and the one of third order is
 // under 2e-8 up to the 0.3 rad and D = 16.
-// spans_possible: what the plan alone decides (no template of a plan with more
-// than 0.05 rad of rotation per half tile takes spans, so none are launched).
-__host__ __device__ inline bool spans_possible(const PlanConst& P) {
-  return 2.0 * kPi * P.sid_rate_cyc * 0.5 * kResTile * P.dt <= kSpanAngle;
-}
-__host__ __device__ inline int32_t tile_form(const PlanConst& P, double om_b, double ecc,
-                                             int32_t knot_log2) {
+//
+// tile_limits (host): the limits as angular rates, so that the kernel compares
+// only; a plan with more than 0.05 rad of rotation per half tile admits no spans
+// at all (span_w < 0) and launches none.
+inline void tile_limits(PlanConst& P) {
   const double half = 0.5 * kResTile * P.dt;
   const double sid = 2.0 * kPi * P.sid_rate_cyc;
-  const double w = om_b / ((1.0 - ecc) * (1.0 - ecc));
-  if (knot_log2 < kKnotLogGlobal || !spans_possible(P) ||
-      !(w * half <= (ecc > 0.0 ? kSpanOrbitKepler : kSpanOrbit)))
-    return kTilePoints;
-  return fmax(w, sid) * P.dt * double(P.D) <= kSpanCurve ? kTileSmooth : kTileCurved;
+  const bool spans = sid * half <= kSpanAngle;
+  P.span_w = spans ? kSpanOrbit / half : -1.0;
+  P.curve_w = kSpanCurve / (P.dt * double(P.D));
+  if (sid > P.curve_w) P.curve_w = -1.0;
+}
+inline bool spans_possible(const PlanConst& P) { return P.span_w >= 0.0; }
+__host__ __device__ inline int32_t tile_form(const PlanConst& P, double om_b, double ecc,
+                                             int32_t knot_log2) {
+  const double e2 = (1.0 - ecc) * (1.0 - ecc);
+  const double lim = (ecc > 0.0 ? kSpanOrbitKepler / kSpanOrbit : 1.0) * P.span_w;
+  if (knot_log2 < kKnotLogGlobal || !(om_b <= lim * e2)) return kTilePoints;
+  return om_b <= P.curve_w * e2 ? kTileSmooth : kTileCurved;
 }
 
 // A template's row: orbit, knot spacing, spin-down phase, sky vector and its

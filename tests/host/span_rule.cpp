@@ -29,6 +29,7 @@ int main() {
   std::memset(&P, 0, sizeof P);
   P.dt = 1.0;
   P.D = 8;
+  tile_limits(P);
   const NodeFit fit = make_node_fit();
   double worst = 0.0;
   for (double ecc : {0.0, 0.02, 0.1, 0.2, 0.3, 0.4, 0.5, 0.6, 0.8}) {
