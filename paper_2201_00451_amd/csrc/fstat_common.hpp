@@ -139,7 +139,7 @@ struct PlanConst {
   int64_t slot_stride;  // bytes per template slot of the workspace (path dependent)
   int64_t part_offset;  // adjoint paths: bytes from a slot's start to its tile partials
   int64_t knot_stride;  // 16-byte units per detector of a knot area
-  double span_w;        // limit of tile_form (tile_limits)
+  float span_w, curve_w;  // limits of tile_form (tile_limits)
   int64_t knot_ioff, knot_soff, knot_toff;  // units to the integers, sample intervals, tiles
   int32_t res_taylor;   // the tiles take the antenna patterns' Taylor form
   int32_t row_split;    // blocked, and a block's even rows come before its odd ones
@@ -152,7 +152,6 @@ struct PlanConst {
   double eph_t0, eph_dt, inv_eph_dt;
   const double* moments;
   DetConst det[kMaxDet];
-  double curve_w;       // limit of tile_form (tile_limits)
 };
 
 // Per-template constants, one block per workspace slot.

@@ -152,18 +152,17 @@ constexpr double kSpanCurve = 1.5e-3;      // phase over the taps of one side, r
 inline void tile_limits(PlanConst& P) {
   const double half = 0.5 * kResTile * P.dt;
   const double sid = 2.0 * kPi * P.sid_rate_cyc;
-  const bool spans = sid * half <= kSpanAngle;
-  P.span_w = spans ? kSpanOrbit / half : -1.0;
-  P.curve_w = kSpanCurve / (P.dt * double(P.D));
-  if (sid > P.curve_w) P.curve_w = -1.0;
+  const double curve = kSpanCurve / (P.dt * double(P.D));
+  P.span_w = sid * half <= kSpanAngle ? float(kSpanOrbit / half) : -1.0f;
+  P.curve_w = sid <= curve ? float(curve) : -1.0f;
 }
-inline bool spans_possible(const PlanConst& P) { return P.span_w >= 0.0; }
+inline bool spans_possible(const PlanConst& P) { return P.span_w >= 0.0f; }
 __host__ __device__ inline int32_t tile_form(const PlanConst& P, double om_b, double ecc,
                                              int32_t knot_log2) {
   const double e2 = (1.0 - ecc) * (1.0 - ecc);
-  const double lim = (ecc > 0.0 ? kSpanOrbitKepler / kSpanOrbit : 1.0) * P.span_w;
+  const double lim = (ecc > 0.0 ? kSpanOrbitKepler / kSpanOrbit : 1.0) * double(P.span_w);
   if (knot_log2 < kKnotLogGlobal || !(om_b <= lim * e2)) return kTilePoints;
-  return om_b <= P.curve_w * e2 ? kTileSmooth : kTileCurved;
+  return om_b <= double(P.curve_w) * e2 ? kTileSmooth : kTileCurved;
 }
 
 // A template's row: orbit, knot spacing, spin-down phase, sky vector and its
@@ -413,6 +412,7 @@ inline void template_params(const PlanConst& P, const double* row, TmplParams& t
 // the interpolation taps of the last sample end before the last computed
 // point, so grid points beyond k_pad are exactly zero.
 constexpr int kParamThreads = 128;
+constexpr int kParamRowLog = 16;  // log2 of the templates in a row of k_params' blocks
 static_assert(kParamThreads == 2 * kParamLanes, "two waves");
 static_assert(sizeof(TmplParams) % sizeof(uint64_t) == 0, "copied in 8-byte words");
 __device__ inline void block_params(const PlanConst& P, const double* __restrict__ row,
@@ -487,7 +487,7 @@ __global__ __launch_bounds__(kParamThreads) void k_params(PlanConst P,
                                                           const double* __restrict__ templates,
                                                           int64_t ntmpl, void* ws, int slots,
                                                           RowOutput out) {
-  const int64_t t = int64_t(blockIdx.y) * gridDim.x + blockIdx.x;
+  const int64_t t = (int64_t(blockIdx.y) << kParamRowLog) + blockIdx.x;
   if (threadIdx.x == 0) {
     if (t < slots) *group_status(ws, P, slots, int(t)) = 0;
     if (t == 0) *flag_counter(ws) = 0ull;

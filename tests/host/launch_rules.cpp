@@ -39,6 +39,7 @@ static void param_launch() {
                     (int64_t(1) << 25) - 1, int64_t(1) << 25, int64_t(3000000001)}) {
     const ParamGrid g = param_grid(n);
     check(g.x >= 1 && int64_t(g.x) * g.y >= n, "a block per template");
+    check(g.y == 1 || g.x == 1u << kParamRowLog, "rows of the kernel's length");
     check(int64_t(g.x) * kParamThreads < int64_t(1) << 32 && g.y <= 65535, "launch limits");
     if (n > 0) check(int64_t(g.x) * (g.y - 1) < n, "no empty row of blocks");
   }
