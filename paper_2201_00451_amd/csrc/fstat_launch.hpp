@@ -29,10 +29,9 @@ inline unsigned point_blocks(int64_t tiles, int64_t n, bool spans) {
 
 // Grid of k_params for n templates (and status words), one block each: a
 // dimension of a launch holds fewer than 2^32 threads, which blocks of 128 pass
-// at 2^25 templates, so the second one carries on from 2^kParamRowLog on: a
-// constant, since reading the grid's size delayed every block (8.0 against 7.7
-// us for 11 templates; a walk of the templates in a loop took 206 registers
-// instead of 110).
+// at 2^25 templates, so the second one carries on from 2^kParamRowLog on (a
+// constant: the kernel need not read the grid's size).  A walk of the templates
+// in a loop took 206 registers instead of 110.
 struct ParamGrid {
   unsigned x, y;
 };
