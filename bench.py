@@ -40,10 +40,10 @@ METRIC = "templates/s (full-band 2F) & % HBM roofline, batched vs plain, rel err
 # header and build flags with this digest; for any other version the
 # roofline reports traffic as null.
 MEASURED_TRAFFIC = {
-    "sources_sha256": "86893e7221d92b932e52b8eb5c6a174c272a19769c8573477d2a24167977684c",
+    "sources_sha256": "087003c13fe36d767623fbd68131d21adb30b4e7e4dae657755c8fc0195dd195",
     "bytes_per_template": {
-        "binary": {"resample": 190059765, "fft_columns": 260420974, "fft_rows_2f": 231387746},
-        "sky_spindown": {"resample": 3171116, "fft_columns": 48114543, "fft_rows_2f": 41978569},
+        "binary": {"resample": 228469283, "fft_columns": 222513196, "fft_rows_2f": 239674243},
+        "sky_spindown": {"resample": 3833309, "fft_columns": 47436855, "fft_rows_2f": 42031900},
     },
 }
 

@@ -15,12 +15,12 @@ namespace fstat {
 // k_grad), for n templates of `tiles` tiles: one block per tile where every
 // template takes them, and else (spans) while the launch stays below
 // kPointBlocks; a larger launch walks the tiles.  A template that takes the other
-// kernel of its pair leaves all its blocks empty, and 160 000 empty blocks of
-// both kernels cost 84 us (32 templates of 2.6 M points, 4350 us a call; under 20
-// at 32 768).  Walking costs 3 % (32 templates of 1 M points with a sample every 5
-// s 4510 us, 4360 with a block per tile), and 256 blocks per template are one
-// workgroup per compute unit where four fit (one template 326 us against 186,
-// two 373 / 319).
+// kernel of its pair leaves all its blocks empty: 160 000 of both kernels cost 100
+// us (32 templates of 2.6 M points, 4350 us a call), 32 768 cost 40, 8192 cost
+// 19.  Walking costs 3 % (32 templates of 1 M points with a sample every 5 s 4510
+// us, 4360 with a block per tile), and 256 blocks per template are one workgroup
+// per compute unit where four fit (one template 326 us against 186, two 373 /
+// 319).
 constexpr int64_t kPointBlocks = 32768;
 inline unsigned point_blocks(int64_t tiles, int64_t n, bool spans) {
   if (!spans) return unsigned(tiles);
