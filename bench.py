@@ -40,7 +40,7 @@ METRIC = "templates/s (full-band 2F) & % HBM roofline, batched vs plain, rel err
 # header and build flags with this digest; for any other version the
 # roofline reports traffic as null.
 MEASURED_TRAFFIC = {
-    "sources_sha256": "087003c13fe36d767623fbd68131d21adb30b4e7e4dae657755c8fc0195dd195",
+    "sources_sha256": "226b7a95a6fe8b15a6d1a2eadc40f2b84fd65708bbd2045f183c749c31adf075",
     "bytes_per_template": {
         "binary": {"resample": 228469283, "fft_columns": 222513196, "fft_rows_2f": 239674243},
         "sky_spindown": {"resample": 3833309, "fft_columns": 47436855, "fft_rows_2f": 42031900},

@@ -18,7 +18,7 @@ namespace fstat {
 // kernel of its pair leaves all its blocks empty: 160 000 of both kernels cost 100
 // us (32 templates of 2.6 M points, 4350 us a call), 32 768 cost 40, 8192 cost
 // 19.  Walking costs 3 % (32 templates of 1 M points with a sample every 5 s 4510
-// us, 4360 with a block per tile), and 256 blocks per template are one workgroup
+// us, 4395 with a block per tile), and 256 blocks per template are one workgroup
 // per compute unit where four fit (one template 326 us against 186, two 373 /
 // 319).
 constexpr int64_t kPointBlocks = 32768;
