@@ -367,3 +367,22 @@ def test_gradients_refuse_delays_beyond_the_bound(torch_dev, porb_d):
         binding.sync_check()
         assert bool(torch_dev.isfinite(g).all()) == (excess == 0.0)
         assert bool(torch_dev.isnan(g).all()) == (excess > 0.0)
+
+
+@pytest.mark.parametrize("half_tile", [0.178, 0.19])
+def test_eccentric_gradients_at_the_spans_limit(torch_dev, half_tile):
+    """Single-bin gradients of an eccentric orbit (0.4) on either side of the
+    limit of the quintics per tile, 0.18 rad of phase at periapsis per half tile,
+    against the FP64 oracle."""
+    from paper_2201_00451_amd import binding
+    ecc, dt = 0.4, 2.0
+    porb_d = 2 * np.pi * 256 * dt / (half_tile * (1 - ecc) ** 2) / synth.DAY
+    ds, row = orbit_case(porb_d, 0.1, 2, 8, 3000, ecc)
+    dd = binding.DeviceData(ds)
+    m = int(np.argmax(O.oracle_twoF(ds, row[None])[0]))
+    w = np.zeros(ds.n_bins)
+    w[m] = 1.0
+    _, ref = G.oracle_grad(ds, row, w)
+    got, _ = binding.compute_2f_grad_bin(dd, row[None], [m])
+    binding.sync_check()
+    assert np.all(np.abs(got.cpu().numpy()[0] - ref) <= GRAD_RTOL * np.abs(ref))
